@@ -905,21 +905,24 @@ aa_status agent_attn_bwd(const aa_desc* desc, const void* Q, const void* K, cons
     return AA_ERR_ALIAS;
 
   Problem pr = make_problem(desc, params);
-  // the kernels that keep no attention matrix in memory have the smaller workspace, so there is no falling back
-  // from them: they need aligned tensors (strided ones are staged into aligned copies)
-  if (aa::backward_fused_supported(pr) && !(aligned16(A) && aligned16(dA))) return AA_ERR_UNSUPPORTED;
-  if (aa::backward_fused_supported(pr) && dense_layout(desc) &&
-      !(aligned16(Q) && aligned16(K) && aligned16(V) && aligned16(dO) && aligned16(dQ) && aligned16(dK) && aligned16(dV)))
-    return AA_ERR_UNSUPPORTED;
+  const bool aligned = aligned16(Q) && aligned16(K) && aligned16(V) && aligned16(dO) && aligned16(dQ) && aligned16(dK) &&
+                       aligned16(dV) && aligned16(A) && aligned16(dA);
+  // a problem without agent bias and DWC has no path but the recomputing kernels (their workspace is the smaller one):
+  // they need aligned tensors (strided ones are staged into aligned copies when they are not)
+  if (aa::backward_pure_16bit(pr) && !(aligned16(A) && aligned16(dA))) return AA_ERR_UNSUPPORTED;
+  if (aa::backward_pure_16bit(pr) && dense_layout(desc) && !aligned) return AA_ERR_UNSUPPORTED;
+  // the recomputing kernels read strided tensors and windows where they lie
+  const bool in_place = aa::backward_fused_supported(pr) && aligned && layout_vectorizable(pr.lay) &&
+                        (!windowed(desc) || (int64_t)desc->N * desc->grid_w < ((int64_t)1 << 32));
   hipStream_t stream = (hipStream_t)hip_stream;
   char* ws = (char*)workspace;
-  // Strided tensors: the kernels below work on dense copies staged at the end of the workspace
+  // Strided tensors otherwise: the kernels below work on dense copies staged at the end of the workspace
   void* sdQ = nullptr;
   void* sdK = nullptr;
   void* sdV = nullptr;
   void *udQ = dQ, *udK = dK, *udV = dV;
   const Problem strided_pr = pr;
-  if (!dense_layout(desc)) {
+  if (!dense_layout(desc) && !in_place) {
     const size_t sb = bwd_stage_bytes(desc);
     char* stage = ws + need - 7 * sb;
     AA_HIP(aa::launch_restride(pr, true, false, Q, stage, stream));
@@ -946,7 +949,8 @@ aa_status agent_attn_bwd(const aa_desc* desc, const void* Q, const void* K, cons
     agents = ws;
   }
   const bool use_mfma = (pr.dtype == AA_F16 || pr.dtype == AA_BF16) && pr.d % 8 == 0 && aligned16(Q) && aligned16(K) &&
-                        aligned16(V) && aligned16(dO) && aligned16(agents);
+                        aligned16(V) && aligned16(dO) && aligned16(agents) &&
+                        (sdQ || (aligned16(dQ) && aligned16(dK) && aligned16(dV))) && aligned16(dA);
   AA_HIP(aa::launch_backward(pr, Q, K, V, agents, dO, (float*)(ws + bwd_agents_bytes(desc)), dQ, dK, dV, dA, !pooling,
                              use_mfma, pg, stream));
   if (sdQ) {

@@ -1,0 +1,130 @@
+// What the units of the recomputing backward share: kernel arguments, the agent-bias tables and the launchers.
+#pragma once
+#include "kernels.h"
+
+namespace aa {
+
+constexpr int kThreads = 256;       // four waves per block
+enum { kFwd = 0, kBc = 1, kAgg = 2, kBcStat = 3 };
+
+// Agent bias of one kind as the recomputing kernels read it (fp32, times log2 e; see backward_fused.inc):
+//   bias(a, (y, x)) = (1 - f) T[i][x][a] + f T[i + 1][x][a] + R[y][a]
+// T in two orders, wp = gw rounded up to 16 (columns past gw hold a score mask), ld agents (n rounded up, zeros):
+//   ta [heads][cells][ld / 4][wp][4 agents]     for lanes that hold a token and four agents
+//   tx [heads][cells][wp / 4][ld][4 columns]    for lanes that hold an agent and four neighbours in x
+// rows [heads][gh][ld], null when there is no row component.
+struct BiasTables {
+  const float *ta, *tx, *rows;
+  int cells, ld;
+};
+
+// Where a unit's rows start and which row a token is: Layout for the recomputing kernels, with 32-bit strides, every
+// division a multiplication and the windows behind one branch (at 10 us a kernel the scalar instructions ahead of its
+// first load show).
+struct UnitPlace {
+  uint32_t sb, sh, ob, oh;
+  int sn, on, heads, line;
+  uint32_t inv_heads, inv_nwin, inv_wxn, inv_ww;         // ceil(2^32 / divisor), 0 for a divisor of 1 (inv_ww: no windows)
+  int nwin, wxn, ww, win_rows;                           // win_rows: image rows of a window times line
+
+  static uint32_t inverse(int v) { return v > 1 ? (uint32_t)((((uint64_t)1 << 32) + v - 1) / v) : 0u; }
+  // strides below 2^32 elements; windows only where N * ww < 2^32
+  static bool fits(const Layout& l, int N) {
+    return (unsigned long long)l.sb >> 32 == 0 && (unsigned long long)l.sh >> 32 == 0 && (unsigned long long)l.ob >> 32 == 0 &&
+           (unsigned long long)l.oh >> 32 == 0 && (l.line == 0 || (unsigned long long)N * l.ww >> 32 == 0);
+  }
+  static UnitPlace make(const Layout& l, int heads) {
+    UnitPlace p{};
+    p.sb = (uint32_t)l.sb, p.sh = (uint32_t)l.sh, p.ob = (uint32_t)l.ob, p.oh = (uint32_t)l.oh;
+    p.sn = l.sn, p.on = l.on, p.heads = heads, p.line = l.line;
+    p.nwin = l.nwin, p.wxn = l.wxn, p.ww = l.line ? l.ww : 0, p.win_rows = l.wh * l.line;
+    p.inv_heads = inverse(heads), p.inv_nwin = inverse(l.nwin), p.inv_wxn = inverse(l.wxn);
+    p.inv_ww = l.line ? inverse(l.ww) : 0u;
+    return p;
+  }
+  // n / divisor for n * divisor < 2^32 (the product n * inv is then off by less than one part in 2^32 of a whole)
+  static __device__ __forceinline__ int quotient(int n, uint32_t inv) {
+    return inv == 0u ? n : (int)__umulhi((uint32_t)n, inv);
+  }
+  __device__ __forceinline__ int entry(int u) const { return quotient(u, inv_heads); }
+  __device__ __forceinline__ size_t base(int u, bool out) const {
+    const uint32_t bw = entry(u), hd = u - bw * heads;
+    uint32_t b = bw;
+    size_t at = (size_t)hd * (out ? oh : sh);
+    if (line != 0) {
+      b = quotient(bw, inv_nwin);
+      const int win = bw - b * nwin, wy = quotient(win, inv_wxn), wx = win - wy * wxn;
+      at += ((size_t)wy * (size_t)win_rows + (size_t)(wx * ww)) * (size_t)(out ? on : sn);
+    }
+    return at + (size_t)b * (out ? ob : sb);
+  }
+  __device__ __forceinline__ size_t row(int t) const {
+    if (line == 0) return (size_t)t;
+    const int y = quotient(t, inv_ww);
+    return (size_t)t + (size_t)((long long)y * (line - ww));
+  }
+  __device__ __forceinline__ int pitch(int gw) const { return line == 0 ? gw : line; }
+};
+
+struct TokenArgs {
+  const uint16_t *X, *Y, *M1, *M2;
+  const float *rs1, *rs2;
+  float *st1, *st2;
+  void *O1, *O2;
+  int N, n, d, n_rows, ch_rows;      // n_rows: n rounded up to 32; ch_rows: agents staged at a time (x32)
+  const float* dA;                   // kBc: the finished dA [units][n][d] when the agents were pooled (else null)
+  int gh, gw, ah, aw;                // token grid, the pooling's agent grid
+  float sc, oscale;
+  const uint16_t* G;      // kAgg: dO, for the share of dV that comes through the V residual (Appendix C.1: O += k V)
+  float vk;               //   and through the depthwise convolution (Eq. (6), dwc_w [heads][d][3][3] or null)
+  const float* dwc_w;
+  UnitPlace at;           // Q, K, V and the gradients lie with the input strides, dO with the output strides
+  BiasTables bt;          // with a bias only
+};
+
+struct AgentArgs {
+  const uint16_t *X, *Y, *M1, *M2;
+  const float *ts1, *ts2, *rs1, *rs2;
+  float *P1, *P2, *pm, *pl;
+  int N, n, d, chunk, S;      // chunk: tokens per range (without a bias)
+  float sc;
+  UnitPlace at;               // Q, K, V lie with the input strides, dO with the output strides
+  int gh, gw;
+  // with a bias: ranges are `per` of the `pairs` pairs of columns (see Walk in backward_fused.inc), a column being 16
+  // neighbours in x of the seg_len image rows of one of `segs` segments
+  int segs, seg_len, pairs, per;
+  BiasTables bt;
+  float *gt, *gr;             // parts of the gradients of T and R (null: not wanted), see BiasGradParts
+};
+
+// the kernels with a bias (backward_bias_{bf16,f16}.hip); prob kFwd .. kBcStat, dp 32 / 64 / 128, cols 16-agent columns
+// per wave
+template <class E>
+hipError_t launch_token_bias(int prob, int dp, const TokenArgs& a, dim3 grid, size_t lds, hipStream_t st);
+template <class E>
+hipError_t launch_agent_bias(int prob, int dp, int cols, const AgentArgs& a, dim3 grid, size_t lds, hipStream_t st);
+constexpr int kBiasTokenCols = 2;      // 16-token columns (image rows) per wave of the token kernels with a bias
+
+// --- backward_module.hip ---
+// Tables of one kind (1 or 2) into ta, tx, rows (rows null: no row component).
+hipError_t launch_backward_bias_tables(const Problem& p, int kind, int cells, int ld, float* ta, float* tx, float* rows,
+                                       hipStream_t st);
+// Parts of one kind's bias gradients as the agent kernels leave them (fp32, unrounded score gradients):
+//   gt [units][segs][cells][wp / 4][ld][4]    sums of (1 - f) dS and f dS over the image rows of a segment, for the
+//                                             cell rows the segment touches (others are not written)
+//   gr [units][xts][gh][ld]                   sums of dS over the 16 columns of an x-tile
+// and sum, room for gt of one batch element and segment ([heads][cells][wp / 4][ld][4]).
+struct BiasGradParts {
+  const float *gt, *gr;
+  float* sum;
+  int segs, seg_len, cells, ld;
+};
+hipError_t launch_backward_bias_grads(const Problem& p, int kind, const BiasGradParts& parts, int h0, int w0, float* col,
+                                      float* row, float* blk, hipStream_t st);
+// DWC parameter gradients from V and dO in the element type (d a multiple of 8, 16-byte rows); part: room for
+// dwc_param_part_floats() floats
+size_t dwc_param_part_floats(const Problem& p);
+hipError_t launch_dwc_param_grads(const Problem& p, const void* V, const void* dO, float* part, float* dw, float* db,
+                                  hipStream_t st);
+
+}  // namespace aa

@@ -1151,21 +1151,27 @@ hipError_t launch_backward_mfma(const Problem& p, const void* Q, const void* K, 
 }  // namespace
 
 size_t backward_workspace_floats(const Problem& p) {
-  if (backward_fused_supported(p)) return backward_fused_workspace_floats(p);
+  if (backward_pure_16bit(p)) return backward_fused_workspace_floats(p);
   const size_t u = (size_t)p.units, Nd = (size_t)p.N * p.d, nd = (size_t)p.n * p.d;
   // fp32 path: Q, K, V, dO, dQ, dK, dV (7 x N*d), A, V_A, dV_A, dA (4 x n*d), P1, dS1, P2, dS2 (4 x n*N).
   // 16-bit path: 5 x N*d + n*d fp32, the two score matrices in fp32 and four 16-bit copies (rows padded
   // to a multiple of 8), V_A and dV_A in 16 bits: never more than the figure below.
   const size_t nN = (size_t)p.n * ((p.N + 7) / 8 * 8), Nn = (size_t)p.N * ((p.n + 7) / 8 * 8);
-  return u * (7 * Nd + 4 * nd + 2 * nN + 2 * Nn) + dwc_part_floats(p);      // the slice sums at the very end
+  const size_t own = u * (7 * Nd + 4 * nd + 2 * nN + 2 * Nn) + dwc_part_floats(p);      // the slice sums at the very end
+  // module terms in 16 bits: the recomputing kernels when the tensors turn out to be aligned, else the fp32 path here
+  return backward_fused_supported(p) ? std::max(own, backward_fused_workspace_floats(p)) : own;
+}
+
+bool backward_pure_16bit(const Problem& p) {
+  return backward_fused_supported(p) && !p.b1.any() && !p.b2.any() && !p.dwc_w;
 }
 
 hipError_t launch_backward(const Problem& p, const void* Q, const void* K, const void* V, const void* A_elem,
                            const void* dO, float* ws, void* dQ, void* dK, void* dV, void* dA, bool agents_given,
                            bool use_mfma, const BackwardParamGrads& pg, hipStream_t st) {
-  if (backward_fused_supported(p)) {      // its workspace is the smaller one: there is no falling back from here
-    if (!use_mfma) return hipErrorInvalidValue;
-    return launch_backward_fused(p, Q, K, V, A_elem, dO, ws, dQ, dK, dV, dA, agents_given, st);
+  if (backward_fused_supported(p)) {
+    if (use_mfma) return launch_backward_fused(p, Q, K, V, A_elem, dO, ws, dQ, dK, dV, dA, agents_given, pg, st);
+    if (backward_pure_16bit(p)) return hipErrorInvalidValue;      // its workspace is the smaller one: no falling back
   }
   if (use_mfma && p.dtype == 2)
     return launch_backward_mfma<ElemBF16>(p, Q, K, V, A_elem, dO, ws, dQ, dK, dV, dA, agents_given, pg, st);

@@ -88,14 +88,16 @@ hipError_t launch_backward(const Problem& p, const void* Q, const void* K, const
                            bool use_mfma, const BackwardParamGrads& pg, hipStream_t st);
 
 // Backward without the attention matrices in memory (score tiles recomputed in the kernels that use them):
-// fp16 / bf16, d a multiple of 8 up to 128, no agent bias and no DWC (the V residual is handled); every tensor
-// 16-byte aligned.  launch_backward takes this path whenever the problem allows it, and the workspace figure
-// above is then this path's (a few n x d and N-long arrays, split partial sums).
+// fp16 / bf16, d a multiple of 8 up to 128, with any of the module terms; every tensor 16-byte aligned, strides
+// multiples of 8 elements, windows addressed in place.  launch_backward takes this path whenever use_mfma is set and
+// the problem allows it.  A problem without agent bias and DWC (backward_pure_16bit) has no other path: its workspace
+// is this path's (a few n x d and N-long arrays, split partial sums).
 bool backward_fused_supported(const Problem& p);
+bool backward_pure_16bit(const Problem& p);
 size_t backward_fused_workspace_floats(const Problem& p);
 hipError_t launch_backward_fused(const Problem& p, const void* Q, const void* K, const void* V, const void* A_elem,
                                  const void* dO, float* ws, void* dQ, void* dK, void* dV, void* dA, bool agents_given,
-                                 hipStream_t st);
+                                 const BackwardParamGrads& pg, hipStream_t st);
 
 // --- small-agent regime (n <= 64, d in {32, 64}, fp16 / bf16): MFMA kernels that keep A and V_A in
 //     registers and stream tokens straight from global memory ---

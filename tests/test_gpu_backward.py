@@ -161,6 +161,41 @@ def test_backward_module_mode_many_tokens(aa, oracle, agrid, dtype, batch, heads
               module=True, blk=(4, 3))
 
 
+@pytest.mark.parametrize("grid,agrid,d,dtype,blk,batch", [
+    ((5, 37), (3, 4), 32, "f16", (7, 7), 2),        # more cell rows than image rows: some are never touched
+    ((33, 16), (11, 12), 64, "bf16", (4, 5), 1),    # one x-tile: columns are segments; two agent blocks, the last ragged
+    ((9, 70), (9, 15), 128, "bf16", (1, 3), 1),     # one cell row; odd number of x-tiles; agents past one LDS chunk
+    ((40, 17), (8, 16), 40, "f16", (3, 17), 3),     # one token in the last x-tile; exactly one LDS chunk of agents
+    ((4, 200), (2, 33), 16, "bf16", (3, 2), 2),     # many pairs of columns per range, one segment
+    ((64, 3), (9, 3), 24, "f16", (9, 2), 1)])       # three columns wide, the rest of the tile masked
+def test_backward_agent_bias_off_the_tile_sizes(aa, oracle, grid, agrid, d, dtype, blk, batch):
+    """The recomputing kernels with an agent bias walk down 16-token columns of the image: grids, cell grids and
+    agent counts on and off their tiles, every gradient (bars as everywhere in this file)."""
+    _run_case(aa, oracle, _wl("bias_tiles", dtype, grid, agrid, d, batch=batch, index=81), module=True, blk=blk)
+
+
+@pytest.mark.parametrize("keys", [("b1_col",), ("b1_row", "b2_blk"), ("b2_row", "dwc_w"), ("dwc_w",)])
+def test_backward_single_module_terms(aa, oracle, keys):
+    """One stage with a bias and the other without, single components, the convolution alone: the gradients against
+    those of the fp32 path on the same values (itself held against the oracle above), at the bf16 bar."""
+    import torch
+    wl = _wl("terms", "bf16", (21, 30), (5, 6), 64, batch=2, heads=2, index=83)
+    t = inputs.make_qkv(wl)
+    t["dO"] = inputs.make_tensor((wl.units, wl.N, wl.d), stream=wl.index * 16 + 12, dtype=wl.dtype)
+    shape = (wl.batch, wl.heads, wl.N, wl.d)
+    dv = [util.to_device(t[k], wl.dtype, shape) for k in ("Q", "K", "V", "dO")]
+    A = util.to_device(inputs.make_tensor((wl.units, wl.n, wl.d), stream=wl.index * 16 + 11, dtype=wl.dtype), wl.dtype,
+                       (wl.batch, wl.heads, wl.n, wl.d))
+    full = util.params_to_device(inputs.make_module_params(wl.heads, wl.n, wl.d, wl.grid, blk=(4, 3), index=wl.index))
+    params = {k: full[k] for k in keys}
+    got = aa.agent_attn_bwd(*dv, A, grid=wl.grid, params=params)
+    ref = aa.agent_attn_bwd(*[x.float() for x in dv], A.float(), grid=wl.grid, params=params)
+    assert set(got) == set(ref)
+    for k in ref:
+        a, b = got[k].double(), ref[k].double()
+        assert bool(torch.isfinite(a).all()) and float((a - b).norm() / b.norm()) <= 1e-2, k
+
+
 def test_backward_module_given_agents_and_residual(aa, oracle):
     wl = _wl("module-given", "f32", (8, 8), (2, 8), 24)
     _run_case(aa, oracle, wl, given=True, module=True, kw=dict(v_residual_k=0.075, scale2=24 ** -0.15))
