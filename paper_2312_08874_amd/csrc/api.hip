@@ -60,6 +60,7 @@ struct Plan {
   size_t off_acc, off_m, off_l;
   size_t off_VA;       // merged V_A, fp32
   BiasPlan bias;       // agent-bias tables, offsets relative to off_bias
+  size_t off_f32;      // workspace of the fp32 kernels that stream their tokens (kNoStage: they are not used)
   size_t off_stage;    // window mode: window-major copies of Q, K, V and of the output (kNoStage: not needed)
   size_t stage_bytes;  // size of one of the four
   size_t off_bias;     // where they live in the workspace (unused when the caller brings prepared tables)
@@ -257,7 +258,8 @@ int padded_width(int d);
 
 constexpr size_t kNoStage = ~(size_t)0;
 
-Plan make_plan(const aa_desc* d, const aa_params* params = nullptr) {
+// small: without the fp32 kernels' bias tables and partial sums (callers with a workspace of fixed size)
+Plan make_plan(const aa_desc* d, const aa_params* params = nullptr, bool small = false) {
   Plan pl{};
   const size_t units = (size_t)units_of(d);
   pl.S = choose_splits(d);
@@ -304,6 +306,12 @@ Plan make_plan(const aa_desc* d, const aa_params* params = nullptr) {
   pl.bias = plan_bias(d, params);
   pl.off_bias = off;
   if (!(params && params->bias_tables)) off += pl.bias.total;      // prepared tables need no room here
+  pl.off_f32 = kNoStage;
+  const Problem full = make_problem(d, params);
+  if (!small && d->n_splits <= 0 && aa::forward_f32_supported(full)) {      // an explicit split count: the kernels that take one
+    pl.off_f32 = off;
+    off += align_up(aa::forward_f32_workspace_floats(full) * sizeof(float));
+  }
   pl.total = off;
   return pl;
 }
@@ -610,7 +618,8 @@ aa_status prepare_dense_bias(Problem& pr, const Plan& pl, const aa_params* param
 aa_status run_pool(const Problem& pr, const void* Q, void* A, void* Alo, hipStream_t st) {
   if (use_small(pr, {Q, A}))
     AA_HIP(aa::launch_small_pool(pr, Q, A, Alo, st));
-  else if ((pr.dtype == 1 || pr.dtype == 2) && pr.d % 8 == 0 && aligned16(Q) && aligned16(A))
+  else if (pr.d % (pr.dtype == AA_F32 ? 4 : 8) == 0 && aligned16(Q) && aligned16(A) &&
+           (pr.dtype != AA_F32 || (pr.lay.sb % 4 == 0 && pr.lay.sh % 4 == 0 && pr.lay.sn % 4 == 0)))
     AA_HIP(aa::launch_pool_chunk(pr, Q, A, Alo, st));
   else
     AA_HIP(aa::launch_pool_generic(pr, Q, A, Alo, st));
@@ -777,6 +786,11 @@ static aa_status forward_core(Problem pr, const Plan& pl, const aa_params* param
     agents = ws + pl.off_A;
     agents_lo = lo;
   }
+  if (pl.off_f32 != kNoStage && aligned16(Q) && aligned16(K) && aligned16(V) && aligned16(agents) && aligned16(out) &&
+      aligned16(pr.dwc_b) && aa::fused_layout_supported(pr)) {
+    AA_HIP(aa::launch_forward_f32(pr, Q, K, V, agents, (float*)(ws + pl.off_f32), out, stream));
+    return AA_OK;
+  }
   float* VA = (float*)(ws + pl.off_VA);
   if (use_small(pr, {Q, K, V, agents, out})) {
     // small-agent regime: the broadcast blocks merge the split partials themselves (no merge launch)
@@ -790,9 +804,10 @@ static aa_status forward_core(Problem pr, const Plan& pl, const aa_params* param
   return run_broadcast(pr, Q, agents, agents_lo, VA, V, out, pl, stream);
 }
 
-aa_status agent_attn_fwd(const aa_desc* desc, const void* Q, const void* K, const void* V, const void* A,
-                         const aa_params* params, void* workspace, size_t workspace_bytes, void* out,
-                         void* hip_stream) {
+// agent_attn_fwd; small: plan without the streaming fp32 kernels' workspace
+static aa_status forward_checked(const aa_desc* desc, const void* Q, const void* K, const void* V, const void* A,
+                                 const aa_params* params, void* workspace, size_t workspace_bytes, void* out,
+                                 void* hip_stream, bool small) {
   const bool pooling = (A == nullptr);
   aa_status st = check_desc(desc, pooling || params_use_grid(params), pooling);
   if (st == AA_ERR_SHAPE && pooling && desc && desc->grid_h == 0 && desc->grid_w == 0) st = AA_ERR_POOL;
@@ -800,7 +815,7 @@ aa_status agent_attn_fwd(const aa_desc* desc, const void* Q, const void* K, cons
   st = check_params(params);
   if (st != AA_OK) return st;
   if (!Q || !K || !V || !out) return AA_ERR_NULL;
-  const Plan pl = make_plan(desc, params);
+  const Plan pl = make_plan(desc, params, small);
   st = check_workspace(workspace, workspace_bytes, pl);
   if (st != AA_OK) return st;
   const size_t es = elem_size(desc->dtype), units = (size_t)units_of(desc);
@@ -838,6 +853,12 @@ aa_status agent_attn_fwd(const aa_desc* desc, const void* Q, const void* K, cons
     }
   }
   return forward_core(pr, pl, params, Q, K, V, A, workspace, out, stream);
+}
+
+aa_status agent_attn_fwd(const aa_desc* desc, const void* Q, const void* K, const void* V, const void* A,
+                         const aa_params* params, void* workspace, size_t workspace_bytes, void* out,
+                         void* hip_stream) {
+  return forward_checked(desc, Q, K, V, A, params, workspace, workspace_bytes, out, hip_stream, false);
 }
 
 // Backward workspace: the pooled agents in the element type (256-byte aligned), then the fp32 scratch, then,
@@ -912,8 +933,7 @@ aa_status agent_attn_bwd(const aa_desc* desc, const void* Q, const void* K, cons
   if (aa::backward_pure_16bit(pr) && !(aligned16(A) && aligned16(dA))) return AA_ERR_UNSUPPORTED;
   if (aa::backward_pure_16bit(pr) && dense_layout(desc) && !aligned) return AA_ERR_UNSUPPORTED;
   // the recomputing kernels read strided tensors and windows where they lie
-  const bool in_place = aa::backward_fused_supported(pr) && aligned && layout_vectorizable(pr.lay) &&
-                        (!windowed(desc) || (int64_t)desc->N * desc->grid_w < ((int64_t)1 << 32));
+  const bool in_place = aa::backward_fused_supported(pr) && aligned && aa::fused_layout_supported(pr);
   hipStream_t stream = (hipStream_t)hip_stream;
   char* ws = (char*)workspace;
   // Strided tensors otherwise: the kernels below work on dense copies staged at the end of the workspace
@@ -948,11 +968,10 @@ aa_status agent_attn_bwd(const aa_desc* desc, const void* Q, const void* K, cons
     if (st != AA_OK) return st;
     agents = ws;
   }
-  const bool use_mfma = (pr.dtype == AA_F16 || pr.dtype == AA_BF16) && pr.d % 8 == 0 && aligned16(Q) && aligned16(K) &&
-                        aligned16(V) && aligned16(dO) && aligned16(agents) &&
-                        (sdQ || (aligned16(dQ) && aligned16(dK) && aligned16(dV))) && aligned16(dA);
+  // staged tensors are aligned, whatever the caller's are
+  const bool all_aligned = sdQ ? aligned16(A) && aligned16(dA) : aligned;
   AA_HIP(aa::launch_backward(pr, Q, K, V, agents, dO, (float*)(ws + bwd_agents_bytes(desc)), dQ, dK, dV, dA, !pooling,
-                             use_mfma, pg, stream));
+                             all_aligned, pg, stream));
   if (sdQ) {
     AA_HIP(aa::launch_restride(strided_pr, false, false, sdQ, udQ, stream));
     AA_HIP(aa::launch_restride(strided_pr, false, false, sdK, udK, stream));
@@ -974,7 +993,8 @@ aa_status agent_attn_fwd_static(const aa_desc* desc, const void* Q, const void* 
   st = check_params(params);
   if (st != AA_OK) return st;
   if (!Q || !K || !V || !out) return AA_ERR_NULL;
-  if (make_plan(desc, params).total > AA_STATIC_SCRATCH_BYTES) return AA_ERR_WORKSPACE;
+  const bool small = make_plan(desc, params).total > AA_STATIC_SCRATCH_BYTES;
+  if (small && make_plan(desc, params, true).total > AA_STATIC_SCRATCH_BYTES) return AA_ERR_WORKSPACE;
   // device address of this GPU's copy of the array, looked up once per device
   constexpr int kMaxDevices = 64;
   static std::mutex mu;
@@ -993,7 +1013,7 @@ aa_status agent_attn_fwd_static(const aa_desc* desc, const void* Q, const void* 
     }
     ptr = base[dev];
   }
-  return agent_attn_fwd(desc, Q, K, V, A, params, ptr, AA_STATIC_SCRATCH_BYTES, out, hip_stream);
+  return forward_checked(desc, Q, K, V, A, params, ptr, AA_STATIC_SCRATCH_BYTES, out, hip_stream, small);
 }
 
 aa_status agent_attn_fwd_timed(const aa_desc* desc, const void* Q, const void* K, const void* V, const void* A,
@@ -1183,6 +1203,8 @@ size_t agent_attn_plan_str(const aa_desc* desc, int agents_given, char* buf, siz
                    pl.S_large > 1 ? " + large_merge" : "", 32 * pl.bcast_waves_large);
   } else if (pl.prefer_fused && aa::fused_f32_supported(pr)) {
     len = snprintf(buf, buf_len, "fused_f32");
+  } else if (pl.off_f32 != kNoStage) {
+    len = snprintf(buf, buf_len, "%sforward_f32 (generic: aggregate + merge + broadcast)", agents_given ? "" : "pool_chunk + ");
   } else {
     len = snprintf(buf, buf_len, "%saggregate_generic(S=%d) + %sbroadcast_generic", agents_given ? "" : "pool_generic + ",
                    pl.S, pl.S > 1 ? "merge_generic + " : "");

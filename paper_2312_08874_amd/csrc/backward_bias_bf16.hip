@@ -2,6 +2,6 @@
 #include "backward_fused.inc"
 
 namespace aa {
-template hipError_t launch_token_bias<ElemBF16>(int, int, const TokenArgs&, dim3, size_t, hipStream_t);
-template hipError_t launch_agent_bias<ElemBF16>(int, int, int, const AgentArgs&, dim3, size_t, hipStream_t);
+template hipError_t launch_token<ElemBF16, true>(int, int, int, const TokenArgs&, dim3, size_t, hipStream_t);
+template hipError_t launch_agent<ElemBF16, true>(int, int, int, const AgentArgs&, dim3, size_t, hipStream_t);
 }  // namespace aa

@@ -5,7 +5,7 @@
 namespace aa {
 
 constexpr int kThreads = 256;       // four waves per block
-enum { kFwd = 0, kBc = 1, kAgg = 2, kBcStat = 3 };
+enum { kFwd = 0, kBc = 1, kAgg = 2, kBcStat = 3, kOut = 4 };
 
 // Agent bias of one kind as the recomputing kernels read it (fp32, times log2 e; see backward_fused.inc):
 //   bias(a, (y, x)) = (1 - f) T[i][x][a] + f T[i + 1][x][a] + R[y][a]
@@ -67,7 +67,7 @@ struct UnitPlace {
 };
 
 struct TokenArgs {
-  const uint16_t *X, *Y, *M1, *M2;
+  const void *X, *Y, *M1, *M2;      // in the element type
   const float *rs1, *rs2;
   float *st1, *st2;
   void *O1, *O2;
@@ -75,15 +75,16 @@ struct TokenArgs {
   const float* dA;                   // kBc: the finished dA [units][n][d] when the agents were pooled (else null)
   int gh, gw, ah, aw;                // token grid, the pooling's agent grid
   float sc, oscale;
-  const uint16_t* G;      // kAgg: dO, for the share of dV that comes through the V residual (Appendix C.1: O += k V)
-  float vk;               //   and through the depthwise convolution (Eq. (6), dwc_w [heads][d][3][3] or null)
-  const float* dwc_w;
+  const void* G;          // kAgg: dO, for the share of dV that comes through the V residual (Appendix C.1: O += k V)
+  float vk;               //   and through the depthwise convolution (Eq. (6), dwc_w [heads][d][3][3] or null);
+  const float* dwc_w;     //   kOut: V, for these terms themselves
+  const float* dwc_b;     // kOut: [heads][d] or null
   UnitPlace at;           // Q, K, V and the gradients lie with the input strides, dO with the output strides
   BiasTables bt;          // with a bias only
 };
 
 struct AgentArgs {
-  const uint16_t *X, *Y, *M1, *M2;
+  const void *X, *Y, *M1, *M2;      // in the element type
   const float *ts1, *ts2, *rs1, *rs2;
   float *P1, *P2, *pm, *pl;
   int N, n, d, chunk, S;      // chunk: tokens per range (without a bias)
@@ -97,13 +98,13 @@ struct AgentArgs {
   float *gt, *gr;             // parts of the gradients of T and R (null: not wanted), see BiasGradParts
 };
 
-// the kernels with a bias (backward_bias_{bf16,f16}.hip); prob kFwd .. kBcStat, dp 32 / 64 / 128, cols 16-agent columns
-// per wave
-template <class E>
-hipError_t launch_token_bias(int prob, int dp, const TokenArgs& a, dim3 grid, size_t lds, hipStream_t st);
-template <class E>
-hipError_t launch_agent_bias(int prob, int dp, int cols, const AgentArgs& a, dim3 grid, size_t lds, hipStream_t st);
-constexpr int kBiasTokenCols = 2;      // 16-token columns (image rows) per wave of the token kernels with a bias
+// The kernels, compiled by backward_fused_kernels.hip (16-bit, no bias), backward_bias_{bf16,f16}.hip and
+// backward_f32.hip.  dp: padded head width (16-bit 32 / 64 / 128, fp32 also 48 and 96); cols: 16-token columns per wave
+// (token kernels) or 16-agent columns (agent kernels)
+template <class E, bool BIAS>
+hipError_t launch_token(int prob, int dp, int cols, const TokenArgs& a, dim3 grid, size_t lds, hipStream_t st);
+template <class E, bool BIAS>
+hipError_t launch_agent(int prob, int dp, int cols, const AgentArgs& a, dim3 grid, size_t lds, hipStream_t st);
 
 // --- backward_module.hip ---
 // Tables of one kind (1 or 2) into ta, tx, rows (rows null: no row component).

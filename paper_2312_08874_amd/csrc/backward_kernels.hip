@@ -1158,7 +1158,7 @@ size_t backward_workspace_floats(const Problem& p) {
   // to a multiple of 8), V_A and dV_A in 16 bits: never more than the figure below.
   const size_t nN = (size_t)p.n * ((p.N + 7) / 8 * 8), Nn = (size_t)p.N * ((p.n + 7) / 8 * 8);
   const size_t own = u * (7 * Nd + 4 * nd + 2 * nN + 2 * Nn) + dwc_part_floats(p);      // the slice sums at the very end
-  // module terms in 16 bits: the recomputing kernels when the tensors turn out to be aligned, else the fp32 path here
+  // module terms or fp32: the recomputing kernels when the tensors turn out to be aligned, else the path here
   return backward_fused_supported(p) ? std::max(own, backward_fused_workspace_floats(p)) : own;
 }
 
@@ -1168,11 +1168,12 @@ bool backward_pure_16bit(const Problem& p) {
 
 hipError_t launch_backward(const Problem& p, const void* Q, const void* K, const void* V, const void* A_elem,
                            const void* dO, float* ws, void* dQ, void* dK, void* dV, void* dA, bool agents_given,
-                           bool use_mfma, const BackwardParamGrads& pg, hipStream_t st) {
+                           bool aligned, const BackwardParamGrads& pg, hipStream_t st) {
   if (backward_fused_supported(p)) {
-    if (use_mfma) return launch_backward_fused(p, Q, K, V, A_elem, dO, ws, dQ, dK, dV, dA, agents_given, pg, st);
+    if (aligned) return launch_backward_fused(p, Q, K, V, A_elem, dO, ws, dQ, dK, dV, dA, agents_given, pg, st);
     if (backward_pure_16bit(p)) return hipErrorInvalidValue;      // its workspace is the smaller one: no falling back
   }
+  const bool use_mfma = aligned && p.dtype != 0 && p.d % 8 == 0;
   if (use_mfma && p.dtype == 2)
     return launch_backward_mfma<ElemBF16>(p, Q, K, V, A_elem, dO, ws, dQ, dK, dV, dA, agents_given, pg, st);
   if (use_mfma && p.dtype == 1)

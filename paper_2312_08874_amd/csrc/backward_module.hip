@@ -156,37 +156,55 @@ __global__ __launch_bounds__(256) void bias_grad_out_kernel(const f32x4* __restr
 
 // ---------------------------------------------------------------------------
 // DWC parameter gradients: dw[c][tap] = sum over batch and tokens of dO[y,x,c] V[y + p, x + q, c], db[c] = sum dO.
-// A thread owns eight channels of an image column and walks down its rows with the 3 x 3 neighbourhood of V in
+// A thread owns a 16-byte piece of the channels of an image column and walks down its rows with the 3 x 3 neighbourhood of V in
 // registers, so that a row costs three 16-byte reads of V (two of them shared with the neighbouring columns through
 // L1) and one of dO; CHP = 16-byte pieces per token rounded up to a power of two.  The lanes of a block are added by
 // a fixed tree, the blocks by dwc_param_sum_kernel.
 // grid = (slices, heads); slice = 256 / CHP (column, row segment, image) items.
 // ---------------------------------------------------------------------------
+template <class E>
+struct Piece {      // 16 bytes of elements as floats
+  using S = uint16_t;
+  static constexpr int kCount = 8;
+  static __device__ __forceinline__ void unpack(u32x4 p, float* o) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) Mx<E>::unpack2(p[i], o[2 * i], o[2 * i + 1]);
+  }
+};
+template <>
+struct Piece<ElemF32> {
+  using S = float;
+  static constexpr int kCount = 4;
+  static __device__ __forceinline__ void unpack(u32x4 p, float* o) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) o[i] = __uint_as_float(p[i]);
+  }
+};
+
 template <class E, int CHP>
-__global__ __launch_bounds__(256) void dwc_param_kernel(const uint16_t* __restrict__ V, const uint16_t* __restrict__ dO,
+__global__ __launch_bounds__(256) void dwc_param_kernel(const typename Piece<E>::S* __restrict__ V,
+                                                        const typename Piece<E>::S* __restrict__ dO,
                                                         float* __restrict__ part, int heads, int d, Layout lay, int gh, int gw,
                                                         int segs, int seg_len, int items) {
-  __shared__ float red[4][CHP][80];
+  using S = typename Piece<E>::S;
+  constexpr int P = Piece<E>::kCount;
+  __shared__ float red[4][CHP][10 * P];
   const int hd = blockIdx.y, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int ch = tid % CHP;
   const int item = blockIdx.x * (256 / CHP) + tid / CHP;
-  float acc[10][8];
+  float acc[10][P];
 #pragma unroll
   for (int k = 0; k < 10; ++k)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) acc[k][i] = 0.0f;
-  if (item < items && ch * 8 < d) {
+    for (int i = 0; i < P; ++i) acc[k][i] = 0.0f;
+  if (item < items && ch * P < d) {
     const int x = item % gw, s = item / gw % segs, b = item / gw / segs;
     const int u = b * heads + hd, pitch = lay.pitch(gw);
-    const uint16_t* v = V + lay.in_unit(u, heads) + ch * 8;
-    const uint16_t* g = dO + lay.out_unit(u, heads) + ch * 8;
+    const S* v = V + lay.in_unit(u, heads) + ch * P;
+    const S* g = dO + lay.out_unit(u, heads) + ch * P;
     const int y0 = s * seg_len, y1 = min(gh, y0 + seg_len);
-    float win[3][3][8];      // rows y - 1, y, y + 1 (rotating), columns x - 1 .. x + 1
-    auto unpack = [](u32x4 p, float* o) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) Mx<E>::unpack2(p[i], o[2 * i], o[2 * i + 1]);
-    };
-    auto load_row = [&](int y, float (&o)[3][8]) {
+    float win[3][3][P];      // rows y - 1, y, y + 1 (rotating), columns x - 1 .. x + 1
+    auto load_row = [&](int y, float (&o)[3][P]) {
       u32x4 p[3];
 #pragma unroll
       for (int q = 0; q < 3; ++q) {
@@ -195,19 +213,19 @@ __global__ __launch_bounds__(256) void dwc_param_kernel(const uint16_t* __restri
         if (y >= 0 && y < gh && xx >= 0 && xx < gw) p[q] = *reinterpret_cast<const u32x4*>(v + ((size_t)y * pitch + xx) * lay.sn);
       }
 #pragma unroll
-      for (int q = 0; q < 3; ++q) unpack(p[q], o[q]);
+      for (int q = 0; q < 3; ++q) Piece<E>::unpack(p[q], o[q]);
     };
-    auto row = [&](int y, const float (&a)[3][8], const float (&m)[3][8], float (&z)[3][8]) {
+    auto row = [&](int y, const float (&a)[3][P], const float (&m)[3][P], float (&z)[3][P]) {
       const u32x4 gp = *reinterpret_cast<const u32x4*>(g + ((size_t)y * pitch + x) * lay.on);
       load_row(y + 1, z);
-      float gv[8];
-      unpack(gp, gv);
+      float gv[P];
+      Piece<E>::unpack(gp, gv);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) acc[9][i] += gv[i];
+      for (int i = 0; i < P; ++i) acc[9][i] += gv[i];
 #pragma unroll
       for (int q = 0; q < 3; ++q)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int i = 0; i < P; ++i) {
           acc[q][i] = fmaf(gv[i], a[q][i], acc[q][i]);
           acc[3 + q][i] = fmaf(gv[i], m[q][i], acc[3 + q][i]);
           acc[6 + q][i] = fmaf(gv[i], z[q][i], acc[6 + q][i]);
@@ -227,7 +245,7 @@ __global__ __launch_bounds__(256) void dwc_param_kernel(const uint16_t* __restri
 #pragma unroll
   for (int k = 0; k < 10; ++k)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < P; ++i) {
       float t = acc[k][i];
 #pragma unroll
       for (int o = CHP; o < 64; o <<= 1) t += __shfl_xor(t, o, 64);
@@ -237,11 +255,11 @@ __global__ __launch_bounds__(256) void dwc_param_kernel(const uint16_t* __restri
 #pragma unroll
     for (int k = 0; k < 10; ++k)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) red[w][lane][i * 10 + k] = acc[k][i];
+      for (int i = 0; i < P; ++i) red[w][lane][i * 10 + k] = acc[k][i];
   __syncthreads();
   for (int i = tid; i < d * 10; i += 256)      // channel-major, ten sums each
     part[((size_t)hd * gridDim.x + blockIdx.x) * d * 10 + i] =
-        (red[0][i / 80][i % 80] + red[1][i / 80][i % 80]) + (red[2][i / 80][i % 80] + red[3][i / 80][i % 80]);
+        (red[0][i / (10 * P)][i % (10 * P)] + red[1][i / (10 * P)][i % (10 * P)]) + (red[2][i / (10 * P)][i % (10 * P)] + red[3][i / (10 * P)][i % (10 * P)]);
 }
 
 // one wave per (head, channel): lane l adds the slices l, l + 64, ... in order, the lanes are added by a fixed tree
@@ -272,7 +290,8 @@ struct DwcPlan {
 };
 DwcPlan dwc_plan(const Problem& p) {
   DwcPlan q{};
-  q.chp = p.d <= 16 ? 2 : (p.d <= 32 ? 4 : (p.d <= 64 ? 8 : 16));
+  const int pieces = p.d / (p.dtype == 0 ? 4 : 8);
+  q.chp = pieces <= 2 ? 2 : (pieces <= 4 ? 4 : (pieces <= 8 ? 8 : (pieces <= 16 ? 16 : 32)));
   const int batch = p.units / p.heads, per_block = 256 / q.chp;
   const long long cols = (long long)batch * p.gw;
   const long long blocks = (cols + per_block - 1) / per_block * p.heads;
@@ -335,17 +354,24 @@ hipError_t launch_dwc_param_grads(const Problem& p, const void* V, const void* d
                                   hipStream_t st) {
   const DwcPlan q = dwc_plan(p);
   const dim3 grid(q.slices, p.heads);
-  auto go = [&](auto kernel) {
-    kernel<<<grid, dim3(256), 0, st>>>((const uint16_t*)V, (const uint16_t*)dO, part, p.heads, p.d, p.lay, p.gh, p.gw, q.segs,
-                                       q.seg_len, q.items);
+  auto go = [&](auto kernel, auto elem) {
+    using S = typename Piece<decltype(elem)>::S;
+    kernel<<<grid, dim3(256), 0, st>>>((const S*)V, (const S*)dO, part, p.heads, p.d, p.lay, p.gh, p.gw, q.segs, q.seg_len,
+                                       q.items);
   };
-  auto by_type = [&](auto bf, auto hf) { p.dtype == 2 ? go(bf) : go(hf); };
-  switch (q.chp) {
-    case 2: by_type(dwc_param_kernel<ElemBF16, 2>, dwc_param_kernel<ElemF16, 2>); break;
-    case 4: by_type(dwc_param_kernel<ElemBF16, 4>, dwc_param_kernel<ElemF16, 4>); break;
-    case 8: by_type(dwc_param_kernel<ElemBF16, 8>, dwc_param_kernel<ElemF16, 8>); break;
-    default: by_type(dwc_param_kernel<ElemBF16, 16>, dwc_param_kernel<ElemF16, 16>); break;
-  }
+  auto by_pieces = [&](auto elem) {
+    using E = decltype(elem);
+    switch (q.chp) {
+      case 2: go(dwc_param_kernel<E, 2>, elem); break;
+      case 4: go(dwc_param_kernel<E, 4>, elem); break;
+      case 8: go(dwc_param_kernel<E, 8>, elem); break;
+      case 16: go(dwc_param_kernel<E, 16>, elem); break;
+      default: go(dwc_param_kernel<E, 32>, elem); break;      // fp32 only
+    }
+  };
+  if (p.dtype == 2) by_pieces(ElemBF16{});
+  else if (p.dtype == 1) by_pieces(ElemF16{});
+  else by_pieces(ElemF32{});
   dwc_param_total_kernel<<<dim3(p.d, p.heads), dim3(64), 0, st>>>(part, dw, db, p.d, q.slices);
   return hipGetLastError();
 }

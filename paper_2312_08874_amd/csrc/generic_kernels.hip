@@ -37,62 +37,56 @@ __global__ __launch_bounds__(64) void pool_generic_kernel(const typename E::T* _
 }
 
 // ---------------------------------------------------------------------------
-// The same for the 16-bit element types with d a multiple of 8 and 16-byte aligned tensors: thread = one
-// (agent, 8-channel chunk) item, 16-byte loads, four window rows in flight.  grid = (ceil(n*d/8 / 256),
-// units).  Accumulation is fp32 in window order (row-major), as in the kernel above.
+// The same for rows of whole 16-byte pieces and 16-byte aligned tensors: thread = one (agent, 16-byte piece) item, four
+// window rows in flight.  grid = (ceil(pieces * n / 256), units).  Accumulation is fp32 in window order (row-major), as
+// in the kernel above.
 // ---------------------------------------------------------------------------
 template <class E>
-__global__ __launch_bounds__(256) void pool_chunk_kernel(const uint16_t* __restrict__ Q, uint16_t* __restrict__ A,
-                                                         uint16_t* __restrict__ Alo, int N, int n, int d, int heads,
+__global__ __launch_bounds__(256) void pool_chunk_kernel(const typename E::T* __restrict__ Q, typename E::T* __restrict__ A,
+                                                         typename E::T* __restrict__ Alo, int N, int n, int d, int heads,
                                                          Layout lay, int gh, int gw, int ah, int aw) {
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-  const int cpr = d >> 3, u = blockIdx.y;
+  using T = typename E::T;
+  constexpr int PE = 16 / (int)sizeof(T);      // elements per piece
+  struct alignas(16) Piece {
+    T e[PE];
+  };
+  const int cpr = d / PE, u = blockIdx.y;
   const int item = blockIdx.x * 256 + threadIdx.x;
   if (item >= n * cpr) return;
   const int a = item / cpr, chunk = item - a * cpr;
   const int ay = a / aw, ax = a - ay * aw;
   const int y0 = pool_win_lo(ay, gh, ah), y1 = pool_win_hi(ay, gh, ah);
   const int x0 = pool_win_lo(ax, gw, aw), x1 = pool_win_hi(ax, gw, aw);
-  const uint16_t* q = Q + lay.in_unit(u, heads) + 8 * chunk;
-  float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  auto add = [&](const u32x4& v) {
+  const T* q = Q + lay.in_unit(u, heads) + PE * chunk;
+  float acc[PE];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      union { uint16_t h[2]; uint32_t w; } t;
-      t.w = v[k];
-      acc[2 * k] += E::to_f32(*(const typename E::T*)&t.h[0]);
-      acc[2 * k + 1] += E::to_f32(*(const typename E::T*)&t.h[1]);
-    }
+  for (int k = 0; k < PE; ++k) acc[k] = 0.0f;
+  auto add = [&](const Piece& v) {
+#pragma unroll
+    for (int k = 0; k < PE; ++k) acc[k] += E::to_f32(v.e[k]);
   };
   for (int y = y0; y < y1; ++y) {
-    const uint16_t* row = q + (size_t)y * lay.pitch(gw) * lay.sn;
+    const T* row = q + (size_t)y * lay.pitch(gw) * lay.sn;
     int x = x0;
     for (; x + 4 <= x1; x += 4) {
-      u32x4 v[4];
+      Piece v[4];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) v[j] = *(const u32x4*)(row + (size_t)(x + j) * lay.sn);
+      for (int j = 0; j < 4; ++j) v[j] = *(const Piece*)(row + (size_t)(x + j) * lay.sn);
 #pragma unroll
       for (int j = 0; j < 4; ++j) add(v[j]);
     }
-    for (; x < x1; ++x) add(*(const u32x4*)(row + (size_t)x * lay.sn));
+    for (; x < x1; ++x) add(*(const Piece*)(row + (size_t)x * lay.sn));
   }
   const float inv = 1.0f / (float)((y1 - y0) * (x1 - x0));
-  u32x4 w, wlo;
+  Piece w, wlo;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    union { uint16_t h[2]; uint32_t w; } t, tl;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const float mean = acc[2 * k + j] * inv;
-      const typename E::T hi = E::from_f32(mean);
-      *(typename E::T*)&t.h[j] = hi;
-      *(typename E::T*)&tl.h[j] = E::from_f32(mean - E::to_f32(hi));      // what the rounding left over
-    }
-    w[k] = t.w;
-    wlo[k] = tl.w;
+  for (int k = 0; k < PE; ++k) {
+    const float mean = acc[k] * inv;
+    w.e[k] = E::from_f32(mean);
+    wlo.e[k] = E::from_f32(mean - E::to_f32(w.e[k]));      // what the rounding left over
   }
-  *(u32x4*)(A + ((size_t)u * n + a) * d + 8 * chunk) = w;
-  if (Alo) *(u32x4*)(Alo + ((size_t)u * n + a) * d + 8 * chunk) = wlo;
+  *(Piece*)(A + ((size_t)u * n + a) * d + PE * chunk) = w;
+  if (Alo) *(Piece*)(Alo + ((size_t)u * n + a) * d + PE * chunk) = wlo;
 }
 
 // ---------------------------------------------------------------------------
@@ -675,15 +669,10 @@ hipError_t launch_pool_generic(const Problem& p, const void* Q, void* A, void* A
 }
 
 hipError_t launch_pool_chunk(const Problem& p, const void* Q, void* A, void* Alo, hipStream_t st) {
-  const dim3 grid((p.n * (p.d >> 3) + 255) / 256, p.units);
-  if (p.dtype == 2)
-    pool_chunk_kernel<ElemBF16><<<grid, dim3(256), 0, st>>>((const uint16_t*)Q, (uint16_t*)A, (uint16_t*)Alo, p.N, p.n, p.d,
-                                                            p.heads, p.lay, p.gh, p.gw, p.ah, p.aw);
-  else if (p.dtype == 1)
-    pool_chunk_kernel<ElemF16><<<grid, dim3(256), 0, st>>>((const uint16_t*)Q, (uint16_t*)A, (uint16_t*)Alo, p.N, p.n, p.d,
-                                                           p.heads, p.lay, p.gh, p.gw, p.ah, p.aw);
-  else
-    return hipErrorInvalidValue;
+  const dim3 grid((p.n * (p.d / (p.dtype == 0 ? 4 : 8)) + 255) / 256, p.units);
+  if (p.dtype == 0) Alo = nullptr;      // fp32 agents carry no residual worth keeping
+  AA_DISPATCH_DTYPE(p.dtype, pool_chunk_kernel<E><<<grid, dim3(256), 0, st>>>(
+      (const typename E::T*)Q, (typename E::T*)A, (typename E::T*)Alo, p.N, p.n, p.d, p.heads, p.lay, p.gh, p.gw, p.ah, p.aw));
   return hipGetLastError();
 }
 

@@ -37,7 +37,7 @@ struct Partials {
 // one, so a forward pass that pools its own agents does not lose them to a 16-bit rounding.  Agents handed in by
 // the caller are exact in the element type: Alo is null for them.
 hipError_t launch_pool_generic(const Problem& p, const void* Q, void* A, void* Alo, hipStream_t st);
-// fp16 / bf16, d a multiple of 8, Q and A 16-byte aligned: 16-byte loads, thread per (agent, 8 channels)
+// rows of whole 16-byte pieces, Q and A 16-byte aligned: 16-byte loads, thread per (agent, piece)
 hipError_t launch_pool_chunk(const Problem& p, const void* Q, void* A, void* Alo, hipStream_t st);
 // agent bias of kind 1 (p.b1 -> out1) and / or 2 (p.b2 -> out2) evaluated for all pairs into the padded dense
 // layout of BiasArgs, in one launch; a null output skips that kind
@@ -81,23 +81,30 @@ struct BackwardParamGrads {      // fp32 device outputs, any may be null; layout
 // fp32 scratch the backward needs, in floats
 size_t backward_workspace_floats(const Problem& p);
 // A_elem: the agents in the element type (pooled by the forward's pooling kernel, or as given).
-// dA is written only when agents_given.  use_mfma: fp16 / bf16, d a multiple of 8 and every tensor
-// 16-byte aligned -- the matrix products then run on MFMA with P and dS kept in the element type.
+// dA is written only when agents_given.  aligned: every tensor is 16-byte aligned (and p.lay passes
+// fused_layout_supported): the recomputing kernels below then serve what they can; 16-bit problems they do not serve
+// (d a multiple of 8 above 128) run their matrix products on MFMA, with P and dS kept in the element type.
 hipError_t launch_backward(const Problem& p, const void* Q, const void* K, const void* V, const void* A_elem,
                            const void* dO, float* ws, void* dQ, void* dK, void* dV, void* dA, bool agents_given,
-                           bool use_mfma, const BackwardParamGrads& pg, hipStream_t st);
+                           bool aligned, const BackwardParamGrads& pg, hipStream_t st);
 
-// Backward without the attention matrices in memory (score tiles recomputed in the kernels that use them):
-// fp16 / bf16, d a multiple of 8 up to 128, with any of the module terms; every tensor 16-byte aligned, strides
-// multiples of 8 elements, windows addressed in place.  launch_backward takes this path whenever use_mfma is set and
-// the problem allows it.  A problem without agent bias and DWC (backward_pure_16bit) has no other path: its workspace
-// is this path's (a few n x d and N-long arrays, split partial sums).
+// Backward without the attention matrices in memory (score tiles recomputed in the kernels that use them): d up to
+// 128 in rows of whole 16-byte pieces, with any of the module terms, strided tensors and windows addressed in place
+// where fused_layout_supported.  A 16-bit problem without agent bias and DWC (backward_pure_16bit) has no other path:
+// its workspace is this path's (a few n x d and N-long arrays, split partial sums).
 bool backward_fused_supported(const Problem& p);
+bool fused_layout_supported(const Problem& p);
 bool backward_pure_16bit(const Problem& p);
 size_t backward_fused_workspace_floats(const Problem& p);
 hipError_t launch_backward_fused(const Problem& p, const void* Q, const void* K, const void* V, const void* A_elem,
                                  const void* dO, float* ws, void* dQ, void* dK, void* dV, void* dA, bool agents_given,
                                  const BackwardParamGrads& pg, hipStream_t st);
+// The forward pass of fp32 problems on the same kernels (agents A pooled or given, ws 256-byte aligned, every tensor
+// 16-byte aligned, fused_layout_supported)
+bool forward_f32_supported(const Problem& p);
+size_t forward_f32_workspace_floats(const Problem& p);
+hipError_t launch_forward_f32(const Problem& p, const void* Q, const void* K, const void* V, const void* A, float* ws,
+                              void* out, hipStream_t st);
 
 // --- small-agent regime (n <= 64, d in {32, 64}, fp16 / bf16): MFMA kernels that keep A and V_A in
 //     registers and stream tokens straight from global memory ---

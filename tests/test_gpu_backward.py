@@ -167,7 +167,9 @@ def test_backward_module_mode_many_tokens(aa, oracle, agrid, dtype, batch, heads
     ((9, 70), (9, 15), 128, "bf16", (1, 3), 1),     # one cell row; odd number of x-tiles; agents past one LDS chunk
     ((40, 17), (8, 16), 40, "f16", (3, 17), 3),     # one token in the last x-tile; exactly one LDS chunk of agents
     ((4, 200), (2, 33), 16, "bf16", (3, 2), 2),     # many pairs of columns per range, one segment
-    ((64, 3), (9, 3), 24, "f16", (9, 2), 1)])       # three columns wide, the rest of the tile masked
+    ((64, 3), (9, 3), 24, "f16", (9, 2), 1),        # three columns wide, the rest of the tile masked
+    ((13, 33), (8, 8), 96, "f32", (5, 4), 1),       # fp32: exactly one LDS chunk of agents, one token column per wave
+    ((21, 20), (5, 13), 128, "f32", (3, 3), 1), ((10, 47), (4, 4), 44, "f32", (2, 7), 2)])
 def test_backward_agent_bias_off_the_tile_sizes(aa, oracle, grid, agrid, d, dtype, blk, batch):
     """The recomputing kernels with an agent bias walk down 16-token columns of the image: grids, cell grids and
     agent counts on and off their tiles, every gradient (bars as everywhere in this file)."""

@@ -277,6 +277,25 @@ def test_module_terms_many_agents(aa, oracle, which, grid, agrid, blk, dtype, d)
                        max_abs=1e-2 * max(1.0, float(np.abs(ref).max())))
 
 
+@pytest.mark.parametrize("grid,agrid,d,module", [
+    ((31, 43), (7, 9), 48, True), ((20, 50), (8, 8), 64, False),      # a whole chunk of 64 agents in LDS
+    ((9, 16), (5, 13), 96, True), ((40, 33), (13, 10), 128, True),    # past one chunk, one token column per wave
+    ((12, 130), (4, 33), 20, False), ((60, 15), (11, 3), 36, True)])  # head widths padded to 32 and 48
+def test_forward_f32_streaming_kernels(aa, oracle, grid, agrid, d, module):
+    """fp32 problems that do not fit the one-launch kernel (tokens, agents or an agent bias): chunks, head widths and
+    grids on and off the tiles, every module term together; the fp32 bar."""
+    import dataclasses
+    wl = dataclasses.replace(WL["tiny"], batch=2, heads=2, grid=grid, agent_grid=agrid, d=d, index=15)
+    assert "forward_f32" in aa.plan_str(aa.make_desc(2, 2, wl.N, wl.n, d, 0, grid, agrid))
+    t = inputs.make_qkv(wl)
+    dv = dev_qkv(wl, t)
+    params = inputs.make_module_params(wl.heads, wl.n, d, grid, blk=(4, 3), index=15) if module else None
+    O = aa.agent_attn_fwd(dv["Q"], dv["K"], dv["V"], grid=grid, agent_grid=agrid, v_residual_k=0.075,
+                          params=util.params_to_device(params) if module else None)
+    ref = util.oracle_forward_units(oracle, wl, t, list(range(wl.units)), params=params, v_residual_k=0.075)
+    util.assert_parity(util.to_host64(O).reshape(ref.shape), ref, "f32", "fp32 streaming")
+
+
 _PREPARED_EXTRA = {"large_dense_many": dict(grid=(15, 15), agent_grid=(10, 13), d=64, dtype="bf16", heads=2),
                    "large_dense_few": dict(grid=(12, 10), agent_grid=(3, 5), d=40, dtype="f16", heads=2)}
 
