@@ -1163,7 +1163,7 @@ size_t backward_workspace_floats(const Problem& p) {
 }
 
 bool backward_pure_16bit(const Problem& p) {
-  return backward_fused_supported(p) && !p.b1.any() && !p.b2.any() && !p.dwc_w;
+  return p.dtype != 0 && backward_fused_supported(p) && !p.b1.any() && !p.b2.any() && !p.dwc_w;
 }
 
 hipError_t launch_backward(const Problem& p, const void* Q, const void* K, const void* V, const void* A_elem,
