@@ -13,8 +13,15 @@ enum { kFwd = 0, kBc = 1, kAgg = 2, kBcStat = 3, kOut = 4 };
 //   ta [heads][cells][ld / 4][wp][4 agents]     for lanes that hold a token and four agents
 //   tx [heads][cells][wp / 4][ld][4 columns]    for lanes that hold an agent and four neighbours in x
 // rows [heads][gh][ld], null when there is no row component.
+// yi [gh]: what an image row needs to know of the interpolation along y.
+struct YInfo {
+  int cell, next;      // cell row i; the first image row below with another one (or gh)
+  float f;             // weight of cell row i + 1 (0 on the last cell row)
+  int pad;
+};
 struct BiasTables {
   const float *ta, *tx, *rows;
+  const YInfo* yi;
   int cells, ld;
 };
 
@@ -28,10 +35,12 @@ struct UnitPlace {
   int nwin, wxn, ww, win_rows;                           // win_rows: image rows of a window times line
 
   static uint32_t inverse(int v) { return v > 1 ? (uint32_t)((((uint64_t)1 << 32) + v - 1) / v) : 0u; }
-  // strides below 2^32 elements; windows only where N * ww < 2^32
+  static unsigned long long rows(const Layout& l, int N) { return l.line ? (unsigned long long)l.wh * l.line : (unsigned long long)N; }
+  // strides below 2^32 elements, a unit's extent below 2^32 bytes; windows only where N * ww < 2^32
   static bool fits(const Layout& l, int N) {
     return (unsigned long long)l.sb >> 32 == 0 && (unsigned long long)l.sh >> 32 == 0 && (unsigned long long)l.ob >> 32 == 0 &&
-           (unsigned long long)l.oh >> 32 == 0 && (l.line == 0 || (unsigned long long)N * l.ww >> 32 == 0);
+           (unsigned long long)l.oh >> 32 == 0 && (l.line == 0 || (unsigned long long)N * l.ww >> 32 == 0) &&
+           rows(l, N) * (unsigned long long)l.sn >> 30 == 0 && rows(l, N) * (unsigned long long)l.on >> 30 == 0;
   }
   static UnitPlace make(const Layout& l, int heads) {
     UnitPlace p{};
@@ -91,7 +100,7 @@ struct AgentArgs {
   float sc;
   UnitPlace at;               // Q, K, V lie with the input strides, dO with the output strides
   int gh, gw;
-  // with a bias: ranges are `per` of the `pairs` pairs of columns (see Walk in backward_fused.inc), a column being 16
+  // with a bias: ranges are `per` of the `pairs` pairs of columns (see bias_agent_kernel), a column being 16
   // neighbours in x of the seg_len image rows of one of `segs` segments
   int segs, seg_len, pairs, per;
   BiasTables bt;
@@ -109,7 +118,7 @@ hipError_t launch_agent(int prob, int dp, int cols, const AgentArgs& a, dim3 gri
 // --- backward_module.hip ---
 // Tables of one kind (1 or 2) into ta, tx, rows (rows null: no row component).
 hipError_t launch_backward_bias_tables(const Problem& p, int kind, int cells, int ld, float* ta, float* tx, float* rows,
-                                       hipStream_t st);
+                                       YInfo* yi, hipStream_t st);
 // Parts of one kind's bias gradients as the agent kernels leave them (fp32, unrounded score gradients):
 //   gt [units][segs][cells][wp / 4][ld][4]    sums of (1 - f) dS and f dS over the image rows of a segment, for the
 //                                             cell rows the segment touches (others are not written)

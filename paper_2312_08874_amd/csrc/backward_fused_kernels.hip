@@ -92,14 +92,14 @@ __global__ __launch_bounds__(64) void fused_reduce_agg_kernel(const float* __res
 // host side
 // ---------------------------------------------------------------------------
 struct FusedPlan {
-  int DP, n_rows, ch_rows, agent_cols, token_cols, agent_blocks, S[2], chunk[2];      // [0]: agent kBc, [1]: agent kFwd / kAgg
+  int DP, n_rows, ch_rows, token_cols, agent_cols[2], agent_blocks[2], S[2], chunk[2];      // [0]: agent kBc, [1]: kFwd / kAgg
   bool wide;
   // agent bias, [0]: the broadcast's (B2), [1]: the aggregation's (B1); segments and pairs of columns as in AgentArgs
   bool bias[2];
   int cells[2], ld, segs[2], seg_len[2], pairs[2], per[2];
   // workspace offsets in floats (every region a multiple of 64 floats)
   size_t VAf, VAe, dVAe, lse1, D1, lse2, D2, dAf, part, total;
-  size_t ta[2], tx[2], rows[2], gt[2], gr[2], gsum[2], dwc;
+  size_t ta[2], tx[2], rows[2], yi[2], gt[2], gr[2], gsum[2], dwc;
 };
 
 size_t up64(size_t v) { return (v + 63) / 64 * 64; }
@@ -111,28 +111,29 @@ FusedPlan fused_plan(const Problem& p, bool forward = false) {
   f.DP = p.d <= 32 ? 32 : (f32 && p.d <= 48 ? 48 : (p.d <= 64 ? 64 : (f32 && p.d <= 96 ? 96 : 128)));
   f.n_rows = (p.n + 31) / 32 * 32;      // the token kernels take agent tiles in pairs
   f.ch_rows = std::min(f.n_rows, f32 ? El<ElemF32>::kChunk : El<ElemBF16>::kChunk);
-  f.agent_cols = (f32 || f.DP == 128 || p.n <= 64) ? 1 : 2;
+  f.bias[0] = p.b2.any(), f.bias[1] = p.b1.any();
   f.token_cols = f32 && f.DP > 64 ? 1 : 2;
-  const int per_block = 64 * f.agent_cols;      // agents per block of the agent kernels
-  f.agent_blocks = (p.n + per_block - 1) / per_block;
-  const int groups = f.agent_blocks * p.units;
-  // token ranges: about two blocks per CU for the broadcast's agent kernel (192 registers), three for the other
-  // two (which fit three blocks; four measured no faster).  At most 64: the merge gives every range a lane.
+  // token ranges: about two blocks per CU for the broadcast's agent kernel (192 registers) and with a bias, three for
+  // the other two (which fit three blocks; four measured no faster).  At most 64: the merge gives every range a lane.
+  int groups[2];
   for (int k = 0; k < 2; ++k) {
-    int S = ((2 + k) * kComputeUnits + groups - 1) / groups;
-    S = max(min(min(S, 64), (p.N + 127) / 128), 1);
+    f.agent_cols[k] = (f32 || f.DP == 128 || p.n <= 64 || (k == 0 && f.bias[0] && f.DP == 64)) ? 1 : 2;
+    const int per_block = 64 * f.agent_cols[k];      // agents per block
+    f.agent_blocks[k] = (p.n + per_block - 1) / per_block;
+    groups[k] = f.agent_blocks[k] * p.units;
+    f.ld = std::max(f.ld, f.agent_blocks[k] * per_block);
+    int S = ((2 + k) * kComputeUnits + groups[k] - 1) / groups[k];
+    S = std::max(std::min(std::min(S, 64), (p.N + 127) / 128), 1);
     f.chunk[k] = ((p.N + S - 1) / S + 31) / 32 * 32;
     f.S[k] = (p.N + f.chunk[k] - 1) / f.chunk[k];
   }
-  f.bias[0] = p.b2.any(), f.bias[1] = p.b1.any();
   f.cells[0] = p.b2.blk ? p.b2.h0 : 1, f.cells[1] = p.b1.blk ? p.b1.h0 : 1;
-  f.ld = std::max((p.n + 63) / 64 * 64, f.agent_blocks * per_block);
   const int xts = (p.gw + 15) / 16;
   for (int k = 0; k < 2; ++k) {
     if (!f.bias[k]) continue;
     // the ranges are pairs of columns: enough segments of at least four image rows for the number of ranges wanted,
     // an even number of columns, ranges of equally many pairs
-    const int want = std::max(std::min((2 * kComputeUnits + groups - 1) / groups, 64), 1);
+    const int want = std::max(std::min((2 * kComputeUnits + groups[k] - 1) / groups[k], 64), 1);
     int segs = std::max(1, std::min((2 * want + xts - 1) / xts, p.gh / 4));
     if (xts % 2 == 1 && segs % 2 == 1 && segs < p.gh) ++segs;
     f.seg_len[k] = (p.gh + segs - 1) / segs;
@@ -165,6 +166,7 @@ FusedPlan fused_plan(const Problem& p, bool forward = false) {
     f.ta[k] = o, o += table;
     f.tx[k] = o, o += table;
     f.rows[k] = o, o += up64(H * p.gh * f.ld);
+    f.yi[k] = o, o += up64((size_t)4 * p.gh);
     if (forward) continue;
     f.gt[k] = o, o += up64(u * f.segs[k] * f.cells[k] * f.ld * wp);
     f.gr[k] = o, o += up64(u * xts * p.gh * f.ld);
@@ -190,8 +192,9 @@ struct Pass {
       if (!f.bias[k]) continue;
       const bool has_rows = k == 0 ? p.b2.row != nullptr : p.b1.row != nullptr;
       float* rows = has_rows ? ws + f.rows[k] : nullptr;
-      bt[k] = BiasTables{ws + f.ta[k], ws + f.tx[k], rows, f.cells[k], f.ld};
-      const hipError_t e = launch_backward_bias_tables(p, k == 0 ? 2 : 1, f.cells[k], f.ld, ws + f.ta[k], ws + f.tx[k], rows, st);
+      YInfo* yi = reinterpret_cast<YInfo*>(ws + f.yi[k]);
+      bt[k] = BiasTables{ws + f.ta[k], ws + f.tx[k], rows, yi, f.cells[k], f.ld};
+      const hipError_t e = launch_backward_bias_tables(p, k == 0 ? 2 : 1, f.cells[k], f.ld, ws + f.ta[k], ws + f.tx[k], rows, yi, st);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -212,12 +215,12 @@ struct Pass {
   hipError_t agent(int prob, AgentArgs& a, float* gt, float* gr) {
     const int k = prob == kBc ? 0 : 1;
     const size_t lds = (size_t)4 * 32 * (f.DP + El<E>::kRowPad) * sizeof(T) + 2 * 64 * sizeof(float);
-    const dim3 grid(f.S[k], f.agent_blocks, p.units);
+    const dim3 grid(f.S[k], f.agent_blocks[k], p.units);
     a.chunk = f.chunk[k], a.S = f.S[k];
-    if (!f.bias[k]) return launch_agent<E, false>(prob, f.DP, f.agent_cols, a, grid, lds, st);
+    if (!f.bias[k]) return launch_agent<E, false>(prob, f.DP, f.agent_cols[k], a, grid, lds, st);
     a.bt = bt[k], a.segs = f.segs[k], a.seg_len = f.seg_len[k], a.pairs = f.pairs[k], a.per = f.per[k];
     a.gt = gt, a.gr = gr;
-    return launch_agent<E, true>(prob, f.DP, f.agent_cols, a, grid, lds, st);
+    return launch_agent<E, true>(prob, f.DP, f.agent_cols[k], a, grid, lds, st);
   }
   AgentArgs agent_args() const {
     AgentArgs a{};
@@ -305,7 +308,7 @@ hipError_t run_fused(const Problem& p, const FusedPlan& f, const void* Q, const 
 
 bool backward_fused_supported(const Problem& p) {
   return p.d % (p.dtype == 0 ? 4 : 8) == 0 && p.d <= 128 && p.units <= 65535 &&
-         (unsigned long long)p.N * p.d * p.heads < (1ull << 32);      // dense strides fit UnitPlace
+         (unsigned long long)p.N * p.d * p.heads < (1ull << 32) && (unsigned long long)p.N * p.d < (1ull << 30);      // UnitPlace::fits, dense
 }
 
 bool fused_layout_supported(const Problem& p) {

@@ -9,13 +9,13 @@ namespace {
 
 // ---------------------------------------------------------------------------
 // Tables of one bias kind (BiasTables).  Blocks [0, tblocks): a thread takes four columns x four agents of one cell
-// row, lanes along the agents (tx is then written in one piece per wave, ta in 64-byte pieces).  The rest: R, four
-// agents per thread.
+// row, lanes along the agents (tx is then written in one piece per wave, ta in 64-byte pieces).  The next rblocks: R,
+// four agents per thread.  The rest: the image rows' interpolation along y.
 // ---------------------------------------------------------------------------
 template <int KIND>
 __global__ __launch_bounds__(256) void bias_tables_kernel(BiasArgs b, float* __restrict__ ta, float* __restrict__ tx,
-                                                          float* __restrict__ rows, int heads, int n, int gh, int gw, int cells,
-                                                          int ld, unsigned tblocks) {
+                                                          float* __restrict__ rows, YInfo* __restrict__ yi, int heads, int n,
+                                                          int gh, int gw, int cells, int ld, unsigned tblocks, unsigned rblocks) {
   const int l4 = ld / 4, wp = (gw + 15) / 16 * 16;
   if (blockIdx.x < tblocks) {
     const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(256) void bias_tables_kernel(BiasArgs b, float* __r
 #pragma unroll
     for (int k = 0; k < 4; ++k)
       *reinterpret_cast<f32x4*>(tx + base + ((size_t)x4 * ld + 4 * a4 + k) * 4) = f32x4{v[0][k], v[1][k], v[2][k], v[3][k]};
-  } else {
+  } else if (blockIdx.x < tblocks + rblocks) {
     const size_t i = (size_t)(blockIdx.x - tblocks) * 256 + threadIdx.x;
     const int a4 = (int)(i % l4), y = (int)(i / l4 % gh), hd = (int)(i / l4 / gh);
     if (hd >= heads) return;
@@ -69,6 +69,20 @@ __global__ __launch_bounds__(256) void bias_tables_kernel(BiasArgs b, float* __r
       v[k] = a < n ? kLog2e * (KIND == 1 ? b.row[((size_t)hd * n + a) * gh + y] : b.row[((size_t)hd * gh + y) * n + a]) : 0.0f;
     }
     *reinterpret_cast<f32x4*>(rows + ((size_t)hd * gh + y) * ld + 4 * a4) = f32x4{v[0], v[1], v[2], v[3]};
+  } else {
+    const int y = (int)(blockIdx.x - tblocks - rblocks) * 256 + threadIdx.x;
+    if (y >= gh) return;
+    int i0, i1;
+    float f;
+    bilinear_coord(y, gh, cells, i0, i1, f);
+    int next = y + 1;
+    for (; next < gh; ++next) {
+      int c;
+      float g;
+      bilinear_coord(next, gh, cells, c, i1, g);
+      if (c != i0) break;
+    }
+    yi[y] = YInfo{i0, next, i0 >= cells - 1 ? 0.0f : f, 0};
   }
 }
 
@@ -307,16 +321,15 @@ DwcPlan dwc_plan(const Problem& p) {
 }  // namespace
 
 hipError_t launch_backward_bias_tables(const Problem& p, int kind, int cells, int ld, float* ta, float* tx, float* rows,
-                                       hipStream_t st) {
+                                       YInfo* yi, hipStream_t st) {
   const int wp = (p.gw + 15) / 16 * 16;
   const size_t tcount = (size_t)p.heads * cells * (wp / 4) * (ld / 4), rcount = rows ? (size_t)p.heads * p.gh * (ld / 4) : 0;
-  const unsigned tblocks = (unsigned)((tcount + 255) / 256), rblocks = (unsigned)((rcount + 255) / 256);
+  const unsigned tb = (unsigned)((tcount + 255) / 256), rb = (unsigned)((rcount + 255) / 256), yb = (unsigned)((p.gh + 255) / 256);
+  const dim3 grid(tb + rb + yb);
   if (kind == 1)
-    bias_tables_kernel<1><<<dim3(tblocks + rblocks), dim3(256), 0, st>>>(p.b1, ta, tx, rows, p.heads, p.n, p.gh, p.gw, cells,
-                                                                        ld, tblocks);
+    bias_tables_kernel<1><<<grid, dim3(256), 0, st>>>(p.b1, ta, tx, rows, yi, p.heads, p.n, p.gh, p.gw, cells, ld, tb, rb);
   else
-    bias_tables_kernel<2><<<dim3(tblocks + rblocks), dim3(256), 0, st>>>(p.b2, ta, tx, rows, p.heads, p.n, p.gh, p.gw, cells,
-                                                                        ld, tblocks);
+    bias_tables_kernel<2><<<grid, dim3(256), 0, st>>>(p.b2, ta, tx, rows, yi, p.heads, p.n, p.gh, p.gw, cells, ld, tb, rb);
   return hipGetLastError();
 }
 
