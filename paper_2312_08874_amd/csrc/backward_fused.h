@@ -116,9 +116,8 @@ template <class E, bool BIAS>
 hipError_t launch_agent(int prob, int dp, int cols, const AgentArgs& a, dim3 grid, size_t lds, hipStream_t st);
 
 // --- backward_module.hip ---
-// Tables of one kind (1 or 2) into ta, tx, rows (rows null: no row component).
-hipError_t launch_backward_bias_tables(const Problem& p, int kind, int cells, int ld, float* ta, float* tx, float* rows,
-                                       YInfo* yi, hipStream_t st);
+// Fills the tables of the kinds in use ([0]: B2, [1]: B1; the same ld, a multiple of 64).
+hipError_t launch_backward_bias_tables(const Problem& p, const BiasTables (&t)[2], const bool (&used)[2], hipStream_t st);
 // Parts of one kind's bias gradients as the agent kernels leave them (fp32, unrounded score gradients):
 //   gt [units][segs][cells][wp / 4][ld][4]    sums of (1 - f) dS and f dS over the image rows of a segment, for the
 //                                             cell rows the segment touches (others are not written)
@@ -129,12 +128,11 @@ struct BiasGradParts {
   float* sum;
   int segs, seg_len, cells, ld;
 };
-hipError_t launch_backward_bias_grads(const Problem& p, int kind, const BiasGradParts& parts, int h0, int w0, float* col,
-                                      float* row, float* blk, hipStream_t st);
-// DWC parameter gradients from V and dO in the element type (d a multiple of 8, 16-byte rows); part: room for
-// dwc_param_part_floats() floats
 size_t dwc_param_part_floats(const Problem& p);
-hipError_t launch_dwc_param_grads(const Problem& p, const void* V, const void* dO, float* part, float* dw, float* db,
-                                  hipStream_t st);
+// The parameter gradients: the bias components' from parts ([0]: B2, [1]: B1; gt null: not in use), the convolution's
+// from V and dO in the element type (d a multiple of 8, fp32 of 4, 16-byte rows); dwc_part: room for
+// dwc_param_part_floats() floats.
+hipError_t launch_backward_param_grads(const Problem& p, const BiasGradParts (&parts)[2], const BackwardParamGrads& pg,
+                                       const void* V, const void* dO, float* dwc_part, hipStream_t st);
 
 }  // namespace aa

@@ -194,10 +194,8 @@ struct Pass {
       float* rows = has_rows ? ws + f.rows[k] : nullptr;
       YInfo* yi = reinterpret_cast<YInfo*>(ws + f.yi[k]);
       bt[k] = BiasTables{ws + f.ta[k], ws + f.tx[k], rows, yi, f.cells[k], f.ld};
-      const hipError_t e = launch_backward_bias_tables(p, k == 0 ? 2 : 1, f.cells[k], f.ld, ws + f.ta[k], ws + f.tx[k], rows, yi, st);
-      if (e != hipSuccess) return e;
     }
-    return hipSuccess;
+    return launch_backward_bias_tables(p, bt, f.bias, st);
   }
   hipError_t token(int prob, TokenArgs& a) {
     const int k = prob == kAgg ? 1 : 0;
@@ -292,16 +290,10 @@ hipError_t run_fused(const Problem& p, const FusedPlan& f, const void* Q, const 
   tk.X = Q, tk.Y = dO, tk.M2 = VAe, tk.sc = sc2, tk.oscale = p.scale2, tk.O1 = dQ, tk.dA = agents_given ? nullptr : dAf;
   if ((e = pass.token(kBc, tk)) != hipSuccess) return e;
 
-  // parameter gradients
-  for (int k = 0; k < 2; ++k) {
-    if (!f.bias[k]) continue;
-    const BiasGradParts parts{ws + f.gt[k], ws + f.gr[k], ws + f.gsum[k], f.segs[k], f.seg_len[k], f.cells[k], f.ld};
-    e = k == 0 ? launch_backward_bias_grads(p, 2, parts, pg.h0, pg.w0, pg.db2_col, pg.db2_row, pg.db2_blk, st)
-               : launch_backward_bias_grads(p, 1, parts, pg.h0, pg.w0, pg.db1_col, pg.db1_row, pg.db1_blk, st);
-    if (e != hipSuccess) return e;
-  }
-  if (p.dwc_w && pg.ddwc_w) return launch_dwc_param_grads(p, V, dO, ws + f.dwc, pg.ddwc_w, pg.ddwc_b, st);
-  return hipGetLastError();
+  BiasGradParts parts[2] = {};
+  for (int k = 0; k < 2; ++k)
+    if (f.bias[k]) parts[k] = BiasGradParts{ws + f.gt[k], ws + f.gr[k], ws + f.gsum[k], f.segs[k], f.seg_len[k], f.cells[k], f.ld};
+  return launch_backward_param_grads(p, parts, pg, V, dO, ws + f.dwc, st);
 }
 
 }  // namespace

@@ -8,82 +8,110 @@ namespace aa {
 namespace {
 
 // ---------------------------------------------------------------------------
-// Tables of one bias kind (BiasTables).  Blocks [0, tblocks): a thread takes four columns x four agents of one cell
-// row, lanes along the agents (tx is then written in one piece per wave, ta in 64-byte pieces).  The next rblocks: R,
-// four agents per thread.  The rest: the image rows' interpolation along y.
+// Tables of both bias kinds (BiasTables) in one launch.  A block makes a tile of 64 agents x 16 columns of one cell row
+// (T) or x 16 image rows (R) in LDS: the components are read with the lanes along their contiguous axis (columns or
+// rows for B1, agents for B2) and both orders of T are written in pieces of 256 bytes and more.  The last blocks of a
+// kind: the image rows' interpolation along y.  Bound by the tables' bytes; with the lanes always along the agents
+// B1's components were read, and ta written, a few bytes per line (8 heads, 1024 agents, 128 x 128 tokens: 126 -> 44 us
+// for the 117 MB of both kinds; 3 heads, 49 agents, 14 x 14 tokens, where it is the launches: 14 -> 4 us).
 // ---------------------------------------------------------------------------
+struct TableKind {
+  BiasArgs b;
+  float *ta, *tx, *rows;
+  YInfo* yi;
+  int kind, cells;
+  unsigned tblocks, rblocks, blocks;
+};
+
 template <int KIND>
-__global__ __launch_bounds__(256) void bias_tables_kernel(BiasArgs b, float* __restrict__ ta, float* __restrict__ tx,
-                                                          float* __restrict__ rows, YInfo* __restrict__ yi, int heads, int n,
-                                                          int gh, int gw, int cells, int ld, unsigned tblocks, unsigned rblocks) {
-  const int l4 = ld / 4, wp = (gw + 15) / 16 * 16;
-  if (blockIdx.x < tblocks) {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    const int a4 = (int)(i % l4);
-    const size_t rest = i / l4;
-    const int x4 = (int)(rest % (wp / 4));
-    const int cell = (int)(rest / (wp / 4) % cells), hd = (int)(rest / (wp / 4) / cells);
-    if (hd >= heads) return;
-    float v[4][4];      // [column][agent]
+__device__ __forceinline__ void bias_table_block(const TableKind& k, unsigned block, int n, int gh, int gw, int ld,
+                                                 float (&tile)[16][68]) {
+  const BiasArgs& b = k.b;
+  const int tid = threadIdx.x, ats = ld / 64, xts = (gw + 15) / 16, yts = (gh + 15) / 16;
+  // entry (i, a) of the tile this thread makes in step j: lanes along the components' contiguous axis
+  auto place = [&](int j, int& i, int& al) {
+    i = KIND == 1 ? tid & 15 : (tid >> 6) + 4 * j;
+    al = KIND == 1 ? (tid >> 4) + 16 * j : tid & 63;
+  };
+  if (block < k.tblocks) {
+    const int at = block % ats, xt = block / ats % xts, cell = block / ats / xts % k.cells, hd = block / ats / xts / k.cells;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int x = 4 * x4 + j;
-      int x0 = 0, x1 = 0;
-      float fx = 0.0f;
-      if (b.blk) bilinear_coord(min(x, gw - 1), gw, b.w0, x0, x1, fx);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const int a = 4 * a4 + k;
-        float s = 0.0f;
-        if (x >= gw) {
-          s = -1.0e30f;      // a column past the image weighs nothing
-        } else if (a < n) {
-          if (b.col) s = KIND == 1 ? b.col[((size_t)hd * n + a) * gw + x] : b.col[((size_t)hd * gw + x) * n + a];
-          if (b.blk) {
-            const size_t step = KIND == 1 ? 1 : n;
-            const float* q = KIND == 1 ? b.blk + (((size_t)hd * n + a) * b.h0 + cell) * b.w0
-                                       : b.blk + ((size_t)hd * b.h0 + cell) * b.w0 * n + a;
-            const float v0 = q[x0 * step], v1 = q[x1 * step];
-            s += v0 + (v1 - v0) * fx;
-          }
-          s *= kLog2e;
+      int i, al;
+      place(j, i, al);
+      const int x = 16 * xt + i, a = 64 * at + al;
+      float v = 0.0f;
+      if (x >= gw) {
+        v = -1.0e30f;      // a column past the image weighs nothing
+      } else if (a < n) {
+        if (b.col) v = KIND == 1 ? b.col[((size_t)hd * n + a) * gw + x] : b.col[((size_t)hd * gw + x) * n + a];
+        if (b.blk) {
+          int x0, x1;
+          float fx;
+          bilinear_coord(x, gw, b.w0, x0, x1, fx);
+          const size_t step = KIND == 1 ? 1 : n;
+          const float* q = KIND == 1 ? b.blk + (((size_t)hd * n + a) * b.h0 + cell) * b.w0
+                                     : b.blk + ((size_t)hd * b.h0 + cell) * b.w0 * n + a;
+          const float v0 = q[x0 * step], v1 = q[x1 * step];
+          v += v0 + (v1 - v0) * fx;
         }
-        v[j][k] = s;
+        v *= kLog2e;
       }
+      tile[i][al] = v;
     }
-    const size_t base = ((size_t)hd * cells + cell) * ld * wp;
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      *reinterpret_cast<f32x4*>(ta + base + ((size_t)a4 * wp + 4 * x4 + j) * 4) = f32x4{v[j][0], v[j][1], v[j][2], v[j][3]};
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      *reinterpret_cast<f32x4*>(tx + base + ((size_t)x4 * ld + 4 * a4 + k) * 4) = f32x4{v[0][k], v[1][k], v[2][k], v[3][k]};
-  } else if (blockIdx.x < tblocks + rblocks) {
-    const size_t i = (size_t)(blockIdx.x - tblocks) * 256 + threadIdx.x;
-    const int a4 = (int)(i % l4), y = (int)(i / l4 % gh), hd = (int)(i / l4 / gh);
-    if (hd >= heads) return;
-    float v[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int a = 4 * a4 + k;
-      v[k] = a < n ? kLog2e * (KIND == 1 ? b.row[((size_t)hd * n + a) * gh + y] : b.row[((size_t)hd * gh + y) * n + a]) : 0.0f;
+    __syncthreads();
+    const int wp = 16 * xts;
+    const size_t base = ((size_t)hd * k.cells + cell) * ld * wp;
+    {
+      const int i = tid & 15, a4 = tid >> 4;
+      *reinterpret_cast<f32x4*>(k.ta + base + ((size_t)(16 * at + a4) * wp + 16 * xt + i) * 4) =
+          *reinterpret_cast<const f32x4*>(&tile[i][4 * a4]);
     }
-    *reinterpret_cast<f32x4*>(rows + ((size_t)hd * gh + y) * ld + 4 * a4) = f32x4{v[0], v[1], v[2], v[3]};
+    const int x4 = tid >> 6, al = tid & 63;
+    *reinterpret_cast<f32x4*>(k.tx + base + ((size_t)(4 * xt + x4) * ld + 64 * at + al) * 4) =
+        f32x4{tile[4 * x4][al], tile[4 * x4 + 1][al], tile[4 * x4 + 2][al], tile[4 * x4 + 3][al]};
+  } else if (block < k.tblocks + k.rblocks) {
+    block -= k.tblocks;
+    const int at = block % ats, yt = block / ats % yts, hd = block / ats / yts;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      int i, al;
+      place(j, i, al);
+      const int y = 16 * yt + i, a = 64 * at + al;
+      float v = 0.0f;
+      if (y < gh && a < n) v = kLog2e * (KIND == 1 ? b.row[((size_t)hd * n + a) * gh + y] : b.row[((size_t)hd * gh + y) * n + a]);
+      tile[i][al] = v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int i = (tid >> 6) + 4 * j, al = tid & 63, y = 16 * yt + i;
+      if (y < gh) k.rows[((size_t)hd * gh + y) * ld + 64 * at + al] = tile[i][al];
+    }
   } else {
-    const int y = (int)(blockIdx.x - tblocks - rblocks) * 256 + threadIdx.x;
+    const int y = (int)(block - k.tblocks - k.rblocks) * 256 + tid;
     if (y >= gh) return;
     int i0, i1;
     float f;
-    bilinear_coord(y, gh, cells, i0, i1, f);
+    bilinear_coord(y, gh, k.cells, i0, i1, f);
     int next = y + 1;
     for (; next < gh; ++next) {
       int c;
       float g;
-      bilinear_coord(next, gh, cells, c, i1, g);
+      bilinear_coord(next, gh, k.cells, c, i1, g);
       if (c != i0) break;
     }
-    yi[y] = YInfo{i0, next, i0 >= cells - 1 ? 0.0f : f, 0};
+    k.yi[y] = YInfo{i0, next, i0 >= k.cells - 1 ? 0.0f : f, 0};
   }
+}
+
+__global__ __launch_bounds__(256) void bias_tables_kernel(TableKind first, TableKind second, int n, int gh, int gw, int ld) {
+  __shared__ __align__(16) float tile[16][68];
+  const bool one = blockIdx.x < first.blocks;
+  const unsigned block = one ? blockIdx.x : blockIdx.x - first.blocks;
+  const TableKind& k = one ? first : second;
+  if (k.kind == 1) bias_table_block<1>(k, block, n, gh, gw, ld, tile);
+  else bias_table_block<2>(k, block, n, gh, gw, ld, tile);
 }
 
 // cell rows [c0, c1] that the image rows of segment s touch
@@ -95,76 +123,152 @@ __device__ __forceinline__ void segment_cells(int s, int seg_len, int gh, int ce
   c1 = min(c1 + 1, cells - 1);
 }
 
+// What the gradients of one bias kind are made from and where they go (null: not wanted)
+struct GradKind {
+  const f32x4 *gt, *sum;      // sum: of the parts, = gt where there is a single one
+  f32x4* total;               // where the sum goes (null: a single part)
+  const float* gr;
+  float *col, *row, *blk;
+  int kind, segs, seg_len, cells, w0;
+  float live;                 // 0: the softmax has a single entry, is constant, and its scores' gradients are zero (the
+                              // parts hold the rounding error of a difference of equal terms)
+  unsigned sblocks, cblocks, rblocks, blocks;
+};
+
 // sum [heads][cells][wp / 4][ld] of four columns each: the parts of the batch's units and their segments, in order
-__global__ __launch_bounds__(256) void bias_grad_sum_kernel(const f32x4* __restrict__ gt, f32x4* __restrict__ sum, int batch,
-                                                            int heads, int segs, int seg_len, int gh, int cells, size_t per_cell) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= (size_t)heads * cells * per_cell) return;
+__global__ __launch_bounds__(256) void bias_grad_sum_kernel(GradKind first, GradKind second, int batch, int heads, int gh,
+                                                            size_t per_cell) {
+  const bool one = blockIdx.x < first.sblocks;
+  const GradKind& k = one ? first : second;
+  const size_t i = (size_t)(one ? blockIdx.x : blockIdx.x - first.sblocks) * 256 + threadIdx.x;
+  if (i >= (size_t)heads * k.cells * per_cell) return;
   const size_t e = i % per_cell;
-  const int cell = (int)(i / per_cell % cells), hd = (int)(i / per_cell / cells);
+  const int cell = (int)(i / per_cell % k.cells), hd = (int)(i / per_cell / k.cells);
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int s = 0; s < segs; ++s) {
+  for (int s = 0; s < k.segs; ++s) {
     int c0, c1;
-    segment_cells(s, seg_len, gh, cells, c0, c1);
+    segment_cells(s, k.seg_len, gh, k.cells, c0, c1);
     if (cell < c0 || cell > c1) continue;
-    const f32x4* p = gt + (((size_t)hd * segs + s) * cells + cell) * per_cell + e;
-    const size_t step = (size_t)heads * segs * cells * per_cell;
-#pragma unroll 4
+    const f32x4* p = k.gt + (((size_t)hd * k.segs + s) * k.cells + cell) * per_cell + e;
+    const size_t step = (size_t)heads * k.segs * k.cells * per_cell;
+#pragma unroll 16      // a round trip to memory per sixteen images, not per four
     for (int bt = 0; bt < batch; ++bt) acc += p[bt * step];
   }
-  sum[i] = acc;
+  k.total[i] = acc;
 }
 
-// The components' gradients from the sums: column blocks, then row blocks, then block-cell blocks, one output element
-// per thread, lanes along the agents.  live = 0: the softmax has a single entry, is constant, and its scores' gradients
-// are zero (the parts hold the rounding error of a difference of equal terms).
+// The components' gradients from the sums: column blocks (a thread has an agent and four columns), then row blocks (a
+// block has 64 agents and four image rows, its waves share out the parts), then block-cell blocks (one output element
+// per thread, over the columns that can touch it), lanes along the agents; after both kinds the convolution's
+// parameter gradients from their slices.  One launch, because small problems are a chain of launches (3 heads, batch
+// 64, 49 agents, 14 x 14 tokens: 81 -> 14 us with the sums above); there a thread walking the batch alone took a round
+// trip per image.  8 heads, 1024 agents, 128 x 128 tokens: 123 -> 71 us, bound by reading the parts and sums (150 MB).
 template <int KIND>
-__global__ __launch_bounds__(256) void bias_grad_out_kernel(const f32x4* __restrict__ sum, const float* __restrict__ gr,
-                                                            float* __restrict__ col, float* __restrict__ row,
-                                                            float* __restrict__ blk, int batch, int heads, int n, int gh, int gw,
-                                                            int cells, int w0, int ld, float live, unsigned cblocks,
-                                                            unsigned rblocks) {
-  const int xts = (gw + 15) / 16, wp = 16 * xts;
+__device__ __forceinline__ void bias_grad_block(const GradKind& k, unsigned block, int batch, int heads, int n, int gh, int gw,
+                                                int ld, float (&red)[4][4][64]) {
+  const int xts = (gw + 15) / 16, wp = 16 * xts, tid = threadIdx.x;
   const size_t per_cell = (size_t)wp / 4 * ld;
-  if (blockIdx.x < cblocks) {
-    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-    const int a = (int)(i % n), x = (int)(i / n % gw), hd = (int)(i / n / gw);
+  if (block < k.cblocks) {
+    const int gw4 = (gw + 3) / 4;
+    const size_t i = (size_t)block * 256 + tid;
+    const int a = (int)(i % n), x4 = (int)(i / n % gw4), hd = (int)(i / n / gw4);
     if (hd >= heads) return;
-    float v = 0.0f;
-    for (int c = 0; c < cells; ++c) v += sum[((size_t)hd * cells + c) * per_cell + (size_t)(x >> 2) * ld + a][x & 3];
-    col[KIND == 1 ? ((size_t)hd * n + a) * gw + x : ((size_t)hd * gw + x) * n + a] = live * v;
-  } else if (blockIdx.x < cblocks + rblocks) {
-    const size_t i = (size_t)(blockIdx.x - cblocks) * 256 + threadIdx.x;
-    const int a = (int)(i % n), y = (int)(i / n % gh), hd = (int)(i / n / gh);
-    if (hd >= heads) return;
-    float v = 0.0f;
-    for (int bt = 0; bt < batch; ++bt)
+    const f32x4* p = k.sum + (size_t)hd * k.cells * per_cell + (size_t)x4 * ld + a;
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+    for (int c = 0; c < k.cells; ++c) v += p[c * per_cell];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int x = 4 * x4 + j;
+      if (x < gw) k.col[KIND == 1 ? ((size_t)hd * n + a) * gw + x : ((size_t)hd * gw + x) * n + a] = k.live * v[j];
+    }
+  } else if (block < k.cblocks + k.rblocks) {
+    block -= k.cblocks;
+    const int ats = (n + 63) / 64, gh4 = (gh + 3) / 4;
+    const int at = block % ats, y0 = 4 * (int)(block / ats % gh4), hd = block / ats / gh4;
+    const int lane = tid & 63, w = tid >> 6;
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    const size_t part = (size_t)gh * ld;
+    const float* p = k.gr + (size_t)hd * xts * part + 64 * at + lane;      // ld reaches past the last tile's agents
 #pragma unroll 4
-      for (int t = 0; t < xts; ++t) v += gr[((((size_t)bt * heads + hd) * xts + t) * gh + y) * ld + a];
-    row[KIND == 1 ? ((size_t)hd * n + a) * gh + y : ((size_t)hd * gh + y) * n + a] = live * v;
+    for (int q = w; q < batch * xts; q += 4) {
+      const int bt = q / xts, t = q - bt * xts;
+      const float* r = p + ((size_t)bt * heads * xts + t) * part;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] += r[(size_t)min(y0 + j, gh - 1) * ld];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) red[w][j][lane] = v[j];
+    __syncthreads();
+    const int j = KIND == 1 ? tid & 3 : w, al = KIND == 1 ? tid >> 2 : lane, a = 64 * at + al, y = y0 + j;
+    if (a < n && y < gh)
+      k.row[KIND == 1 ? ((size_t)hd * n + a) * gh + y : ((size_t)hd * gh + y) * n + a] =
+          k.live * ((red[0][j][al] + red[1][j][al]) + (red[2][j][al] + red[3][j][al]));
   } else {
-    const size_t i = (size_t)(blockIdx.x - cblocks - rblocks) * 256 + threadIdx.x;
-    const int a = (int)(i % n), q = (int)(i / n % w0), cell = (int)(i / n / w0 % cells), hd = (int)(i / n / w0 / cells);
+    const size_t i = (size_t)(block - k.cblocks - k.rblocks) * 256 + tid;
+    const int a = (int)(i % n), q = (int)(i / n % k.w0), cell = (int)(i / n / k.w0 % k.cells), hd = (int)(i / n / k.w0 / k.cells);
     if (hd >= heads) return;
+    // columns whose source coordinate lies within one cell of q, with a column to spare on both sides (the weights
+    // decide); the first and the last cell also take what the clamping sends there
+    const float scale = (float)gw / (float)k.w0;
+    const int lo = q == 0 ? 0 : max((int)(((float)q - 0.5f) * scale - 1.5f), 0);
+    const int hi = q == k.w0 - 1 ? gw : min((int)(((float)q + 1.5f) * scale + 1.5f), gw);
+    const f32x4* p = k.sum + ((size_t)hd * k.cells + cell) * per_cell + a;
     float v = 0.0f;
-    for (int x4 = 0; 4 * x4 < gw; ++x4) {
-      float wx[4];
-      bool any = false;
+#pragma unroll 4
+    for (int x4 = lo / 4; 4 * x4 < hi; ++x4) {
+      const f32x4 s = p[(size_t)x4 * ld];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         int x0, x1;
         float fx;
-        bilinear_coord(min(4 * x4 + j, gw - 1), gw, w0, x0, x1, fx);
-        wx[j] = 4 * x4 + j < gw ? (x0 == q ? 1.0f - fx : 0.0f) + (x1 == q ? fx : 0.0f) : 0.0f;
-        any = any || wx[j] != 0.0f;
+        bilinear_coord(min(4 * x4 + j, gw - 1), gw, k.w0, x0, x1, fx);
+        const float wx = 4 * x4 + j < gw ? (x0 == q ? 1.0f - fx : 0.0f) + (x1 == q ? fx : 0.0f) : 0.0f;
+        if (wx != 0.0f) v = fmaf(wx, s[j], v);
       }
-      if (!any) continue;
-      const f32x4 s = sum[((size_t)hd * cells + cell) * per_cell + (size_t)x4 * ld + a];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) v = fmaf(wx[j], s[j], v);
     }
-    const size_t cellq = (size_t)cell * w0 + q;
-    blk[KIND == 1 ? ((size_t)hd * n + a) * cells * w0 + cellq : ((size_t)hd * cells * w0 + cellq) * n + a] = live * v;
+    const size_t cellq = (size_t)cell * k.w0 + q;
+    k.blk[KIND == 1 ? ((size_t)hd * n + a) * k.cells * k.w0 + cellq : ((size_t)hd * k.cells * k.w0 + cellq) * n + a] = k.live * v;
+  }
+}
+
+struct DwcTotal {
+  const float* part;
+  float *dw, *db;
+  int slices, count;      // count: heads * d
+};
+
+__global__ __launch_bounds__(256) void param_grad_out_kernel(GradKind first, GradKind second, DwcTotal dwc, int batch, int heads,
+                                                             int n, int d, int gh, int gw, int ld) {
+  __shared__ float red[4][4][64];
+  unsigned block = blockIdx.x;
+  if (block < first.blocks + second.blocks) {
+    const bool one = block < first.blocks;
+    const GradKind& k = one ? first : second;
+    if (!one) block -= first.blocks;
+    if (k.kind == 1) bias_grad_block<1>(k, block, batch, heads, n, gh, gw, ld, red);
+    else bias_grad_block<2>(k, block, batch, heads, n, gh, gw, ld, red);
+    return;
+  }
+  // one wave per (head, channel): lane l adds the slices l, l + 64, ... in order, the lanes are added by a fixed tree
+  block -= first.blocks + second.blocks;
+  const int hc = (int)block * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (hc >= dwc.count) return;
+  const int hd = hc / d, c = hc - hd * d;
+  float acc[10];
+#pragma unroll
+  for (int k = 0; k < 10; ++k) acc[k] = 0.0f;
+  for (int s = lane; s < dwc.slices; s += 64) {
+    const float* q = dwc.part + (((size_t)hd * dwc.slices + s) * d + c) * 10;
+#pragma unroll
+    for (int k = 0; k < 10; ++k) acc[k] += q[k];
+  }
+#pragma unroll
+  for (int k = 0; k < 10; ++k) acc[k] = wave_sum(acc[k]);
+  if (lane == 0) {
+#pragma unroll
+    for (int k = 0; k < 9; ++k) dwc.dw[(size_t)hc * 9 + k] = acc[k];
+    if (dwc.db) dwc.db[hc] = acc[9];
   }
 }
 
@@ -276,27 +380,6 @@ __global__ __launch_bounds__(256) void dwc_param_kernel(const typename Piece<E>:
         (red[0][i / (10 * P)][i % (10 * P)] + red[1][i / (10 * P)][i % (10 * P)]) + (red[2][i / (10 * P)][i % (10 * P)] + red[3][i / (10 * P)][i % (10 * P)]);
 }
 
-// one wave per (head, channel): lane l adds the slices l, l + 64, ... in order, the lanes are added by a fixed tree
-__global__ __launch_bounds__(64) void dwc_param_total_kernel(const float* __restrict__ part, float* __restrict__ dw,
-                                                             float* __restrict__ db, int d, int slices) {
-  const int c = blockIdx.x, hd = blockIdx.y, lane = threadIdx.x;
-  float acc[10];
-#pragma unroll
-  for (int k = 0; k < 10; ++k) acc[k] = 0.0f;
-  for (int s = lane; s < slices; s += 64) {
-    const float* q = part + (((size_t)hd * slices + s) * d + c) * 10;
-#pragma unroll
-    for (int k = 0; k < 10; ++k) acc[k] += q[k];
-  }
-#pragma unroll
-  for (int k = 0; k < 10; ++k) acc[k] = wave_sum(acc[k]);
-  if (lane == 0) {
-#pragma unroll
-    for (int k = 0; k < 9; ++k) dw[((size_t)hd * d + c) * 9 + k] = acc[k];
-    if (db) db[(size_t)hd * d + c] = acc[9];
-  }
-}
-
 // 16-byte pieces per token, rounded up to a power of two, and the row segments an image column is cut into: as many as
 // give about 512 blocks, of at least four rows (a segment reads two rows of V it does not own)
 struct DwcPlan {
@@ -320,72 +403,81 @@ DwcPlan dwc_plan(const Problem& p) {
 
 }  // namespace
 
-hipError_t launch_backward_bias_tables(const Problem& p, int kind, int cells, int ld, float* ta, float* tx, float* rows,
-                                       YInfo* yi, hipStream_t st) {
-  const int wp = (p.gw + 15) / 16 * 16;
-  const size_t tcount = (size_t)p.heads * cells * (wp / 4) * (ld / 4), rcount = rows ? (size_t)p.heads * p.gh * (ld / 4) : 0;
-  const unsigned tb = (unsigned)((tcount + 255) / 256), rb = (unsigned)((rcount + 255) / 256), yb = (unsigned)((p.gh + 255) / 256);
-  const dim3 grid(tb + rb + yb);
-  if (kind == 1)
-    bias_tables_kernel<1><<<grid, dim3(256), 0, st>>>(p.b1, ta, tx, rows, yi, p.heads, p.n, p.gh, p.gw, cells, ld, tb, rb);
-  else
-    bias_tables_kernel<2><<<grid, dim3(256), 0, st>>>(p.b2, ta, tx, rows, yi, p.heads, p.n, p.gh, p.gw, cells, ld, tb, rb);
-  return hipGetLastError();
-}
-
-hipError_t launch_backward_bias_grads(const Problem& p, int kind, const BiasGradParts& q, int h0, int w0, float* col,
-                                      float* row, float* blk, hipStream_t st) {
-  const int batch = p.units / p.heads, wp = (p.gw + 15) / 16 * 16;
-  const size_t per_cell = (size_t)(wp / 4) * q.ld;
-  const float* sum = q.gt;      // one unit per head and one segment: the parts are the sums
-  if ((col || blk) && (batch > 1 || q.segs > 1)) {
-    const size_t count = (size_t)p.heads * q.cells * per_cell;
-    bias_grad_sum_kernel<<<dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st>>>(
-        reinterpret_cast<const f32x4*>(q.gt), reinterpret_cast<f32x4*>(q.sum), batch, p.heads, q.segs, q.seg_len, p.gh, q.cells,
-        per_cell);
-    sum = q.sum;
+hipError_t launch_backward_bias_tables(const Problem& p, const BiasTables (&t)[2], const bool (&used)[2], hipStream_t st) {
+  TableKind kinds[2] = {};
+  int ld = 0;
+  for (int i = 0; i < 2; ++i) {
+    if (!used[i]) continue;
+    TableKind& k = kinds[i];
+    k.kind = i == 0 ? 2 : 1, k.b = i == 0 ? p.b2 : p.b1, k.cells = t[i].cells, ld = t[i].ld;
+    k.ta = const_cast<float*>(t[i].ta), k.tx = const_cast<float*>(t[i].tx), k.rows = const_cast<float*>(t[i].rows);
+    k.yi = const_cast<YInfo*>(t[i].yi);
+    const size_t ats = (size_t)p.heads * (ld / 64);
+    k.tblocks = (unsigned)(ats * k.cells * ((p.gw + 15) / 16));
+    k.rblocks = k.rows ? (unsigned)(ats * ((p.gh + 15) / 16)) : 0;
+    k.blocks = k.tblocks + k.rblocks + (unsigned)((p.gh + 255) / 256);
   }
-  const unsigned cb = col ? (unsigned)(((size_t)p.heads * p.gw * p.n + 255) / 256) : 0;
-  const unsigned rb = row ? (unsigned)(((size_t)p.heads * p.gh * p.n + 255) / 256) : 0;
-  const unsigned bb = blk ? (unsigned)(((size_t)p.heads * h0 * w0 * p.n + 255) / 256) : 0;
-  if (cb + rb + bb == 0) return hipGetLastError();
-  const float live = (kind == 1 ? p.N : p.n) > 1 ? 1.0f : 0.0f;
-  if (kind == 1)
-    bias_grad_out_kernel<1><<<dim3(cb + rb + bb), dim3(256), 0, st>>>(reinterpret_cast<const f32x4*>(sum), q.gr, col, row, blk,
-                                                                     batch, p.heads, p.n, p.gh, p.gw, q.cells, w0, q.ld, live, cb,
-                                                                     rb);
-  else
-    bias_grad_out_kernel<2><<<dim3(cb + rb + bb), dim3(256), 0, st>>>(reinterpret_cast<const f32x4*>(sum), q.gr, col, row, blk,
-                                                                     batch, p.heads, p.n, p.gh, p.gw, q.cells, w0, q.ld, live, cb,
-                                                                     rb);
+  const unsigned blocks = kinds[0].blocks + kinds[1].blocks;
+  if (blocks == 0) return hipSuccess;
+  bias_tables_kernel<<<dim3(blocks), dim3(256), 0, st>>>(kinds[0], kinds[1], p.n, p.gh, p.gw, ld);
   return hipGetLastError();
 }
 
 size_t dwc_param_part_floats(const Problem& p) { return (size_t)p.heads * dwc_plan(p).slices * p.d * 10; }
 
-hipError_t launch_dwc_param_grads(const Problem& p, const void* V, const void* dO, float* part, float* dw, float* db,
-                                  hipStream_t st) {
-  const DwcPlan q = dwc_plan(p);
-  const dim3 grid(q.slices, p.heads);
-  auto go = [&](auto kernel, auto elem) {
-    using S = typename Piece<decltype(elem)>::S;
-    kernel<<<grid, dim3(256), 0, st>>>((const S*)V, (const S*)dO, part, p.heads, p.d, p.lay, p.gh, p.gw, q.segs, q.seg_len,
-                                       q.items);
-  };
-  auto by_pieces = [&](auto elem) {
-    using E = decltype(elem);
-    switch (q.chp) {
-      case 2: go(dwc_param_kernel<E, 2>, elem); break;
-      case 4: go(dwc_param_kernel<E, 4>, elem); break;
-      case 8: go(dwc_param_kernel<E, 8>, elem); break;
-      case 16: go(dwc_param_kernel<E, 16>, elem); break;
-      default: go(dwc_param_kernel<E, 32>, elem); break;      // fp32 only
+hipError_t launch_backward_param_grads(const Problem& p, const BiasGradParts (&parts)[2], const BackwardParamGrads& pg,
+                                       const void* V, const void* dO, float* dwc_part, hipStream_t st) {
+  const int batch = p.units / p.heads, wp = (p.gw + 15) / 16 * 16;
+  GradKind kinds[2] = {};
+  int ld = 64;
+  for (int i = 0; i < 2; ++i) {
+    const BiasGradParts& q = parts[i];
+    GradKind& k = kinds[i];
+    k.kind = i == 0 ? 2 : 1;
+    if (!q.gt) continue;
+    ld = q.ld;
+    k.col = i == 0 ? pg.db2_col : pg.db1_col, k.row = i == 0 ? pg.db2_row : pg.db1_row, k.blk = i == 0 ? pg.db2_blk : pg.db1_blk;
+    k.gt = k.sum = reinterpret_cast<const f32x4*>(q.gt), k.gr = q.gr;
+    k.segs = q.segs, k.seg_len = q.seg_len, k.cells = q.cells, k.w0 = pg.w0;
+    k.live = (k.kind == 1 ? p.N : p.n) > 1 ? 1.0f : 0.0f;
+    if ((k.col || k.blk) && (batch > 1 || q.segs > 1)) {
+      k.sum = k.total = reinterpret_cast<f32x4*>(q.sum);
+      k.sblocks = (unsigned)(((size_t)p.heads * q.cells * (wp / 4) * ld + 255) / 256);
     }
-  };
-  if (p.dtype == 2) by_pieces(ElemBF16{});
-  else if (p.dtype == 1) by_pieces(ElemF16{});
-  else by_pieces(ElemF32{});
-  dwc_param_total_kernel<<<dim3(p.d, p.heads), dim3(64), 0, st>>>(part, dw, db, p.d, q.slices);
+    k.cblocks = k.col ? (unsigned)(((size_t)p.heads * ((p.gw + 3) / 4) * p.n + 255) / 256) : 0;
+    k.rblocks = k.row ? (unsigned)((size_t)p.heads * ((p.gh + 3) / 4) * ((p.n + 63) / 64)) : 0;
+    k.blocks = k.cblocks + k.rblocks + (k.blk ? (unsigned)(((size_t)p.heads * pg.h0 * pg.w0 * p.n + 255) / 256) : 0);
+  }
+  if (kinds[0].sblocks + kinds[1].sblocks != 0)
+    bias_grad_sum_kernel<<<dim3(kinds[0].sblocks + kinds[1].sblocks), dim3(256), 0, st>>>(kinds[0], kinds[1], batch, p.heads, p.gh,
+                                                                                       (size_t)(wp / 4) * ld);
+  DwcTotal total{};
+  if (p.dwc_w && pg.ddwc_w) {
+    const DwcPlan q = dwc_plan(p);
+    const dim3 grid(q.slices, p.heads);
+    auto go = [&](auto kernel, auto elem) {
+      using S = typename Piece<decltype(elem)>::S;
+      kernel<<<grid, dim3(256), 0, st>>>((const S*)V, (const S*)dO, dwc_part, p.heads, p.d, p.lay, p.gh, p.gw, q.segs, q.seg_len,
+                                         q.items);
+    };
+    auto by_pieces = [&](auto elem) {
+      using E = decltype(elem);
+      switch (q.chp) {
+        case 2: go(dwc_param_kernel<E, 2>, elem); break;
+        case 4: go(dwc_param_kernel<E, 4>, elem); break;
+        case 8: go(dwc_param_kernel<E, 8>, elem); break;
+        case 16: go(dwc_param_kernel<E, 16>, elem); break;
+        default: go(dwc_param_kernel<E, 32>, elem); break;      // fp32 only
+      }
+    };
+    if (p.dtype == 2) by_pieces(ElemBF16{});
+    else if (p.dtype == 1) by_pieces(ElemF16{});
+    else by_pieces(ElemF32{});
+    total = DwcTotal{dwc_part, pg.ddwc_w, pg.ddwc_b, q.slices, p.heads * p.d};
+  }
+  const unsigned blocks = kinds[0].blocks + kinds[1].blocks + (unsigned)((total.count + 3) / 4);
+  if (blocks == 0) return hipGetLastError();
+  param_grad_out_kernel<<<dim3(blocks), dim3(256), 0, st>>>(kinds[0], kinds[1], total, batch, p.heads, p.n, p.d, p.gh, p.gw, ld);
   return hipGetLastError();
 }
 
