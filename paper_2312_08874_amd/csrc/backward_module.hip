@@ -440,7 +440,8 @@ hipError_t launch_backward_param_grads(const Problem& p, const BiasGradParts (&p
     k.gt = k.sum = reinterpret_cast<const f32x4*>(q.gt), k.gr = q.gr;
     k.segs = q.segs, k.seg_len = q.seg_len, k.cells = q.cells, k.w0 = pg.w0;
     k.live = (k.kind == 1 ? p.N : p.n) > 1 ? 1.0f : 0.0f;
-    if ((k.col || k.blk) && (batch > 1 || q.segs > 1)) {
+    // a single part is the sum itself, where the image rows touch every cell row (at least as many rows as cells)
+    if ((k.col || k.blk) && (batch > 1 || q.segs > 1 || q.cells > p.gh)) {
       k.sum = k.total = reinterpret_cast<f32x4*>(q.sum);
       k.sblocks = (unsigned)(((size_t)p.heads * q.cells * (wp / 4) * ld + 255) / 256);
     }

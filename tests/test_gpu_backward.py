@@ -176,6 +176,18 @@ def test_backward_agent_bias_off_the_tile_sizes(aa, oracle, grid, agrid, d, dtyp
     _run_case(aa, oracle, _wl("bias_tiles", dtype, grid, agrid, d, batch=batch, index=81), module=True, blk=blk)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_backward_block_grid_finer_than_the_image(aa, oracle, dtype):
+    """Cell rows that no image row touches have gradients of exactly zero, whatever the workspace held (one image and
+    one segment: the parts the kernels leave would serve as the sums)."""
+    import torch
+    ws = torch.full((32 << 20,), 0x41, dtype=torch.uint8, device="cuda")
+    got = _run_case(aa, oracle, _wl("fine_blocks", dtype, (2, 9), (2, 3), 16, batch=1, index=21), module=True, blk=(7, 12),
+                    kw={"workspace": ws})
+    for g in (got["db1_blk"], got["db2_blk"].permute(0, 3, 1, 2)):
+        assert bool((g[:, :, [0, 3, 6]] == 0).all())      # the image rows read cells 1, 2 and 4, 5
+
+
 @pytest.mark.parametrize("keys", [("b1_col",), ("b1_row", "b2_blk"), ("b2_row", "dwc_w"), ("dwc_w",)])
 def test_backward_single_module_terms(aa, oracle, keys):
     """One stage with a bias and the other without, single components, the convolution alone: the gradients against
