@@ -804,6 +804,28 @@ static aa_status forward_core(Problem pr, const Plan& pl, const aa_params* param
   return run_broadcast(pr, Q, agents, agents_lo, VA, V, out, pl, stream);
 }
 
+// The same on window-major copies: the tensors of the windows are dense and lie where the plan keeps them.
+static aa_status forward_staged(const Problem& pr, const Plan& pl, const aa_params* params, const void* A, void* workspace,
+                                hipStream_t stream) {
+  char* stage = (char*)workspace + pl.off_stage;
+  const size_t sb = pl.stage_bytes;
+  Problem inner = pr;
+  inner.lay = aa::Layout{};
+  inner.lay.sn = inner.lay.on = pr.d;
+  inner.lay.sh = inner.lay.oh = (long long)pr.N * pr.d;
+  inner.lay.sb = inner.lay.ob = (long long)pr.N * pr.d * pr.heads;
+  return forward_core(inner, pl, params, stage, stage + sb, stage + 2 * sb, A, workspace, stage + 3 * sb, stream);
+}
+
+// Windows (Sec. 5.5).  The fp32 / fallback kernels and the one-block-per-unit kernel address them in place; the other
+// 16-bit families run on window-major copies.
+static bool windows_staged(const Problem& pr, const Plan& pl, std::initializer_list<const void*> ptrs) {
+  if (pr.lay.line == 0 || pl.off_stage == kNoStage) return false;
+  const bool mfma = use_small(pr, ptrs) || use_large(pr, ptrs);
+  const bool fused = pl.prefer_fused && aa::small_fused_supported(pr) && use_small(pr, ptrs);
+  return mfma && !fused;
+}
+
 // agent_attn_fwd; small: plan without the streaming fp32 kernels' workspace
 static aa_status forward_checked(const aa_desc* desc, const void* Q, const void* K, const void* V, const void* A,
                                  const aa_params* params, void* workspace, size_t workspace_bytes, void* out,
@@ -829,28 +851,16 @@ static aa_status forward_checked(const aa_desc* desc, const void* Q, const void*
 
   Problem pr = make_problem(desc, params);
   hipStream_t stream = (hipStream_t)hip_stream;
-  if (pr.lay.line != 0) {
-    // Windows (Sec. 5.5).  The fp32 / fallback kernels and the one-block-per-unit kernel address them in place;
-    // the other 16-bit families run on window-major copies made here and their result is scattered back.
-    const bool mfma = use_small(pr, {Q, K, V, A, out}) || use_large(pr, {Q, K, V, A, out});
-    const bool fused = pl.prefer_fused && aa::small_fused_supported(pr) && use_small(pr, {Q, K, V, A, out});
-    if (mfma && !fused) {
-      if (pl.off_stage == kNoStage) return AA_ERR_UNSUPPORTED;      // cannot happen: the plan saw the same shape
-      char* stage = (char*)workspace + pl.off_stage;
-      const size_t sb = pl.stage_bytes;
-      AA_HIP(aa::launch_restride(pr, true, false, Q, stage, stream));
-      AA_HIP(aa::launch_restride(pr, true, false, K, stage + sb, stream));
-      AA_HIP(aa::launch_restride(pr, true, false, V, stage + 2 * sb, stream));
-      Problem inner = pr;
-      inner.lay = aa::Layout{};
-      inner.lay.sn = inner.lay.on = pr.d;
-      inner.lay.sh = inner.lay.oh = (long long)pr.N * pr.d;
-      inner.lay.sb = inner.lay.ob = (long long)pr.N * pr.d * pr.heads;
-      st = forward_core(inner, pl, params, stage, stage + sb, stage + 2 * sb, A, workspace, stage + 3 * sb, stream);
-      if (st != AA_OK) return st;
-      AA_HIP(aa::launch_restride(pr, false, true, stage + 3 * sb, out, stream));
-      return AA_OK;
-    }
+  if (windows_staged(pr, pl, {Q, K, V, A, out})) {      // copied here, the result is scattered back
+    char* stage = (char*)workspace + pl.off_stage;
+    const size_t sb = pl.stage_bytes;
+    AA_HIP(aa::launch_restride(pr, true, false, Q, stage, stream));
+    AA_HIP(aa::launch_restride(pr, true, false, K, stage + sb, stream));
+    AA_HIP(aa::launch_restride(pr, true, false, V, stage + 2 * sb, stream));
+    st = forward_staged(pr, pl, params, A, workspace, stream);
+    if (st != AA_OK) return st;
+    AA_HIP(aa::launch_restride(pr, false, true, stage + 3 * sb, out, stream));
+    return AA_OK;
   }
   return forward_core(pr, pl, params, Q, K, V, A, workspace, out, stream);
 }
@@ -1171,6 +1181,28 @@ aa_status agent_attn_module_fwd(const aa_desc* desc, const void* x, const aa_pro
   char* qkv = ws + mp.off_qkv;
   char* o = ws + mp.off_o;
   const int C = mp.C;
+  // 16-bit rows of whole 16-byte pieces: own kernel, with the bias; the attention's windows where they are staged.  (32
+  // bits: the library's product, its fp32 rate being that of the matrix cores.)
+  if (desc->dtype != AA_F32 && C % 8 == 0 && rows <= ((size_t)1 << 30) && aligned16(x) && aligned16(y) && aligned16(proj->w_qkv) &&
+      aligned16(proj->b_qkv) && aligned16(proj->w_out) && aligned16(proj->b_out)) {
+    const Problem pr = make_problem(&inner, params);
+    const Plan pl = make_plan(&inner, params);
+    const char *k = qkv + (size_t)C * es, *v = qkv + (size_t)2 * C * es;
+    char* inner_ws = ws + mp.off_inner;
+    aa::ProjRows dense{}, win{};
+    dense.ld = C;
+    const bool staged = desc->d % 8 == 0 && windows_staged(pr, pl, {qkv, k, v, o}) &&
+                        win.windows(pr.lay, desc->heads, desc->d, mp.tokens, (long long)rows, pl.stage_bytes / es);
+    if (staged) qkv = inner_ws + pl.off_stage, o = qkv + 3 * pl.stage_bytes;
+    aa::ProjRows packed = staged ? win : dense;
+    if (!staged) packed.ld = 3 * C;
+    AA_HIP(aa::launch_projection(desc->dtype, (int)rows, 3 * C, C, x, dense, proj->w_qkv, proj->b_qkv, qkv, packed, stream));
+    st = staged ? forward_staged(pr, pl, params, nullptr, inner_ws, stream)
+                : agent_attn_fwd(&inner, qkv, k, v, nullptr, params, inner_ws, align_up(mp.inner_bytes), o, hip_stream);
+    if (st != AA_OK) return st;
+    AA_HIP(aa::launch_projection(desc->dtype, (int)rows, C, C, o, staged ? win : dense, proj->w_out, proj->b_out, y, dense, stream));
+    return AA_OK;
+  }
   st = linear_rows(desc->dtype, (int)rows, 3 * C, C, x, C, proj->w_qkv, qkv, 3 * C, stream);
   if (st != AA_OK) return st;
   if (proj->b_qkv) AA_HIP(aa::launch_add_row_bias(desc->dtype, qkv, proj->b_qkv, rows, 3 * C, stream));

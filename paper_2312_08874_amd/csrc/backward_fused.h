@@ -34,7 +34,6 @@ struct UnitPlace {
   uint32_t inv_heads, inv_nwin, inv_wxn, inv_ww;         // ceil(2^32 / divisor), 0 for a divisor of 1 (inv_ww: no windows)
   int nwin, wxn, ww, win_rows;                           // win_rows: image rows of a window times line
 
-  static uint32_t inverse(int v) { return v > 1 ? (uint32_t)((((uint64_t)1 << 32) + v - 1) / v) : 0u; }
   static unsigned long long rows(const Layout& l, int N) { return l.line ? (unsigned long long)l.wh * l.line : (unsigned long long)N; }
   // strides below 2^32 elements, a unit's extent below 2^32 bytes; windows only where N * ww < 2^32
   static bool fits(const Layout& l, int N) {
@@ -47,13 +46,9 @@ struct UnitPlace {
     p.sb = (uint32_t)l.sb, p.sh = (uint32_t)l.sh, p.ob = (uint32_t)l.ob, p.oh = (uint32_t)l.oh;
     p.sn = l.sn, p.on = l.on, p.heads = heads, p.line = l.line;
     p.nwin = l.nwin, p.wxn = l.wxn, p.ww = l.line ? l.ww : 0, p.win_rows = l.wh * l.line;
-    p.inv_heads = inverse(heads), p.inv_nwin = inverse(l.nwin), p.inv_wxn = inverse(l.wxn);
-    p.inv_ww = l.line ? inverse(l.ww) : 0u;
+    p.inv_heads = quotient_inverse(heads), p.inv_nwin = quotient_inverse(l.nwin), p.inv_wxn = quotient_inverse(l.wxn);
+    p.inv_ww = l.line ? quotient_inverse(l.ww) : 0u;
     return p;
-  }
-  // n / divisor for n * divisor < 2^32 (the product n * inv is then off by less than one part in 2^32 of a whole)
-  static __device__ __forceinline__ int quotient(int n, uint32_t inv) {
-    return inv == 0u ? n : (int)__umulhi((uint32_t)n, inv);
   }
   __device__ __forceinline__ int entry(int u) const { return quotient(u, inv_heads); }
   __device__ __forceinline__ size_t base(int u, bool out) const {

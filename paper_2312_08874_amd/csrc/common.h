@@ -60,6 +60,15 @@ struct Layout {
   __host__ __device__ int pitch(int gw) const { return line == 0 ? gw : line; }
 };
 
+// n / divisor as a multiplication, for n * divisor < 2^32 (the product n * inverse is then off by less than one part in
+// 2^32 of a whole)
+static inline uint32_t quotient_inverse(int divisor) {      // ceil(2^32 / divisor), 0 for a divisor of 1
+  return divisor > 1 ? (uint32_t)((((uint64_t)1 << 32) + divisor - 1) / divisor) : 0u;
+}
+static __device__ __forceinline__ int quotient(int n, uint32_t inverse) {
+  return inverse == 0u ? n : (int)__umulhi((uint32_t)n, inverse);
+}
+
 constexpr int kComputeUnits = 256;      // MI355X
 
 // ---------------------------------------------------------------------------

@@ -53,6 +53,23 @@ hipError_t launch_resize_agent_axis(const float* src, float* dst, size_t outer, 
 bool fused_f32_supported(const Problem& p);
 hipError_t launch_fused_f32(const Problem& p, const void* Q, const void* K, const void* V, const void* A, void* out,
                             hipStream_t st);
+// --- projection.hip ---
+// Rows of a projection's input or output.  ww == 0: row-major, `ld` elements a row.  Otherwise the rows are the pixels of
+// images of `line` columns (`tokens` of them each) cut into wyn x wxn windows of wh x ww, and the row's channels lie in the
+// attention's window-major tensors [image * windows][heads][wh * ww][d], head_elems = wh * ww * d, the three of q | k | v
+// part_elems apart.
+struct ProjRows {
+  int ld;
+  int ww, wh, line, wyn, wxn, tokens, heads, d;
+  size_t head_elems, part_elems;
+  uint32_t inv_tokens, inv_line, inv_wh, inv_ww, inv_width, inv_d;      // quotient(): 24 divisions a lane took 6 of 31 us
+  // the windows of l; false where an index would be too large
+  bool windows(const Layout& l, int heads, int d, long long image_tokens, long long rows, size_t part);
+};
+// Y [M][O] = X [M][K] W^T + b (W [O][K], b [O] or null), 16-bit elements, fp32 sums; O, K and with windows d multiples of
+// 8, pointers and rows 16-byte aligned
+hipError_t launch_projection(int dtype, int M, int O, int K, const void* X, const ProjRows& x, const void* W, const void* b,
+                             void* Y, const ProjRows& y, hipStream_t st);
 // Y[r][c] += bias[c] for a row-major [rows][cols] matrix of `dtype` (the bias of a linear projection), rounded once
 hipError_t launch_add_row_bias(int dtype, void* Y, const void* bias, size_t rows, int cols, hipStream_t st);
 hipError_t launch_restride(const Problem& p, bool to_dense, bool out_layout, const void* src, void* dst, hipStream_t st);

@@ -721,6 +721,44 @@ def test_module_with_projections(aa, oracle, name, batch, heads, d, grid, window
     assert np.abs(ref - ref2).max() > 1e-3
 
 
+# rows and widths on and off the blocks of the projection kernel (128 or 64 rows; 128, 96 or 64 outputs; steps of 64
+# channels), windows that are staged for the few-agents and for the many-agents kernels, and the library's product
+PROJECTION_CASES = [
+    ("width 8", 1, 1, 8, (9, 7), None, (2, 2), "f16", True),
+    ("width 80, many agents, windows", 2, 2, 40, (40, 16), (20, 16), (9, 9), "bf16", True),
+    ("width 96, few agents, windows", 2, 3, 32, (28, 56), (28, 28), (7, 7), "f16", True),
+    ("blocks of 128 rows, 96 and 64 outputs", 8, 2, 16, (97, 95), None, (3, 3), "bf16", True),
+    ("blocks of 128 rows, 128 outputs", 8, 4, 32, (97, 95), None, (3, 3), "f16", True),
+    ("unaligned rows", 1, 3, 12, (11, 9), None, (3, 3), "bf16", True),
+    ("unaligned weights", 1, 2, 32, (14, 14), None, (7, 7), "bf16", False),
+]
+
+
+@pytest.mark.parametrize("name,batch,heads,d,grid,window,agrid,dtype,aligned", PROJECTION_CASES,
+                         ids=[c[0] for c in PROJECTION_CASES])
+def test_projection_kernel_edges(aa, oracle, name, batch, heads, d, grid, window, agrid, dtype, aligned):
+    import torch
+    C, T = heads * d, grid[0] * grid[1]
+    mk = lambda shape, stream, std: inputs.make_tensor(shape, stream=930 + stream, std=std, dtype=dtype)
+    x = mk((batch, T, C), 0, 1.0)
+    w_qkv, b_qkv = mk((3 * C, C), 1, C ** -0.5), mk((3 * C,), 2, 0.5)
+    w_out, b_out = mk((C, C), 3, C ** -0.5), mk((C,), 4, 0.5)
+
+    def dev(a):
+        t = util.to_device(a, dtype)
+        if aligned:
+            return t
+        room = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)      # one element past the alignment
+        room[1:] = t.reshape(-1)
+        return room[1:].reshape(t.shape)
+    y = aa.agent_attn_module_fwd(dev(x), dev(w_qkv), dev(b_qkv), dev(w_out), dev(b_out), heads=heads, grid=grid,
+                                 agent_grid=agrid, window=window)
+    ref = util.oracle_module_forward(oracle, x, w_qkv, b_qkv, w_out, b_out, dtype, heads=heads, grid=grid,
+                                     agent_grid=agrid, window=window, params=None)
+    util.assert_parity(util.to_host64(y).reshape(ref.shape), ref, dtype, "module " + name,
+                       max_abs=util.TOL[dtype]["max_abs"] * max(1.0, float(np.abs(ref).max())))
+
+
 def test_binding_rejects_mismatched_tensors(aa):
     """The Python layer refuses tensors whose dtype, device, shape or density differ from what the descriptor
     will say (the C ABI sees only pointers), before anything is launched."""
