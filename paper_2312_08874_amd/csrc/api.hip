@@ -258,6 +258,19 @@ int padded_width(int d);
 
 constexpr size_t kNoStage = ~(size_t)0;
 
+// fp32 with an agent bias: the streaming kernels' launches (bias tables and the chain from agents to tokens, 26 us and
+// more) do not pay for few tokens, where the kernels that evaluate the bias per score end sooner: 4 units of 63 tokens x 49
+// agents, d = 64: 22 against 40 us, 24 x 196 x 9, d = 64: 35 against 39, 1 x 840 x 195, d = 40: 43 against 51.  Past these
+// lines the streaming kernels win: 24 x 196 x 49, d = 64: 42 against 45, 4 x 840 x 49, d = 40: 37.0 against 37.4, 192 x
+// 63 x 9, d = 16: 28 against 32.  Above d = 64 the other kernels take two channels a lane: 4 x 196 x 49, d = 128: 45
+// against 51, but 1 x 840 x 49: 57 against 53.  Without a bias the streaming kernels were never slower.
+bool few_biased_tokens(const Problem& p) {
+  if (!p.b1.any() && !p.b2.any()) return false;
+  const long long tokens = (long long)p.units * p.N;
+  if (tokens > 6144 || tokens * p.n * p.d > 12000000) return false;
+  return p.d <= 64 ? tokens <= 1024 || p.N <= 256 : p.N <= 256 && tokens <= 2048;
+}
+
 // small: without the fp32 kernels' bias tables and partial sums (callers with a workspace of fixed size)
 Plan make_plan(const aa_desc* d, const aa_params* params = nullptr, bool small = false) {
   Plan pl{};
@@ -308,7 +321,7 @@ Plan make_plan(const aa_desc* d, const aa_params* params = nullptr, bool small =
   if (!(params && params->bias_tables)) off += pl.bias.total;      // prepared tables need no room here
   pl.off_f32 = kNoStage;
   const Problem full = make_problem(d, params);
-  if (!small && d->n_splits <= 0 && aa::forward_f32_supported(full)) {      // an explicit split count: the kernels that take one
+  if (!small && d->n_splits <= 0 && aa::forward_f32_supported(full) && !few_biased_tokens(full)) {      // an explicit split count: the kernels that take one
     pl.off_f32 = off;
     off += align_up(aa::forward_f32_workspace_floats(full) * sizeof(float));
   }
@@ -1066,7 +1079,8 @@ aa_status agent_attn_fwd_timed(const aa_desc* desc, const void* Q, const void* K
 }
 
 // ---------------------------------------------------------------------------
-// Module with projections: two plain GEMMs through rocBLAS (loaded on first use) around agent_attn_fwd.
+// Module with projections around agent_attn_fwd: 16-bit rows of whole 16-byte pieces on the kernel of projection.hip, the
+// rest through rocBLAS (loaded on first use).
 // ---------------------------------------------------------------------------
 extern "C++" {
 namespace {

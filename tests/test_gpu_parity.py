@@ -296,6 +296,31 @@ def test_forward_f32_streaming_kernels(aa, oracle, grid, agrid, d, module):
     util.assert_parity(util.to_host64(O).reshape(ref.shape), ref, "f32", "fp32 streaming")
 
 
+# both sides of the lines between the kernels that evaluate an fp32 bias per score and the streaming ones: tokens of all
+# units and of one, their product with agents and width, widths past 64
+@pytest.mark.parametrize("batch,heads,grid,agrid,d,few", [
+    (4, 6, (16, 16), (3, 3), 64, True), (5, 5, (16, 16), (3, 3), 64, False), (2, 2, (1, 256), (1, 3), 8, True),
+    (1, 1, (32, 32), (9, 13), 40, True), (1, 1, (25, 41), (9, 13), 40, False), (2, 2, (1, 257), (1, 3), 8, False),
+    (2, 4, (16, 16), (5, 3), 68, True), (1, 9, (16, 16), (5, 3), 68, False), (1, 1, (257, 1), (7, 1), 96, False),
+    (16, 2, (9, 16), (5, 13), 96, False), (1, 16, (15, 17), (7, 7), 60, True), (1, 16, (15, 17), (7, 7), 64, False)])
+def test_forward_f32_bias_routes(aa, oracle, batch, heads, grid, agrid, d, few):
+    import dataclasses
+    wl = dataclasses.replace(WL["tiny"], batch=batch, heads=heads, grid=grid, agent_grid=agrid, d=d, index=16)
+    t = inputs.make_qkv(wl)
+    dv = dev_qkv(wl, t)
+    params = inputs.make_module_params(wl.heads, wl.n, d, grid, blk=(2, 3), index=16)
+    pd = util.params_to_device(params)
+    splits = max(1, min(-(-4096 // (wl.units * wl.n)), -(-wl.N // 128)))      # an explicit count keeps the kernels that take one
+    room = [aa.workspace_bytes(aa.make_desc(batch, heads, wl.N, wl.n, d, 0, grid, agrid, n_splits=k), aa.make_params(pd))
+            for k in (0, splits)]
+    assert (room[0] == room[1]) == few
+    O = aa.agent_attn_fwd(dv["Q"], dv["K"], dv["V"], grid=grid, agent_grid=agrid, params=pd)
+    units = sorted({0, wl.units // 2, wl.units - 1})
+    ref = util.oracle_forward_units(oracle, wl, t, units, params=params)
+    got = util.to_host64(O).reshape(wl.units, wl.N, d)[units]
+    util.assert_parity(got, ref.reshape(got.shape), "f32", "fp32 bias routes")
+
+
 _PREPARED_EXTRA = {"large_dense_many": dict(grid=(15, 15), agent_grid=(10, 13), d=64, dtype="bf16", heads=2),
                    "large_dense_few": dict(grid=(12, 10), agent_grid=(3, 5), d=40, dtype="f16", heads=2)}
 
