@@ -556,7 +556,7 @@ def main():
             "module_prepared_bias_cold_us": step_time(wl, binding, args.ring_bytes, k, w, True, True) * 1e3,
         }
         line["variants"]["tiny_single_call_latency_us"] = single_call_latency_us(inputs.WORKLOADS["tiny"], binding)
-        try:      # two library GEMMs around the operator; not part of the headline figure
+        try:      # the projections around the operator; not part of the headline figure
             line["variants"]["with_projections_hot_us"] = module_with_projections_us(wl, binding)
         except Exception as e:      # the BLAS library is an optional dependency of that entry point alone
             line["variants"]["with_projections_hot_us"] = None

@@ -184,14 +184,15 @@ aa_status agent_attn_resize_bias(int32_t heads, int32_t grid_h, int32_t grid_w, 
  *                                     written token-major [batch, T, heads, d] = [batch, T, C]
  *   y = o Wout^T + bout               Wout [C, C];  y [batch, T, C]
  * q, k, v and o are stored in desc->dtype (one rounding each from the fp32 accumulator), as the activations of a
- * model in that type are.  The two products are plain GEMMs and go to the platform's BLAS library (rocBLAS, fp32
- * accumulation), loaded on first use; everything else is this library's kernels.  All pointers device memory; weights
+ * model in that type are.  16-bit projections of 16-byte aligned tensors (C a multiple of 8) run on this library's
+ * kernel, the bias added before that rounding; the others are plain GEMMs of the platform's BLAS library (rocBLAS, fp32
+ * accumulation), loaded on first use.  All pointers device memory; weights
  * and biases in desc->dtype, row-major; bqkv / bout may be NULL.
  * desc: batch, heads, N, n, d, grids (both needed: the agents are pooled), dtype, scales, v_residual_k, n_splits and
  * image_h / image_w as for agent_attn_fwd; the stride fields must be 0 (the module fixes the layouts).
  * workspace: agent_attn_module_workspace_bytes(), 256-byte aligned (holds q|k|v, o and the attention's workspace).
- * Errors: as agent_attn_fwd; AA_ERR_SHAPE for non-zero strides; AA_ERR_UNSUPPORTED when the BLAS library cannot be
- * loaded; AA_ERR_HIP when one of its calls fails. */
+ * Errors: as agent_attn_fwd; AA_ERR_SHAPE for non-zero strides; AA_ERR_UNSUPPORTED when the BLAS library is
+ * needed and cannot be loaded; AA_ERR_HIP when one of its calls fails. */
 typedef struct {
   const void *w_qkv, *b_qkv; /* [3C, C], [3C] or NULL */
   const void *w_out, *b_out; /* [C, C], [C] or NULL */
@@ -220,15 +221,15 @@ aa_status agent_broadcast_fwd(const aa_desc *desc, const void *Q, const void *A,
 /* ------------------------------------------------------------------------
  * Backward pass (the paper trains its models end to end, Sec. 5; the gradients
  * follow from Eq. (3), (5), (6) and Appendix B / C.1 by the chain rule).
- * Two implementations.  fp16 / bf16 problems with d a multiple of 8 up to 128 run
- * kernels that recompute every score tile where it is used and keep no attention
- * matrix in memory, module terms included; strided tensors and windows are read
- * where they lie.  Without agent bias and DWC the workspace is then a few n*d and
- * N-long arrays per unit and the partial sums of the split token ranges.  Every
- * other problem (fp32, other widths, module terms on unaligned tensors) runs
- * reference-quality kernels that materialise both attention matrices in the
- * workspace: about 4*n*N + 7*N*d + 4*n*d floats per unit, which is also what the
- * query returns for 16-bit problems with module terms.
+ * Two implementations.  Problems with rows of whole 16-byte pieces (d a multiple of 8,
+ * fp32 of 4) up to d = 128 run kernels that recompute every score tile where it is
+ * used and keep no attention matrix in memory, module terms included; strided tensors
+ * and windows are read where they lie.  For 16-bit problems without agent bias and DWC
+ * the workspace is then a few n*d and N-long arrays per unit and the partial sums of
+ * the split token ranges.  Every other problem (other widths, fp32 or module terms on
+ * unaligned tensors) runs reference-quality kernels that materialise both attention
+ * matrices in the workspace: about 4*n*N + 7*N*d + 4*n*d floats per unit, which the
+ * query also covers for fp32 problems and for 16-bit problems with module terms.
  * ---------------------------------------------------------------------- */
 
 /* Gradients of the module parameters (host struct of device pointers, fp32,
