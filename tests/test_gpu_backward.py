@@ -250,6 +250,37 @@ def test_backward_peaky_softmaxes(aa, oracle, scale_qk, given, dtype):
               scale_qk=scale_qk)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("n,d,units,dwc", [(49, 64, 2, False), (63, 32, 1, True), (17, 128, 1, False), (64, 48, 1, False),
+                                           (131, 16, 520, False)])
+def test_backward_scores_far_below_zero(aa, oracle, n, d, units, dwc, dtype):
+    """A token whose scores all lie near -128: exp(-log-sum-exp) overflows, which the rows that fill the last tile of
+    agents must not see (agent counts off the tile of 32; the last case has units enough for the kernel with four token
+    columns per wave).  Channel 0 holds the common part of agents and token: there dQ is the sum of the token's score
+    gradients, zero but for their roundings, times 16, and dA takes 8 times the error of one token's score gradients
+    where other channels take an average over tokens, so these two are asked to be finite only; the bars elsewhere as
+    usual."""
+    wl = _wl("far_below", dtype, (5, 8), (1, n), d, batch=1, heads=units, index=61)
+    t = inputs.make_qkv(wl)
+    t["dO"] = inputs.make_tensor((units, wl.N, d), stream=wl.index * 16 + 12, dtype=dtype)
+    t["A"] = inputs.make_tensor((units, n, d), stream=wl.index * 16 + 11, dtype=dtype)
+    f64 = {k: inputs.to_float64(v, dtype).copy() for k, v in t.items()}
+    f64["A"][:, :, 0] = 16.0
+    f64["Q"][:, :, 0] = 0.0
+    f64["Q"][:, 3, 0] = -8.0 * d ** 0.5
+    dv = [util.to_device(inputs.to_storage(f64[k], dtype), dtype, (1, units) + f64[k].shape[1:]) for k in ("Q", "K", "V", "dO", "A")]
+    f64 = {k: util.to_host64(x).reshape(f64[k].shape) for k, x in zip(("Q", "K", "V", "dO", "A"), dv)}      # as rounded
+    w = np.zeros((units, d, 3, 3), np.float32)
+    kw = dict(grid=wl.grid, params={"dwc_w": util.params_to_device({"w": w})["w"]}) if dwc else {}
+    got = aa.agent_attn_bwd(*dv, **kw)
+    ref = oracle.agent_attn_bwd(f64["Q"], f64["K"], f64["V"], f64["dO"], A=f64["A"], heads=units, grid=wl.grid)
+    for k in ("dQ", "dK", "dV", "dA"):
+        x = util.to_host64(got[k]).reshape(ref[k].shape)
+        assert np.isfinite(x).all(), k
+        first = 1 if k in ("dQ", "dA") else 0
+        _check(got[k][..., first:], ref[k][..., first:], dtype, k)
+
+
 @pytest.mark.parametrize("grid,agrid,d", [((12, 12), (4, 4), 32), ((40, 40), (12, 12), 64)])
 def test_backward_is_deterministic_and_ignores_workspace(aa, grid, agrid, d):
     import torch
