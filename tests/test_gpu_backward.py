@@ -72,7 +72,8 @@ def _check_param(got, ref, dtype, what, floor=0.0):
     assert rel <= {"f32": 1e-4, "f16": 5e-3, "bf16": 1e-2}[dtype], "%s: rel_l2 %.3e" % (what, rel)
 
 
-def _run_case(aa, oracle, wl, *, given=False, module=False, blk=(3, 2), kw=None, scale_qk=1.0):
+def _run_case(aa, oracle, wl, *, given=False, module=False, blk=(3, 2), kw=None, scale_qk=1.0, mask=None):
+    """mask: (parameter, index, value, value for the reference)"""
     kw = kw or {}
     t = inputs.make_qkv(wl, scale_qk=scale_qk)
     dO = inputs.make_tensor((wl.units, wl.N, wl.d), stream=wl.index * 16 + 12, dtype=wl.dtype)
@@ -80,7 +81,11 @@ def _run_case(aa, oracle, wl, *, given=False, module=False, blk=(3, 2), kw=None,
     dv = {k: util.to_device(v, wl.dtype, shape) for k, v in t.items()}
     dOd = util.to_device(dO, wl.dtype, shape)
     params = inputs.make_module_params(wl.heads, wl.n, wl.d, wl.grid, blk=blk, index=wl.index) if module else None
+    if mask:
+        params[mask[0]][mask[1]] = mask[2]
     pd = util.params_to_device(params) if module else None
+    if mask:
+        params[mask[0]][mask[1]] = mask[3]
     A_st = None
     if given:
         A_st = inputs.make_tensor((wl.units, wl.n, wl.d), stream=wl.index * 16 + 11, dtype=wl.dtype)
@@ -123,6 +128,10 @@ def _run_case(aa, oracle, wl, *, given=False, module=False, blk=(3, 2), kw=None,
                              floor=float(np.sqrt(np.abs(q).sum())))
         _check_param(got["ddwc_w"], ref["ddwc_w"], wl.dtype, wl.name + " ddwc_w")
         _check_param(got["ddwc_b"], ref["ddwc_b"], wl.dtype, wl.name + " ddwc_b")
+    if mask and wl.dtype == "f32":      # the forward pass on the same kernels
+        out = aa.agent_attn_fwd(dv["Q"], dv["K"], dv["V"], Ad, grid=wl.grid, params=pd, **kw)
+        _check(out, oracle.agent_attn_fwd(f64["Q"], f64["K"], f64["V"], A=inputs.to_float64(A_st, wl.dtype), **okw), wl.dtype,
+               wl.name + " out")
     return got
 
 
@@ -208,6 +217,29 @@ def test_backward_single_module_terms(aa, oracle, keys):
     for k in ref:
         a, b = got[k].double(), ref[k].double()
         assert bool(torch.isfinite(a).all()) and float((a - b).norm() / b.norm()) <= 1e-2, k
+
+
+# places of a component that mask tokens of the aggregation (B1) or agents of the broadcast (B2), other tokens / agents staying
+ALL = slice(None)
+MASKED = {"b1_col": [(ALL, ALL, slice(0, 16)), (ALL, ALL, slice(17, None)), (ALL, 3, slice(2, 19))],
+          "b1_row": [(ALL, ALL, slice(0, 3)), (ALL, ALL, slice(12, None)), (ALL, 3, slice(0, 15))],
+          "b1_blk": [(ALL, ALL, 0), (ALL, ALL, ALL, 1), (ALL, 3, slice(0, 2))],
+          "b2_col": [(ALL, ALL, 3), (ALL, slice(0, 3), slice(1, None))],
+          "b2_row": [(ALL, ALL, slice(2, 5)), (ALL, slice(12, None), slice(0, 8))],
+          "b2_blk": [(ALL, ALL, ALL, 3), (ALL, 0, ALL, slice(1, None))]}
+
+
+@pytest.mark.parametrize("n,d", [(9, 32), (70, 64)])
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("key", sorted(MASKED))
+def test_masks_in_the_agent_bias(aa, oracle, key, dtype, n, d):
+    """Components that mask whole rows, columns, cells or agents, in the first tiles of a walk and in later ones, with
+    something left to attend to: every gradient and the fp32 forward at the usual bars (16 x 20 tokens, 1280 in all: the
+    fp32 forward takes its streaming kernels)."""
+    for place in MASKED[key]:
+        for value in (-1e4, -1e9):
+            wl = _wl("mask %s %s %g" % (key, place, value), dtype, (16, 20), (1, n), d, index=85)
+            _run_case(aa, oracle, wl, given=True, module=True, mask=(key, place, value, max(value, -1e9)))
 
 
 def test_backward_module_given_agents_and_residual(aa, oracle):
