@@ -72,8 +72,9 @@ struct UnitPlace {
 
 struct TokenArgs {
   const void *X, *Y, *M1, *M2;      // in the element type
-  const float *rs1, *rs2;
-  float *st1, *st2;
+  const float *rs1, *rs2, *rw1;      // reference, D1 and weight of the agents' softmax rows
+  float *st1, *st2, *st3;            // of the tokens': reference, D2, weight
+  int* large;                        // 16 bits with a bias: per unit, whether one of these rows has a large reference
   void *O1, *O2;
   int N, n, d, n_rows, ch_rows;      // n_rows: n rounded up to 32; ch_rows: agents staged at a time (x32)
   const float* dA;                   // kBc: the finished dA [units][n][d] when the agents were pooled (else null)
@@ -89,7 +90,8 @@ struct TokenArgs {
 
 struct AgentArgs {
   const void *X, *Y, *M1, *M2;      // in the element type
-  const float *ts1, *ts2, *rs1, *rs2;
+  const float *ts1, *ts2, *tw1, *rs1, *rs2, *rw1;      // as st1, st2, st3 and rs1, rs2, rw1 of TokenArgs
+  const int* large;           // as in TokenArgs
   float *P1, *P2, *pm, *pl;
   int N, n, d, chunk, S;      // chunk: tokens per range (without a bias)
   float sc;
@@ -112,7 +114,11 @@ hipError_t launch_agent(int prob, int dp, int cols, const AgentArgs& a, dim3 gri
 
 // --- backward_module.hip ---
 // Fills the tables of the kinds in use ([0]: B2, [1]: B1; the same ld, a multiple of 64).
-hipError_t launch_backward_bias_tables(const Problem& p, const BiasTables (&t)[2], const bool (&used)[2], hipStream_t st);
+// Also clears `flags` (n_flags of them, may be null).
+hipError_t launch_backward_bias_tables(const Problem& p, const BiasTables (&t)[2], const bool (&used)[2], int* flags, int n_flags,
+                                       hipStream_t st);
+// A flag that any number of lanes set
+__device__ __forceinline__ void set_flag(int* f) { __hip_atomic_store(f, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 // Parts of one kind's bias gradients as the agent kernels leave them (fp32, unrounded score gradients):
 //   gt [units][segs][cells][wp / 4][ld][4]    sums of (1 - f) dS and f dS over the image rows of a segment, for the
 //                                             cell rows the segment touches (others are not written)

@@ -22,12 +22,13 @@ namespace {
 // Sums over the token ranges, one 64-lane block per (agent, unit), lane = channel (and channel + 64), ranges
 // in order.
 // ---------------------------------------------------------------------------
-// log-sum-exp merge of the recomputed aggregation: V_A (fp32 and element type) and lse1 (log2 domain)
+// log-sum-exp merge of the recomputed aggregation: V_A (fp32 and element type), reference and weight of the rows (log2
+// domain; w1 null: the log-sum-exp, no weight)
 template <class E>
 __global__ __launch_bounds__(64) void fused_merge_kernel(const float* __restrict__ acc, const float* __restrict__ pm,
                                                          const float* __restrict__ pl, int S, int n, int d,
                                                          float* VAf, typename E::T* VAe,
-                                                         float* __restrict__ lse1) {
+                                                         float* __restrict__ lse1, float* __restrict__ w1, int* __restrict__ large) {
   const int ag = blockIdx.x, u = blockIdx.y, lane = threadIdx.x;
   __shared__ float wgt[64];
   // lane s holds range s (S <= 64)
@@ -45,7 +46,12 @@ __global__ __launch_bounds__(64) void fused_merge_kernel(const float* __restrict
     VAf[o] = v;
     VAe[o] = E::from_f32(v);      // fp32: the same array
   }
-  if (lane == 0) lse1[(size_t)u * n + ag] = M + __builtin_amdgcn_logf(L);
+  if (lane == 0) {
+    const bool apart = w1 && (El<E>::kBytes == 4 || fabsf(M) > kLargeRef);
+    lse1[(size_t)u * n + ag] = apart ? M : M + __builtin_amdgcn_logf(L);
+    if (w1) w1[(size_t)u * n + ag] = apart ? 1.0f / L : 1.0f;
+    if (large && apart) set_flag(large + u);
+  }
 }
 
 // dV_A = sum of the ranges (element type), D1 = rowsum(dV_A o V_A), dA = c2 * sum of the ranges
@@ -98,7 +104,8 @@ struct FusedPlan {
   bool bias[2];
   int cells[2], ld, segs[2], seg_len[2], pairs[2], per[2];
   // workspace offsets in floats (every region a multiple of 64 floats)
-  size_t VAf, VAe, dVAe, lse1, D1, lse2, D2, dAf, part, total;
+  size_t VAf, VAe, dVAe, lse1, w1, D1, lse2, w2, large, D2, dAf, part, total;
+  bool weights[2];      // softmax rows may have a weight beside their reference
   size_t ta[2], tx[2], rows[2], yi[2], gt[2], gr[2], gsum[2], dwc;
 };
 
@@ -112,6 +119,7 @@ FusedPlan fused_plan(const Problem& p, bool forward = false) {
   f.n_rows = (p.n + 31) / 32 * 32;      // the token kernels take agent tiles in pairs
   f.ch_rows = std::min(f.n_rows, f32 ? El<ElemF32>::kChunk : El<ElemBF16>::kChunk);
   f.bias[0] = p.b2.any(), f.bias[1] = p.b1.any();
+  f.weights[0] = f32 || f.bias[0], f.weights[1] = f32 || f.bias[1];
   f.token_cols = f32 && f.DP > 64 ? 1 : 2;
   // token ranges: about two blocks per CU for the broadcast's agent kernel (192 registers) and with a bias, three for
   // the other two (which fit three blocks; four measured no faster).  At most 64: the merge gives every range a lane.
@@ -156,6 +164,9 @@ FusedPlan fused_plan(const Problem& p, bool forward = false) {
     f.dVAe = o, o += f32 ? u * nd : u * nd / 2;
     f.D1 = o, o += un;
     f.lse2 = o, o += uN;
+    if (f.weights[1]) f.w1 = o, o += un;
+    if (f.weights[0]) f.w2 = o, o += uN;
+    f.large = o, o += up64(2 * u);
     f.D2 = o, o += uN;
     f.dAf = o, o += u * nd;
   }
@@ -185,6 +196,8 @@ struct Pass {
   const FusedPlan& f;
   float* ws;
   hipStream_t st;
+  float* w1;                  // where the agents' softmax rows leave their weights (null: they have none)
+  int* large;                 // [2][units], of the tokens' and the agents' rows (null: no kernel asks)
   BiasTables bt[2] = {};
 
   hipError_t tables() {
@@ -195,11 +208,11 @@ struct Pass {
       YInfo* yi = reinterpret_cast<YInfo*>(ws + f.yi[k]);
       bt[k] = BiasTables{ws + f.ta[k], ws + f.tx[k], rows, yi, f.cells[k], f.ld};
     }
-    return launch_backward_bias_tables(p, bt, f.bias, st);
+    return launch_backward_bias_tables(p, bt, f.bias, large, large ? 2 * p.units : 0, st);
   }
   hipError_t token(int prob, TokenArgs& a) {
     const int k = prob == kAgg ? 1 : 0;
-    const size_t lds = (size_t)2 * f.ch_rows * (f.DP + El<E>::kRowPad) * sizeof(T) + (size_t)2 * f.ch_rows * sizeof(float);
+    const size_t lds = (size_t)2 * f.ch_rows * (f.DP + El<E>::kRowPad) * sizeof(T) + (size_t)3 * f.ch_rows * sizeof(float);
     if (f.bias[k]) {
       a.bt = bt[k];
       const int items = ((p.gw + 15) / 16) * ((p.gh + f.token_cols - 1) / f.token_cols);
@@ -212,7 +225,7 @@ struct Pass {
   // gt, gr: where the parts of the bias gradients go (null: not wanted)
   hipError_t agent(int prob, AgentArgs& a, float* gt, float* gr) {
     const int k = prob == kBc ? 0 : 1;
-    const size_t lds = (size_t)4 * 32 * (f.DP + El<E>::kRowPad) * sizeof(T) + 2 * 64 * sizeof(float);
+    const size_t lds = (size_t)4 * 32 * (f.DP + El<E>::kRowPad) * sizeof(T) + 2 * 96 * sizeof(float);
     const dim3 grid(f.S[k], f.agent_blocks[k], p.units);
     a.chunk = f.chunk[k], a.S = f.S[k];
     if (!f.bias[k]) return launch_agent<E, false>(prob, f.DP, f.agent_cols[k], a, grid, lds, st);
@@ -241,7 +254,8 @@ struct Pass {
     const hipError_t e = agent(kFwd, a, nullptr, nullptr);
     if (e != hipSuccess) return e;
     fused_merge_kernel<E><<<dim3(p.n, p.units), dim3(64), 0, st>>>(part, pm, pl, f.S[1], p.n, p.d, ws + f.VAf,
-                                                                   reinterpret_cast<T*>(ws + f.VAe), ws + f.lse1);
+                                                                   reinterpret_cast<T*>(ws + f.VAe), ws + f.lse1, w1,
+                                                                   large && f.bias[1] ? large + p.units : nullptr);
     return hipGetLastError();
   }
 };
@@ -260,7 +274,9 @@ hipError_t run_fused(const Problem& p, const FusedPlan& f, const void* Q, const 
   float* part2 = part1 + (size_t)U * f.S[0] * n * d;      // kBc only
   const float sc1 = p.scale1 * kLog2e, sc2 = p.scale2 * kLog2e;
   const dim3 rgrid(n, U);
-  Pass<E> pass{p, f, ws, st};
+  float *w1 = f.weights[1] ? ws + f.w1 : nullptr, *w2 = f.weights[0] ? ws + f.w2 : nullptr;
+  int* large = El<E>::kBytes == 2 && (f.bias[0] || f.bias[1]) ? reinterpret_cast<int*>(ws + f.large) : nullptr;
+  Pass<E> pass{p, f, ws, st, w1, large};
   hipError_t e = pass.tables();
   if (e != hipSuccess) return e;
   // the aggregation again
@@ -270,6 +286,7 @@ hipError_t run_fused(const Problem& p, const FusedPlan& f, const void* Q, const 
   AgentArgs ag = pass.agent_args();
   TokenArgs tk = pass.token_args();
   tk.X = Q, tk.Y = dO, tk.M1 = A, tk.M2 = VAe, tk.st1 = lse2, tk.st2 = D2, tk.sc = sc2, tk.oscale = p.scale2;
+  tk.st3 = w2, ag.tw1 = w2, tk.rw1 = ag.rw1 = w1, tk.large = large, ag.large = large;
   if ((e = pass.token(kBcStat, tk)) != hipSuccess) return e;
   ag.X = Q, ag.Y = dO, ag.M1 = A, ag.M2 = VAe, ag.ts1 = lse2, ag.ts2 = D2, ag.P1 = part1, ag.P2 = part2, ag.sc = sc2;
   if ((e = pass.agent(kBc, ag, pg.db2_col || pg.db2_blk ? ws + f.gt[0] : nullptr, pg.db2_row ? ws + f.gr[0] : nullptr)) !=
@@ -278,6 +295,7 @@ hipError_t run_fused(const Problem& p, const FusedPlan& f, const void* Q, const 
   fused_reduce_bc_kernel<E><<<rgrid, dim3(64), 0, st>>>(part1, part2, f.S[0], n, d, VAf, dVAe, D1, dAf, p.scale2);
 
   // aggregation
+  if (large) tk.large = large + U, ag.large = large + U;
   tk.X = K, tk.Y = V, tk.M2 = dVAe, tk.rs1 = lse1, tk.rs2 = D1, tk.sc = sc1, tk.oscale = p.scale1;
   tk.O1 = dK, tk.O2 = dV, tk.G = dO, tk.vk = p.vk, tk.dwc_w = p.dwc_w;
   if ((e = pass.token(kAgg, tk)) != hipSuccess) return e;
@@ -287,6 +305,7 @@ hipError_t run_fused(const Problem& p, const FusedPlan& f, const void* Q, const 
     return e;
   fused_reduce_agg_kernel<E><<<rgrid, dim3(64), 0, st>>>(part1, f.S[1], n, d, dAf, agents_given ? (T*)dA : nullptr, p.scale1);
   // dQ last: the pooling term needs the finished dA
+  tk.large = large;
   tk.X = Q, tk.Y = dO, tk.M2 = VAe, tk.sc = sc2, tk.oscale = p.scale2, tk.O1 = dQ, tk.dA = agents_given ? nullptr : dAf;
   if ((e = pass.token(kBc, tk)) != hipSuccess) return e;
 
@@ -332,7 +351,7 @@ size_t forward_f32_workspace_floats(const Problem& p) { return fused_plan(p, tru
 hipError_t launch_forward_f32(const Problem& p, const void* Q, const void* K, const void* V, const void* A, float* ws,
                               void* out, hipStream_t st) {
   const FusedPlan f = fused_plan(p, true);
-  Pass<ElemF32> pass{p, f, ws, st};
+  Pass<ElemF32> pass{p, f, ws, st, nullptr, nullptr};
   hipError_t e = pass.tables();
   if (e != hipSuccess) return e;
   if ((e = pass.aggregate(K, V, A)) != hipSuccess) return e;

@@ -105,8 +105,10 @@ __device__ __forceinline__ void bias_table_block(const TableKind& k, unsigned bl
   }
 }
 
-__global__ __launch_bounds__(256) void bias_tables_kernel(TableKind first, TableKind second, int n, int gh, int gw, int ld) {
+__global__ __launch_bounds__(256) void bias_tables_kernel(TableKind first, TableKind second, int n, int gh, int gw, int ld,
+                                                          int* flags, int n_flags) {
   __shared__ __align__(16) float tile[16][68];
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < n_flags; i += gridDim.x * 256) flags[i] = 0;
   const bool one = blockIdx.x < first.blocks;
   const unsigned block = one ? blockIdx.x : blockIdx.x - first.blocks;
   const TableKind& k = one ? first : second;
@@ -403,7 +405,8 @@ DwcPlan dwc_plan(const Problem& p) {
 
 }  // namespace
 
-hipError_t launch_backward_bias_tables(const Problem& p, const BiasTables (&t)[2], const bool (&used)[2], hipStream_t st) {
+hipError_t launch_backward_bias_tables(const Problem& p, const BiasTables (&t)[2], const bool (&used)[2], int* flags, int n_flags,
+                                       hipStream_t st) {
   TableKind kinds[2] = {};
   int ld = 0;
   for (int i = 0; i < 2; ++i) {
@@ -419,7 +422,7 @@ hipError_t launch_backward_bias_tables(const Problem& p, const BiasTables (&t)[2
   }
   const unsigned blocks = kinds[0].blocks + kinds[1].blocks;
   if (blocks == 0) return hipSuccess;
-  bias_tables_kernel<<<dim3(blocks), dim3(256), 0, st>>>(kinds[0], kinds[1], p.n, p.gh, p.gw, ld);
+  bias_tables_kernel<<<dim3(blocks), dim3(256), 0, st>>>(kinds[0], kinds[1], p.n, p.gh, p.gw, ld, flags, n_flags);
   return hipGetLastError();
 }
 

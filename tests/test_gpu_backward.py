@@ -242,6 +242,63 @@ def test_masks_in_the_agent_bias(aa, oracle, key, dtype, n, d):
             _run_case(aa, oracle, wl, given=True, module=True, mask=(key, place, value, max(value, -1e9)))
 
 
+# places that mask a whole softmax row: every token of an agent (B1), every agent of a token (B2)
+ROWS = {"b1_col": (ALL, 3), "b1_row": (ALL, 3), "b1_blk": (ALL, 3), "b2_col": (ALL, slice(17, None)),
+        "b2_row": (ALL, slice(0, 3)), "b2_blk": (ALL, 0)}
+
+
+def _masked_rows(aa, oracle, key, dtype, n, d, value):
+    """dQ, dK, dV, dA with the rows of ROWS[key] at `value`, the reference, dO"""
+    wl = _wl("rows", dtype, (16, 20), (1, n), d, index=86)
+    t = inputs.make_qkv(wl)
+    t["dO"] = inputs.make_tensor((wl.units, wl.N, d), stream=wl.index * 16 + 12, dtype=dtype)
+    t["A"] = inputs.make_tensor((wl.units, n, d), stream=wl.index * 16 + 11, dtype=dtype)
+    dv = [util.to_device(t[k], dtype, (wl.batch, wl.heads) + t[k].shape[1:]) for k in ("Q", "K", "V", "dO", "A")]
+    params = inputs.make_module_params(wl.heads, n, d, wl.grid, blk=(3, 2), index=wl.index)
+    params = {k: params[k] for k in ROWS}
+    params[key][ROWS[key]] = value
+    got = aa.agent_attn_bwd(*dv, grid=wl.grid, params=util.params_to_device(params))
+    f64 = {k: inputs.to_float64(v, dtype) for k, v in t.items()}
+    B1, B2 = util.dense_biases(oracle, params, wl.heads, n, wl.grid)
+    ref = oracle.agent_attn_bwd(f64["Q"], f64["K"], f64["V"], f64["dO"], A=f64["A"], heads=wl.heads, grid=wl.grid, B1=B1, B2=B2)
+    return {k: util.to_host64(got[k]).reshape(ref[k].shape) for k in ("dQ", "dK", "dV", "dA")}, ref, f64["dO"]
+
+
+@pytest.mark.parametrize("n,d", [(9, 32), (70, 64), (40, 128)])
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("key", sorted(ROWS))
+def test_backward_softmax_rows_masked_throughout(aa, oracle, key, dtype, n, d):
+    """Rows in which every entry is masked stay softmax rows.  At -1e4 an fp32 score is a multiple of 2^-10, weights are
+    good to 7e-4.  At -1e9 it is one of 64 and the weights are what the rounding leaves, but they add up to one: then
+    sum_t dV = sum_a dV_A = sum_t dO, to the roundings of P1, P2, dV_A and dV (a few 2^-9, 2^-12 of dO in 16 bits)."""
+    got, ref, _ = _masked_rows(aa, oracle, key, dtype, n, d, -1e4)
+    for k in ref.keys() & got.keys():
+        util.assert_parity(got[k], ref[k], dtype, "%s %s" % (key, k), max_abs=np.inf, rel_l2={"f32": 1e-3, "f16": 5e-3, "bf16": 1e-2}[dtype])
+    got, ref, dO = _masked_rows(aa, oracle, key, dtype, n, d, -1e9)
+    assert all(np.isfinite(v).all() for v in got.values())
+    err = np.linalg.norm(got["dV"].sum(1) - dO.sum(1)) / np.linalg.norm(dO)
+    assert err <= {"f32": 2e-6, "f16": 1e-3, "bf16": 8e-3}[dtype], err
+
+
+@pytest.mark.parametrize("blk", [True, False])
+def test_backward_f32_holds_the_weights_of_its_rows(aa, oracle, blk):
+    """fp32 gradients with and without an agent bias, relative error below 6e-7 (3e-7 to 4e-7 measured): a weight taken
+    from one fp32 log-sum-exp is off by up to 2^-24 of that, which made them 7e-7 to 1.1e-6 with a bias."""
+    wl = _wl("f32 rows", "f32", (30, 41), (5, 7), 48, index=87)
+    t = inputs.make_qkv(wl)
+    t["dO"] = inputs.make_tensor((wl.units, wl.N, wl.d), stream=wl.index * 16 + 12, dtype="f32")
+    t["A"] = inputs.make_tensor((wl.units, wl.n, wl.d), stream=wl.index * 16 + 11, dtype="f32")
+    dv = [util.to_device(t[k], "f32", (wl.batch, wl.heads) + t[k].shape[1:]) for k in ("Q", "K", "V", "dO", "A")]
+    params = inputs.make_module_params(wl.heads, wl.n, wl.d, wl.grid, blk=(3, 2), index=wl.index)
+    params = {k: params[k] for k in ROWS} if blk else {}
+    got = aa.agent_attn_bwd(*dv, grid=wl.grid, params=util.params_to_device(params) if blk else None)
+    f64 = {k: inputs.to_float64(v, "f32") for k, v in t.items()}
+    B1, B2 = util.dense_biases(oracle, params, wl.heads, wl.n, wl.grid)
+    ref = oracle.agent_attn_bwd(f64["Q"], f64["K"], f64["V"], f64["dO"], A=f64["A"], heads=wl.heads, grid=wl.grid, B1=B1, B2=B2)
+    for k in ("dQ", "dK", "dV", "dA"):
+        util.assert_parity(util.to_host64(got[k]).reshape(ref[k].shape), ref[k], "f32", k, rel_l2=6e-7)
+
+
 def test_backward_module_given_agents_and_residual(aa, oracle):
     wl = _wl("module-given", "f32", (8, 8), (2, 8), 24)
     _run_case(aa, oracle, wl, given=True, module=True, kw=dict(v_residual_k=0.075, scale2=24 ** -0.15))
