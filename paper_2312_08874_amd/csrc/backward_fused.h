@@ -13,7 +13,11 @@ enum { kFwd = 0, kBc = 1, kAgg = 2, kBcStat = 3, kOut = 4 };
 //   ta [heads][cells][ld / 4][wp][4 agents]     for lanes that hold a token and four agents
 //   tx [heads][cells][wp / 4][ld][4 columns]    for lanes that hold an agent and four neighbours in x
 // rows [heads][gh][ld], null when there is no row component.
+// Entries of T and R are finite: below kBiasFloor (a mask of the type's lowest value or of minus infinity) they are that,
+// so that differences of two masked entries are zero.  What does not exist (columns past gw, agents past n in the kernels)
+// is kMaskedScore, far below the sum of two of them and still finite.
 // yi [gh]: what an image row needs to know of the interpolation along y.
+constexpr float kBiasFloor = -1.0e30f, kMaskedScore = -1.0e38f;
 struct YInfo {
   int cell, next;      // cell row i; the first image row below with another one (or gh)
   float f;             // weight of cell row i + 1 (0 on the last cell row)

@@ -23,6 +23,8 @@ struct TableKind {
   unsigned tblocks, rblocks, blocks;
 };
 
+__device__ __forceinline__ float floored(float v) { return v < kBiasFloor ? kBiasFloor : v; }      // keeps NaN
+
 template <int KIND>
 __device__ __forceinline__ void bias_table_block(const TableKind& k, unsigned block, int n, int gh, int gw, int ld,
                                                  float (&tile)[16][68]) {
@@ -42,7 +44,7 @@ __device__ __forceinline__ void bias_table_block(const TableKind& k, unsigned bl
       const int x = 16 * xt + i, a = 64 * at + al;
       float v = 0.0f;
       if (x >= gw) {
-        v = -1.0e30f;      // a column past the image weighs nothing
+        v = kMaskedScore;      // a column past the image weighs nothing
       } else if (a < n) {
         if (b.col) v = KIND == 1 ? b.col[((size_t)hd * n + a) * gw + x] : b.col[((size_t)hd * gw + x) * n + a];
         if (b.blk) {
@@ -52,10 +54,10 @@ __device__ __forceinline__ void bias_table_block(const TableKind& k, unsigned bl
           const size_t step = KIND == 1 ? 1 : n;
           const float* q = KIND == 1 ? b.blk + (((size_t)hd * n + a) * b.h0 + cell) * b.w0
                                      : b.blk + ((size_t)hd * b.h0 + cell) * b.w0 * n + a;
-          const float v0 = q[x0 * step], v1 = q[x1 * step];
+          const float v0 = floored(q[x0 * step]), v1 = floored(q[x1 * step]);
           v += v0 + (v1 - v0) * fx;
         }
-        v *= kLog2e;
+        v = floored(v * kLog2e);
       }
       tile[i][al] = v;
     }
@@ -79,7 +81,7 @@ __device__ __forceinline__ void bias_table_block(const TableKind& k, unsigned bl
       place(j, i, al);
       const int y = 16 * yt + i, a = 64 * at + al;
       float v = 0.0f;
-      if (y < gh && a < n) v = kLog2e * (KIND == 1 ? b.row[((size_t)hd * n + a) * gh + y] : b.row[((size_t)hd * gh + y) * n + a]);
+      if (y < gh && a < n) v = floored(kLog2e * (KIND == 1 ? b.row[((size_t)hd * n + a) * gh + y] : b.row[((size_t)hd * gh + y) * n + a]));
       tile[i][al] = v;
     }
     __syncthreads();

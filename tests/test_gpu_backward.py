@@ -237,7 +237,7 @@ def test_masks_in_the_agent_bias(aa, oracle, key, dtype, n, d):
     something left to attend to: every gradient and the fp32 forward at the usual bars (16 x 20 tokens, 1280 in all: the
     fp32 forward takes its streaming kernels)."""
     for place in MASKED[key]:
-        for value in (-1e4, -1e9):
+        for value in (-1e4, -1e9, float(np.finfo(np.float32).min), -np.inf):
             wl = _wl("mask %s %s %g" % (key, place, value), dtype, (16, 20), (1, n), d, index=85)
             _run_case(aa, oracle, wl, given=True, module=True, mask=(key, place, value, max(value, -1e9)))
 
@@ -278,6 +278,10 @@ def test_backward_softmax_rows_masked_throughout(aa, oracle, key, dtype, n, d):
     assert all(np.isfinite(v).all() for v in got.values())
     err = np.linalg.norm(got["dV"].sum(1) - dO.sum(1)) / np.linalg.norm(dO)
     assert err <= {"f32": 2e-6, "f16": 1e-3, "bf16": 8e-3}[dtype], err
+    # at the lowest float nothing of the scores is left, in 64 bits neither: the weights are equal
+    got, ref, _ = _masked_rows(aa, oracle, key, dtype, n, d, float(np.finfo(np.float32).min))
+    for k in ref.keys() & got.keys():
+        util.assert_parity(got[k], ref[k], dtype, "%s %s lowest" % (key, k), max_abs=np.inf, rel_l2={"f32": 1e-5, "f16": 5e-3, "bf16": 1e-2}[dtype])
 
 
 @pytest.mark.parametrize("blk", [True, False])
