@@ -641,8 +641,10 @@ __global__ __launch_bounds__(64) void dwc_param_sum_kernel(const float* __restri
 #pragma unroll
   for (int k = 0; k < 10; ++k) acc[k] = wave_sum(acc[k]);
   if (lane == 0) {
+    if (dw) {
 #pragma unroll
-    for (int k = 0; k < 9; ++k) dw[((size_t)hd * d + c) * 9 + k] = acc[k];
+      for (int k = 0; k < 9; ++k) dw[((size_t)hd * d + c) * 9 + k] = acc[k];
+    }
     if (db) db[(size_t)hd * d + c] = acc[9];
   }
 }
@@ -976,7 +978,7 @@ hipError_t backward_tail(const Problem& p, const float* Vf, const float* dOf, co
     value_extras_kernel<<<dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st>>>(dVf, dOf, p.dwc_w, p.vk, p.heads, N,
                                                                                     d, p.gh, p.gw, count);
   }
-  if (p.dwc_w && pg.ddwc_w) {
+  if (p.dwc_w && (pg.ddwc_w || pg.ddwc_b)) {
     const long long total = (long long)batch * N;
     const int slices = dwc_slices(p);
     const int slice_len = (int)((total + slices - 1) / slices);

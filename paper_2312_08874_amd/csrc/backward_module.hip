@@ -238,7 +238,7 @@ __device__ __forceinline__ void bias_grad_block(const GradKind& k, unsigned bloc
 
 struct DwcTotal {
   const float* part;
-  float *dw, *db;
+  float *dw, *db;         // either may be null
   int slices, count;      // count: heads * d
 };
 
@@ -270,8 +270,10 @@ __global__ __launch_bounds__(256) void param_grad_out_kernel(GradKind first, Gra
 #pragma unroll
   for (int k = 0; k < 10; ++k) acc[k] = wave_sum(acc[k]);
   if (lane == 0) {
+    if (dwc.dw) {
 #pragma unroll
-    for (int k = 0; k < 9; ++k) dwc.dw[(size_t)hc * 9 + k] = acc[k];
+      for (int k = 0; k < 9; ++k) dwc.dw[(size_t)hc * 9 + k] = acc[k];
+    }
     if (dwc.db) dwc.db[hc] = acc[9];
   }
 }
@@ -281,7 +283,7 @@ __global__ __launch_bounds__(256) void param_grad_out_kernel(GradKind first, Gra
 // A thread owns a 16-byte piece of the channels of an image column and walks down its rows with the 3 x 3 neighbourhood of V in
 // registers, so that a row costs three 16-byte reads of V (two of them shared with the neighbouring columns through
 // L1) and one of dO; CHP = 16-byte pieces per token rounded up to a power of two.  The lanes of a block are added by
-// a fixed tree, the blocks by dwc_param_sum_kernel.
+// a fixed tree, the blocks by param_grad_out_kernel.
 // grid = (slices, heads); slice = 256 / CHP (column, row segment, image) items.
 // ---------------------------------------------------------------------------
 template <class E>
@@ -458,7 +460,7 @@ hipError_t launch_backward_param_grads(const Problem& p, const BiasGradParts (&p
     bias_grad_sum_kernel<<<dim3(kinds[0].sblocks + kinds[1].sblocks), dim3(256), 0, st>>>(kinds[0], kinds[1], batch, p.heads, p.gh,
                                                                                        (size_t)(wp / 4) * ld);
   DwcTotal total{};
-  if (p.dwc_w && pg.ddwc_w) {
+  if (p.dwc_w && (pg.ddwc_w || pg.ddwc_b)) {
     const DwcPlan q = dwc_plan(p);
     const dim3 grid(q.slices, p.heads);
     auto go = [&](auto kernel, auto elem) {

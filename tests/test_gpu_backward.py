@@ -303,6 +303,41 @@ def test_backward_f32_holds_the_weights_of_its_rows(aa, oracle, blk):
         util.assert_parity(util.to_host64(got[k]).reshape(ref[k].shape), ref[k], "f32", k, rel_l2=6e-7)
 
 
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("only", [("ddwc_b",), ("ddwc_w",), ("db1_row", "ddwc_b")])
+def test_backward_single_parameter_gradients(aa, only, offset):
+    """A caller may ask for any of the parameter gradients: each has the bits it has when all are asked for, also the
+    convolution's bias without its weights.  offset 1: tensors that are not 16-byte aligned, the path that keeps the
+    matrices in memory."""
+    import ctypes
+    import torch
+    wl = _wl("single", "f32", (9, 10), (3, 2), 12, index=88)
+    params = util.params_to_device(inputs.make_module_params(wl.heads, wl.n, wl.d, wl.grid, blk=(3, 2), index=wl.index))
+    count = wl.units * wl.N * wl.d
+
+    def placed(i):
+        t = torch.zeros(count + 4, device="cuda")
+        v = t[offset:offset + count].reshape(wl.batch, wl.heads, wl.N, wl.d)
+        v.copy_(util.to_device(inputs.make_tensor((wl.units, wl.N, wl.d), stream=950 + i), "f32", v.shape))
+        return v
+
+    q, k, v, dO = (placed(i) for i in range(4))
+    A = util.to_device(inputs.make_tensor((wl.units, wl.n, wl.d), stream=954), "f32", (wl.batch, wl.heads, wl.n, wl.d))
+    full = aa.agent_attn_bwd(q, k, v, dO, A, grid=wl.grid, params=params)
+    desc, p = aa.make_desc(wl.batch, wl.heads, wl.N, wl.n, wl.d, 0, wl.grid), aa.make_params(params)
+    ws = torch.empty(int(aa.lib().agent_attn_bwd_workspace_bytes(ctypes.byref(desc), aa._pp(p))), dtype=torch.uint8, device="cuda")
+    outs = [torch.empty_like(full[x]) for x in ("dQ", "dK", "dV", "dA")]
+    grads, g = {x: torch.full_like(full[x], float("nan")) for x in only}, aa.aa_param_grads()
+    for x, t in grads.items():
+        setattr(g, x, t.data_ptr())
+    st = aa.lib().agent_attn_bwd(ctypes.byref(desc), q.data_ptr(), k.data_ptr(), v.data_ptr(), A.data_ptr(), aa._pp(p), dO.data_ptr(),
+                                 ws.data_ptr(), ws.numel(), *(t.data_ptr() for t in outs), ctypes.byref(g), None)
+    torch.cuda.synchronize()
+    assert st == 0
+    for x, t in grads.items():
+        assert torch.equal(t, full[x]), x
+
+
 def test_backward_module_given_agents_and_residual(aa, oracle):
     wl = _wl("module-given", "f32", (8, 8), (2, 8), 24)
     _run_case(aa, oracle, wl, given=True, module=True, kw=dict(v_residual_k=0.075, scale2=24 ** -0.15))
