@@ -29,9 +29,9 @@ struct BiasTables {
   int cells, ld;
 };
 
-// Where a unit's rows start and which row a token is: Layout for the recomputing kernels, with 32-bit strides, every
-// division a multiplication and the windows behind one branch (at 10 us a kernel the scalar instructions ahead of its
-// first load show).
+// Where a unit's rows start and which row a token is: Layout for the recomputing kernels, with 32-bit strides (in 16-byte
+// pieces of 1 << piece_log2 elements), every division a multiplication and the windows behind one branch (at 10 us a kernel
+// the scalar instructions ahead of its first load show).
 struct UnitPlace {
   uint32_t sb, sh, ob, oh;
   int sn, on, heads, line;
@@ -39,15 +39,17 @@ struct UnitPlace {
   int nwin, wxn, ww, win_rows;                           // win_rows: image rows of a window times line
 
   static unsigned long long rows(const Layout& l, int N) { return l.line ? (unsigned long long)l.wh * l.line : (unsigned long long)N; }
-  // strides below 2^32 elements, a unit's extent below 2^32 bytes; windows only where N * ww < 2^32
-  static bool fits(const Layout& l, int N) {
-    return (unsigned long long)l.sb >> 32 == 0 && (unsigned long long)l.sh >> 32 == 0 && (unsigned long long)l.ob >> 32 == 0 &&
-           (unsigned long long)l.oh >> 32 == 0 && (l.line == 0 || (unsigned long long)N * l.ww >> 32 == 0) &&
-           rows(l, N) * (unsigned long long)l.sn >> 30 == 0 && rows(l, N) * (unsigned long long)l.on >> 30 == 0;
+  // strides below 2^34 elements, windows only where N * ww < 2^32; short_units: a unit's extent below 2^32 bytes, for the
+  // kernels with a bias and the convolution, which keep their places within a unit in 32 bits
+  static bool fits(const Layout& l, int N, bool short_units) {
+    return ((unsigned long long)l.sb | (unsigned long long)l.sh | (unsigned long long)l.ob | (unsigned long long)l.oh) >> 34 == 0 &&
+           (l.line == 0 || (unsigned long long)N * l.ww >> 32 == 0) &&
+           (!short_units || (rows(l, N) * (unsigned long long)l.sn >> 30 == 0 && rows(l, N) * (unsigned long long)l.on >> 30 == 0));
   }
-  static UnitPlace make(const Layout& l, int heads) {
+  static UnitPlace make(const Layout& l, int heads, int piece_log2) {
     UnitPlace p{};
-    p.sb = (uint32_t)l.sb, p.sh = (uint32_t)l.sh, p.ob = (uint32_t)l.ob, p.oh = (uint32_t)l.oh;
+    p.sb = (uint32_t)(l.sb >> piece_log2), p.sh = (uint32_t)(l.sh >> piece_log2);
+    p.ob = (uint32_t)(l.ob >> piece_log2), p.oh = (uint32_t)(l.oh >> piece_log2);
     p.sn = l.sn, p.on = l.on, p.heads = heads, p.line = l.line;
     p.nwin = l.nwin, p.wxn = l.wxn, p.ww = l.line ? l.ww : 0, p.win_rows = l.wh * l.line;
     p.inv_heads = quotient_inverse(heads), p.inv_nwin = quotient_inverse(l.nwin), p.inv_wxn = quotient_inverse(l.wxn);
@@ -55,16 +57,17 @@ struct UnitPlace {
     return p;
   }
   __device__ __forceinline__ int entry(int u) const { return quotient(u, inv_heads); }
+  template <int kPiece>
   __device__ __forceinline__ size_t base(int u, bool out) const {
     const uint32_t bw = entry(u), hd = u - bw * heads;
     uint32_t b = bw;
-    size_t at = (size_t)hd * (out ? oh : sh);
+    size_t at = 0;
     if (line != 0) {
       b = quotient(bw, inv_nwin);
       const int win = bw - b * nwin, wy = quotient(win, inv_wxn), wx = win - wy * wxn;
       at += ((size_t)wy * (size_t)win_rows + (size_t)(wx * ww)) * (size_t)(out ? on : sn);
     }
-    return at + (size_t)b * (out ? ob : sb);
+    return at + ((size_t)hd * (out ? oh : sh) + (size_t)b * (out ? ob : sb)) * kPiece;
   }
   __device__ __forceinline__ size_t row(int t) const {
     if (line == 0) return (size_t)t;

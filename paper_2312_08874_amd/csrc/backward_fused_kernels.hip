@@ -235,12 +235,12 @@ struct Pass {
   }
   AgentArgs agent_args() const {
     AgentArgs a{};
-    a.N = p.N, a.n = p.n, a.d = p.d, a.at = UnitPlace::make(p.lay, p.heads), a.gh = p.gh, a.gw = p.gw;
+    a.N = p.N, a.n = p.n, a.d = p.d, a.at = UnitPlace::make(p.lay, p.heads, El<E>::kBytes == 4 ? 2 : 3), a.gh = p.gh, a.gw = p.gw;
     return a;
   }
   TokenArgs token_args() const {
     TokenArgs a{};
-    a.N = p.N, a.n = p.n, a.d = p.d, a.n_rows = f.n_rows, a.ch_rows = f.ch_rows, a.at = UnitPlace::make(p.lay, p.heads);
+    a.N = p.N, a.n = p.n, a.d = p.d, a.n_rows = f.n_rows, a.ch_rows = f.ch_rows, a.at = UnitPlace::make(p.lay, p.heads, El<E>::kBytes == 4 ? 2 : 3);
     a.gh = p.gh, a.gw = p.gw, a.ah = p.ah, a.aw = p.aw;
     return a;
   }
@@ -317,16 +317,19 @@ hipError_t run_fused(const Problem& p, const FusedPlan& f, const void* Q, const 
 
 }  // namespace
 
+// places within a unit in 32 bits (see UnitPlace::fits)
+static bool short_units(const Problem& p) { return p.b1.any() || p.b2.any() || p.dwc_w; }
+
 bool backward_fused_supported(const Problem& p) {
   return p.d % (p.dtype == 0 ? 4 : 8) == 0 && p.d <= 128 && p.units <= 65535 &&
-         (unsigned long long)p.N * p.d * p.heads < (1ull << 32) && (unsigned long long)p.N * p.d < (1ull << 30);      // UnitPlace::fits, dense
+         (unsigned long long)p.N * p.d * p.heads >> 34 == 0 && (!short_units(p) || (unsigned long long)p.N * p.d < (1ull << 30));
 }
 
 bool fused_layout_supported(const Problem& p) {
   const int m = p.dtype == 0 ? 4 : 8;      // 16-byte rows
   const Layout& l = p.lay;
   return l.sb % m == 0 && l.sh % m == 0 && l.sn % m == 0 && l.ob % m == 0 && l.oh % m == 0 && l.on % m == 0 &&
-         UnitPlace::fits(l, p.N);
+         UnitPlace::fits(l, p.N, short_units(p));
 }
 
 size_t backward_fused_workspace_floats(const Problem& p) { return fused_plan(p).total; }

@@ -230,6 +230,15 @@ def test_bwd_workspace_of_the_largest_workload():
                                                                    (32, 32))), None) > 2e9
 
 
+@pytest.mark.parametrize("heads,side,d", [(1, 4096, 64), (64, 1024, 64), (3, 4096, 128)])
+def test_bwd_workspace_of_very_large_tensors(heads, side, d):
+    """Pure 16-bit problems whose units or images pass 2^30 and 2^32 elements keep no attention matrix either: a few
+    floats per token, where the other path asks for 7 d + 4 n of them."""
+    desc = make_desc(1, heads, side * side, 9, d, binding.AA_BF16, (side, side), (3, 3))
+    need = binding.lib().agent_attn_bwd_workspace_bytes(ctypes.byref(desc), None)
+    assert 0 < need < 4 * heads * side * side * 4
+
+
 def test_bwd_rejects_bad_arguments():
     """agent_attn_bwd validates on the host before anything is launched."""
     L = binding.lib()

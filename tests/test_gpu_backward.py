@@ -338,6 +338,32 @@ def test_backward_single_parameter_gradients(aa, only, offset):
         assert torch.equal(t, full[x]), x
 
 
+def test_backward_of_a_unit_past_2_30_elements(aa):
+    """A pure 16-bit unit of 2^24 + 77 tokens, 64 channels: every gradient against plain fp32 products (bf16 bar of this file)."""
+    import torch
+    N, n, d = (1 << 24) + 77, 4, 64
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    q, k, v, g = (torch.randn(N, d, generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(4))
+    a = torch.randn(n, d, generator=gen, device="cuda", dtype=torch.bfloat16)
+    got = aa.agent_attn_bwd(*(x[None, None] for x in (q, k, v, g)), a[None, None])
+    c, A = d ** -0.5, a.float()
+    P1 = torch.softmax(c * (A @ k.float().t()), 1)
+    VA = P1 @ v.float()
+    P2 = torch.softmax(c * (q.float() @ A.t()), 1)
+    dVA = P2.t() @ g.float()
+    dP2 = g.float() @ VA.t()
+    dS2 = P2 * (dP2 - (P2 * dP2).sum(1, keepdim=True))
+    dP1 = dVA @ v.float().t()
+    dS1 = P1 * (dP1 - (P1 * dP1).sum(1, keepdim=True))
+    ref = {"dQ": c * (dS2 @ A), "dK": c * (dS1.t() @ A), "dV": P1.t() @ dVA, "dA": c * (dS2.t() @ q.float() + dS1 @ k.float())}
+    for name, r in ref.items():
+        x = got[name][0, 0].float()
+        assert bool(torch.isfinite(x).all()), name
+        for part in (slice(0, None), slice(-1000, None)):      # all, and the end by itself
+            err = float((x[part] - r[part]).norm() / r[part].norm())
+            assert err <= 1e-2, (name, err)
+
+
 def test_backward_module_given_agents_and_residual(aa, oracle):
     wl = _wl("module-given", "f32", (8, 8), (2, 8), 24)
     _run_case(aa, oracle, wl, given=True, module=True, kw=dict(v_residual_k=0.075, scale2=24 ** -0.15))
