@@ -321,7 +321,10 @@ Plan make_plan(const aa_desc* d, const aa_params* params = nullptr, bool small =
   if (!(params && params->bias_tables)) off += pl.bias.total;      // prepared tables need no room here
   pl.off_f32 = kNoStage;
   const Problem full = make_problem(d, params);
-  if (!small && d->n_splits <= 0 && aa::forward_f32_supported(full) && !few_biased_tokens(full)) {      // an explicit split count: the kernels that take one
+  // not with an explicit split count (the kernels that take one), nor where the one-launch kernel serves the shape (it asks
+  // the same of pointers and strides, so these are no fallback)
+  if (!small && d->n_splits <= 0 && aa::forward_f32_supported(full) && !few_biased_tokens(full) &&
+      !(pl.prefer_fused && aa::fused_f32_supported(full))) {
     pl.off_f32 = off;
     off += align_up(aa::forward_f32_workspace_floats(full) * sizeof(float));
   }

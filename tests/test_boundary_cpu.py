@@ -215,6 +215,16 @@ def test_binding_has_no_fallback():
     assert "oracle" not in src.replace("no CPU or eager fallback", "")
 
 
+@pytest.mark.parametrize("batch,heads,d,splits", [(1, 1, 32, 2), (64, 3, 16, 1)])
+def test_fwd_workspace_of_the_one_launch_f32_kernel(batch, heads, d, splits):
+    """Shapes that the one-launch fp32 kernel serves ask for the fallback's buffers only: as many bytes as with the split
+    count that the fallback would choose, which rules the streaming kernels out."""
+    def need(**kw):
+        return binding.workspace_bytes(make_desc(batch, heads, 196, 49, d, binding.AA_F32, (14, 14), (7, 7), **kw))
+    assert "fused_f32" in binding.plan_str(make_desc(batch, heads, 196, 49, d, binding.AA_F32, (14, 14), (7, 7)))
+    assert need() == need(n_splits=splits) > 0
+
+
 def test_bwd_workspace_of_the_largest_workload():
     """The recomputing backward keeps no attention matrix: for the 16384-token, 1024-agent workload its workspace
     stays below 200 MB, where the path that a module term selects needs the two n x N matrices several times over."""
