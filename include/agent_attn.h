@@ -26,7 +26,7 @@
  *    pointers that are multiples of 16 bytes, anything else takes the reference kernels.  A
  *    [batch, heads, n, d], V_A and the workspace are dense.  Distinct elements of `out` must not
  *    alias.  token t = y*grid_w + x; agent a = ay*agent_w + ax.  The backward entry point
- *    takes the same strides (through dense staging copies in its workspace).
+ *    takes the same strides (what its kernels cannot address goes through dense staging copies in its workspace).
  *    Element type is desc->dtype (fp32, fp16 or bf16); all accumulation is fp32;
  *    `out` is rounded once to nearest-even.
  *  - Calls enqueue work on `hip_stream` (a hipStream_t passed as void*, NULL =
@@ -94,9 +94,11 @@ typedef struct {
                                windows in row-major order (dA likewise).  Served by agent_attn_fwd (and its
                                _static / _timed forms) and agent_attn_bwd; the stage entry points return
                                AA_ERR_UNSUPPORTED for a windowed descriptor.  fp32 and problems served by
-                               the one-block-per-unit kernel read the windows in place; the other 16-bit
-                               kernel families and the backward pass work on window-major copies that the
-                               call makes in the workspace, and scatter their results back. */
+                               the one-block-per-unit kernel read the windows in place, and so does the
+                               backward pass where its recomputing kernels serve the problem (see
+                               there); the other 16-bit kernel families and the rest of the backward
+                               pass work on window-major copies that the call makes in the workspace,
+                               and scatter their results back. */
 } aa_desc;
 
 /* Module-mode parameters (host struct of device pointers, fp32).  A NULL pointer
