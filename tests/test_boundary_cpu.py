@@ -227,7 +227,8 @@ def test_fwd_workspace_of_the_one_launch_f32_kernel(batch, heads, d, splits):
 
 def test_bwd_workspace_of_the_largest_workload():
     """The recomputing backward keeps no attention matrix: for the 16384-token, 1024-agent workload its workspace
-    stays below 200 MB, where the path that a module term selects needs the two n x N matrices several times over."""
+    stays below 200 MB.  With a module term the query also covers the path that keeps the two n x N matrices several times
+    over, which unaligned tensors take."""
     L = binding.lib()
     desc = make_desc(1, 8, 16384, 1024, 64, binding.AA_BF16, (128, 128), (32, 32))
     pure = L.agent_attn_bwd_workspace_bytes(ctypes.byref(desc), None)
@@ -235,7 +236,7 @@ def test_bwd_workspace_of_the_largest_workload():
     p.b1_col = 1 << 42
     with_bias = L.agent_attn_bwd_workspace_bytes(ctypes.byref(desc), ctypes.byref(p))
     assert 0 < pure < 200e6 and with_bias > 2e9
-    # fp32 problems take the other path as well
+    # the same for fp32 problems
     assert L.agent_attn_bwd_workspace_bytes(ctypes.byref(make_desc(1, 8, 16384, 1024, 64, binding.AA_F32, (128, 128),
                                                                    (32, 32))), None) > 2e9
 
@@ -256,8 +257,8 @@ def test_bwd_rejects_bad_arguments():
     desc = make_desc(2, 3, 196, 49, 32, binding.AA_BF16, (14, 14), (7, 7))
     need = L.agent_attn_bwd_workspace_bytes(ctypes.byref(desc), None)
     assert need > 0 and need % 256 == 0
-    # a pure 16-bit problem keeps no attention matrix in the workspace; with a module term the reference path
-    # runs: about 4*n*N + 7*N*d + 4*n*d floats per unit
+    # a pure 16-bit problem keeps no attention matrix in the workspace; with a module term it also covers the
+    # reference path: about 4*n*N + 7*N*d + 4*n*d floats per unit
     assert need < 6 * 4 * (4 * 49 * 196)
     with_bias = aa_params()
     with_bias.b1_col = 12 * G

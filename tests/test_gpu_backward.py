@@ -2,12 +2,11 @@
 gradients on the same seeded inputs.
 
 Bar, per gradient tensor g with reference r: fp32 path max-abs <= 1e-4 * max(1, max|r|); fp16 / bf16
-paths max-abs <= 1e-2 * max(1, max|r|) and relative L2 <= 5e-3, except bf16 problems with module terms or
-the enlarged second scale of Appendix C.1 (see _check): 1e-2 (the former run the kernels that keep the attention matrices in memory, where the probabilities and the
-score gradients are stored in bf16 before the products that give dQ, dK, dV, so a gradient chains three
+paths max-abs <= 1e-2 * max(1, max|r|) and relative L2 <= 5e-3, except bf16 problems with module terms, wider
+than 128 or with the enlarged second scale of Appendix C.1 (see _check): 1e-2 (a gradient of theirs chains three
 operands of relative error up to 2^-9; five unit roundoffs, as for the parameter gradients below; a near
-one-hot broadcast softmax - the SD variant's scale d^-0.15 together with a bias - reaches 7e-3).  Pure
-16-bit problems run the kernels that recompute their score tiles and round P and dS once, as operands
+one-hot broadcast softmax - the SD variant's scale d^-0.15 together with a bias - reaches 7e-3).  Up to 128
+channels the kernels recompute their score tiles and round P and dS once, as operands
 of the next product.  fp32 parameter gradients relative L2 <= 1e-4 (fp32 inputs), 5e-3 (fp16 inputs) or 1e-2
 (bf16 inputs): the probabilities, V_A and dV_A that feed the MFMA products are rounded to the element
 type, each with a relative error of up to one unit roundoff (2^-9 for bf16, 2^-11 for fp16), and a
@@ -159,15 +158,53 @@ def test_backward_module_mode(aa, oracle, grid, agrid, d, dtype):
     _run_case(aa, oracle, _wl("module", dtype, grid, agrid, d), module=True)
 
 
-@pytest.mark.parametrize("agrid,dtype,batch,heads", [((6, 5), "f32", 2, 1), ((6, 5), "bf16", 2, 1),
-                                                     ((16, 16), "f16", 1, 2)])
-def test_backward_module_mode_many_tokens(aa, oracle, agrid, dtype, batch, heads):
-    """Module terms on a 132 x 128 token grid: an agent's row of score gradients takes more than 64 KB of LDS in
-    the kernel that sums the bias components (opt-in path), with a batch to add up first (and, for fp32, rows that
-    start off the 16-byte grid); with 256 agents a head's broadcast score gradients exceed the size up to which
-    that kernel gathers them, so its three components take the one-pass-per-component kernels."""
-    _run_case(aa, oracle, _wl("many_tokens", dtype, (132, 128), agrid, 16, batch=batch, heads=heads, index=33),
+@pytest.mark.parametrize("agrid,dtype,batch,heads,d", [((6, 5), "f32", 2, 1, 16), ((6, 5), "bf16", 2, 1, 16),
+                                                       ((16, 16), "f16", 1, 2, 16), ((6, 5), "bf16", 2, 1, 136),
+                                                       ((6, 5), "f32", 2, 1, 18), ((16, 16), "f16", 1, 1, 136)])
+def test_backward_module_mode_many_tokens(aa, oracle, agrid, dtype, batch, heads, d):
+    """Module terms on a 132 x 128 token grid.  16 channels: the recomputing kernels, token ranges of many columns.
+    Wider than 128, or rows off the 16-byte grid: the kernels that keep the matrices in memory, where an agent's row of
+    score gradients takes more than 64 KB of LDS in the kernel that sums the bias components (opt-in path), with a batch
+    to add up first; with 256 agents a head's broadcast score gradients exceed the size up to which that kernel gathers
+    them, so its three components take the one-pass-per-component kernels."""
+    _run_case(aa, oracle, _wl("many_tokens", dtype, (132, 128), agrid, d, batch=batch, heads=heads, index=33),
               module=True, blk=(4, 3))
+
+
+@pytest.mark.parametrize("grid,agrid,d,dtype,module", [((12, 10), (3, 5), 136, "bf16", True), ((7, 9), (3, 3), 160, "f16", True),
+                                                       ((20, 21), (9, 10), 136, "f16", True), ((9, 70), (3, 9), 256, "bf16", False),
+                                                       ((1, 1), (1, 1), 136, "f16", False)])
+def test_backward_16_bit_wider_than_128(aa, oracle, grid, agrid, d, dtype, module):
+    """16-bit heads that the recomputing kernels do not serve: matrix products with both attention matrices in memory,
+    rows of up to and past 64 entries, with and without module terms."""
+    _run_case(aa, oracle, _wl("wide", dtype, grid, agrid, d, index=35), module=module)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+def test_backward_of_unaligned_tensors(aa, dtype):
+    """Tensors one element off the 16-byte grid take the fp32 products with the matrices in memory (its workspace and the
+    convolution's sums at the end of it): the gradients of the aligned call, which the tests above hold against the oracle,
+    to the roundings of the two paths (16 bits: the bars of this file)."""
+    import torch
+    wl = _wl("unaligned", dtype, (13, 11), (4, 3), 24, index=36)
+    shape = (wl.batch, wl.heads, wl.N, wl.d)
+    dense = [util.to_device(inputs.make_tensor((wl.units, wl.N, wl.d), stream=960 + i, dtype=dtype), dtype, shape) for i in range(4)]
+    A = util.to_device(inputs.make_tensor((wl.units, wl.n, wl.d), stream=964, dtype=dtype), dtype, (wl.batch, wl.heads, wl.n, wl.d))
+    params = util.params_to_device(inputs.make_module_params(wl.heads, wl.n, wl.d, wl.grid, blk=(3, 2), index=wl.index))
+
+    def off(t):
+        v = torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")[1:].reshape(t.shape)
+        v.copy_(t)
+        assert v.data_ptr() % 16
+        return v
+
+    ref = aa.agent_attn_bwd(*dense, A, grid=wl.grid, params=params, v_residual_k=0.05)
+    got = aa.agent_attn_bwd(*(off(t) for t in dense), A, grid=wl.grid, params=params, v_residual_k=0.05)
+    assert set(got) == set(ref)
+    for k in ref:
+        a, b = got[k].double(), ref[k].double()
+        assert bool(torch.isfinite(a).all()), k
+        assert float((a - b).norm() / b.norm()) <= {"f32": 5e-6, "f16": 5e-3, "bf16": 1e-2}[dtype], k
 
 
 @pytest.mark.parametrize("grid,agrid,d,dtype,blk,batch", [
@@ -453,12 +490,13 @@ def test_backward_is_deterministic_and_ignores_workspace(aa, grid, agrid, d):
         assert torch.equal(a[k], b[k])
 
 
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_backward_windows_in_descriptor(aa, dtype):
+@pytest.mark.parametrize("dtype,d", [("f32", 24), ("bf16", 32), ("f32", 21), ("bf16", 20), ("f16", 136)])
+def test_backward_windows_in_descriptor(aa, dtype, d):
     """Windows named in the descriptor (Sec. 5.5): the gradients of the image tensors are, bit for bit, those
-    of the same windows handed over as a batch (a case the tests above hold against the oracle)."""
+    of the same windows handed over as a batch (a case the tests above hold against the oracle).  The first two widths are
+    read in place, the others staged through window-major copies."""
     import torch
-    batch, heads, image, window, agrid, d = 2, 2, (12, 18), (6, 6), (3, 3), 24 if dtype == "f32" else 32
+    batch, heads, image, window, agrid = 2, 2, (12, 18), (6, 6), (3, 3)
     (Y, X), (wh, ww) = image, window
     nwin = (Y // wh) * (X // ww)
     params = util.params_to_device(inputs.make_module_params(heads, 9, d, window, blk=(3, 2), index=21))
@@ -504,14 +542,14 @@ def test_backward_random_problems(aa, oracle, seed):
               blk=(int(rng.integers(1, 6)), int(rng.integers(1, 6))), kw=kw)
 
 
-@pytest.mark.parametrize("module", [False, True])
-def test_backward_replayed_from_a_graph(aa, module):
+@pytest.mark.parametrize("module,d", [(False, 32), (True, 32), (True, 136)])
+def test_backward_replayed_from_a_graph(aa, module, d):
     """The backward pass allocates nothing and clears nothing with memsets: captured once, every replay gives the
-    bits of the eager call on the inputs of the moment (pure: the recomputing kernels; module terms: the kernels
-    that keep the matrices in memory, with their parameter gradients)."""
+    bits of the eager call on the inputs of the moment (the recomputing kernels, pure and with module terms; wider than
+    128 the kernels that keep the matrices in memory; with their parameter gradients)."""
     import ctypes
     import torch
-    wl = _wl("graph", "bf16", (24, 20), (6, 5), 32, batch=2, heads=2, index=41)
+    wl = _wl("graph", "bf16", (24, 20), (6, 5), d, batch=2, heads=2, index=41)
     shape = (wl.batch, wl.heads, wl.N, wl.d)
     t = [util.to_device(inputs.make_tensor((wl.units, wl.N, wl.d), stream=900 + i, dtype=wl.dtype), wl.dtype, shape)
          for i in range(4)]
@@ -543,14 +581,14 @@ def test_backward_replayed_from_a_graph(aa, module):
             assert torch.equal(got[k], eager[k]), "replay %d: %s differs from the eager call" % (rep, k)
 
 
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("dtype,d", [("f32", 20), ("bf16", 32), ("f32", 21), ("f16", 20), ("bf16", 136)])
 @pytest.mark.parametrize("layout", ["token_major", "fused_qkv"])
-def test_backward_strided_layouts(aa, dtype, layout):
-    """Token-major [B,N,H,d] tensors and the q / k / v slices of a fused projection [B,N,3,H,d]: the
-    backward pass stages them through dense copies, so every gradient has the bits of the dense call
-    and lands with the strides of its tensor."""
+def test_backward_strided_layouts(aa, dtype, d, layout):
+    """Token-major [B,N,H,d] tensors and the q / k / v slices of a fused projection [B,N,3,H,d]: read in place (the first
+    two widths) or staged through dense copies, every gradient has the bits of the dense call and lands with the strides
+    of its tensor."""
     import torch
-    wl = _wl("strided", dtype, (9, 8), (3, 4), 32 if dtype == "bf16" else 20, batch=2, heads=3, index=71)
+    wl = _wl("strided", dtype, (9, 8), (3, 4), d, batch=2, heads=3, index=71)
     t = inputs.make_qkv(wl)
     dO = inputs.make_tensor((wl.units, wl.N, wl.d), stream=wl.index * 16 + 12, dtype=wl.dtype)
     shape = (wl.batch, wl.heads, wl.N, wl.d)
