@@ -127,7 +127,7 @@ def _run_case(aa, oracle, wl, *, given=False, module=False, blk=(3, 2), kw=None,
                              floor=float(np.sqrt(np.abs(q).sum())))
         _check_param(got["ddwc_w"], ref["ddwc_w"], wl.dtype, wl.name + " ddwc_w")
         _check_param(got["ddwc_b"], ref["ddwc_b"], wl.dtype, wl.name + " ddwc_b")
-    if mask and wl.dtype == "f32":      # the forward pass on the same kernels
+    if mask and (wl.dtype == "f32" or mask[2] >= (-1e4 if mask[0] == "b1_blk" else -1e9)):      # 16 bits: finite masks
         out = aa.agent_attn_fwd(dv["Q"], dv["K"], dv["V"], Ad, grid=wl.grid, params=pd, **kw)
         _check(out, oracle.agent_attn_fwd(f64["Q"], f64["K"], f64["V"], A=inputs.to_float64(A_st, wl.dtype), **okw), wl.dtype,
                wl.name + " out")
@@ -261,18 +261,19 @@ ALL = slice(None)
 MASKED = {"b1_col": [(ALL, ALL, slice(0, 16)), (ALL, ALL, slice(17, None)), (ALL, 3, slice(2, 19))],
           "b1_row": [(ALL, ALL, slice(0, 3)), (ALL, ALL, slice(12, None)), (ALL, 3, slice(0, 15))],
           "b1_blk": [(ALL, ALL, 0), (ALL, ALL, ALL, 1), (ALL, 3, slice(0, 2))],
-          "b2_col": [(ALL, ALL, 3), (ALL, slice(0, 3), slice(1, None))],
-          "b2_row": [(ALL, ALL, slice(2, 5)), (ALL, slice(12, None), slice(0, 8))],
-          "b2_blk": [(ALL, ALL, ALL, 3), (ALL, 0, ALL, slice(1, None))]}
+          "b2_col": [(ALL, ALL, 3), (ALL, slice(0, 3), slice(1, None)), (ALL, slice(0, 3), slice(0, -1))],
+          "b2_row": [(ALL, ALL, slice(2, 5)), (ALL, slice(12, None), slice(0, 8)), (ALL, slice(12, None), slice(0, -1))],
+          "b2_blk": [(ALL, ALL, ALL, 3), (ALL, 0, ALL, slice(1, None)), (ALL, 0, ALL, slice(0, -1))]}
 
 
-@pytest.mark.parametrize("n,d", [(9, 32), (70, 64)])
+@pytest.mark.parametrize("n,d", [(9, 32), (70, 64), (130, 32)])
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 @pytest.mark.parametrize("key", sorted(MASKED))
 def test_masks_in_the_agent_bias(aa, oracle, key, dtype, n, d):
     """Components that mask whole rows, columns, cells or agents, in the first tiles of a walk and in later ones, with
-    something left to attend to: every gradient and the fp32 forward at the usual bars (16 x 20 tokens, 1280 in all: the
-    fp32 forward takes its streaming kernels)."""
+    something left to attend to: the forward pass and every gradient at the usual bars (16 x 20 tokens, 1280 in all: the
+    fp32 forward takes its streaming kernels; the 16-bit forward its small kernels, and past 64 agents its large ones with
+    the block component in matrix and in table form)."""
     for place in MASKED[key]:
         for value in (-1e4, -1e9, float(np.finfo(np.float32).min), -np.inf):
             wl = _wl("mask %s %s %g" % (key, place, value), dtype, (16, 20), (1, n), d, index=85)
