@@ -316,6 +316,12 @@ __global__ __launch_bounds__(64 * kWaves) void broadcast_generic_kernel(
 // Agent bias evaluated once for all (agent, token) pairs of every head (Appendix B), in the padded
 // layouts described at BiasArgs.  thread = one element.
 // ---------------------------------------------------------------------------
+// Entries of the tables are finite: a mask of the type's lowest value or of minus infinity is this, so that differences of
+// two masked entries are zero and a row of them has a maximum.  Two of them are above what the MFMA kernels take for a
+// maximum yet to be found (-1e30).  NaN stays NaN.
+constexpr float kTableFloor = -2.5e29f;
+__device__ __forceinline__ float floored(float v) { return v < kTableFloor ? kTableFloor : v; }
+
 template <int KIND>
 __device__ __forceinline__ void bias_dense_element(const BiasArgs& b, float* __restrict__ out, int heads, int n, int N,
                                                    int gh, int gw, size_t i) {
@@ -342,12 +348,12 @@ __device__ __forceinline__ void bias_dense_element(const BiasArgs& b, float* __r
       if (hb.col) hb.col += (size_t)hd * n * gw;
       if (hb.row) hb.row += (size_t)hd * n * gh;
       if (hb.blk) hb.blk += (size_t)hd * n * hb.h0 * hb.w0;
-      v = kLog2e * bias1_at(hb, a, t / gw, t % gw, gh, gw);
+      v = floored(kLog2e * bias1_at(hb, a, t / gw, t % gw, gh, gw));
     } else {
       if (hb.col) hb.col += (size_t)hd * gw * n;
       if (hb.row) hb.row += (size_t)hd * gh * n;
       if (hb.blk) hb.blk += (size_t)hd * hb.h0 * hb.w0 * n;
-      v = kLog2e * bias2_at(hb, a, t / gw, t % gw, gh, gw, n);
+      v = floored(kLog2e * bias2_at(hb, a, t / gw, t % gw, gh, gw, n));
     }
   }
   out[i] = v;
@@ -410,7 +416,7 @@ __global__ __launch_bounds__(256) void bias_half_kernel(BiasArgs b1, float* __re
           int x0, x1;
           float fx;
           bilinear_coord((int)(4 * xq) + j, gw, w0, x0, x1, fx);
-          const float v0 = p[x0], v1 = p[x1];
+          const float v0 = floored(p[x0]), v1 = floored(p[x1]);
           out[j] += v0 + (v1 - v0) * fx;
         }
       }
@@ -433,7 +439,7 @@ __global__ __launch_bounds__(256) void bias_half_kernel(BiasArgs b1, float* __re
       if (a < n) {
         if (col) out[j] = col[a];
         if (p) {
-          const float v0 = p[(size_t)x0 * n + a], v1 = p[(size_t)x1 * n + a];
+          const float v0 = floored(p[(size_t)x0 * n + a]), v1 = floored(p[(size_t)x1 * n + a]);
           out[j] += v0 + (v1 - v0) * fx;
         }
       }
@@ -461,7 +467,8 @@ __global__ __launch_bounds__(256) void bias_half_kernel(BiasArgs b1, float* __re
     dst = rows2;
   }
   typedef float f32x4 __attribute__((ext_vector_type(4)));
-  if (live) *(f32x4*)(dst + quad * 4) = f32x4{out[0] * kLog2e, out[1] * kLog2e, out[2] * kLog2e, out[3] * kLog2e};
+  if (live)
+    *(f32x4*)(dst + quad * 4) = f32x4{floored(out[0] * kLog2e), floored(out[1] * kLog2e), floored(out[2] * kLog2e), floored(out[3] * kLog2e)};
 }
 
 size_t bias_half_floats(int heads, int n, int gw, int he) { return (size_t)heads * round_up64(n) * he * gw; }
@@ -528,7 +535,8 @@ __global__ __launch_bounds__(256) void bias_matrix_kernel(uint16_t* __restrict__
       const int k = 8 * (int)piece + e;
       float v = 0.0f;
       if ((int)a < n && k < h0 * w0) v = b1.blk[((size_t)hd * n + a) * h0 * w0 + k];
-      out[e] = f16_bits(v * kLog2e);
+      v *= kLog2e;      // within fp16: a mask past its range would meet the zero weights of other tokens as an infinity
+      out[e] = f16_bits(v < -65504.0f ? -65504.0f : v > 65504.0f ? 65504.0f : v);
     }
   }
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
