@@ -166,7 +166,7 @@ FusedPlan fused_plan(const Problem& p, bool forward = false) {
     f.lse2 = o, o += uN;
     if (f.weights[1]) f.w1 = o, o += un;
     if (f.weights[0]) f.w2 = o, o += uN;
-    f.large = o, o += up64(2 * u);
+    if (!f32 && (f.bias[0] || f.bias[1])) f.large = o, o += up64(2 * u);
     f.D2 = o, o += uN;
     f.dAf = o, o += u * nd;
   }
@@ -317,8 +317,8 @@ hipError_t run_fused(const Problem& p, const FusedPlan& f, const void* Q, const 
 
 }  // namespace
 
-// places within a unit in 32 bits (see UnitPlace::fits)
-static bool short_units(const Problem& p) { return p.b1.any() || p.b2.any() || p.dwc_w; }
+// places within a unit in 32 bits (see UnitPlace::fits); fp32 units past them have another path
+static bool short_units(const Problem& p) { return p.dtype == 0 || p.b1.any() || p.b2.any() || p.dwc_w; }
 
 bool backward_fused_supported(const Problem& p) {
   return p.d % (p.dtype == 0 ? 4 : 8) == 0 && p.d <= 128 && p.units <= 65535 &&

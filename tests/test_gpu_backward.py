@@ -303,7 +303,7 @@ def _masked_rows(aa, oracle, key, dtype, n, d, value):
     return {k: util.to_host64(got[k]).reshape(ref[k].shape) for k in ("dQ", "dK", "dV", "dA")}, ref, f64["dO"]
 
 
-@pytest.mark.parametrize("n,d", [(9, 32), (70, 64), (40, 128)])
+@pytest.mark.parametrize("n,d", [(9, 32), (70, 24), (70, 64), (40, 128)])
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 @pytest.mark.parametrize("key", sorted(ROWS))
 def test_backward_softmax_rows_masked_throughout(aa, oracle, key, dtype, n, d):
@@ -474,22 +474,33 @@ def test_backward_scores_far_below_zero(aa, oracle, n, d, units, dwc, dtype):
         _check(got[k][..., first:], ref[k][..., first:], dtype, k)
 
 
-@pytest.mark.parametrize("grid,agrid,d", [((12, 12), (4, 4), 32), ((40, 40), (12, 12), 64)])
-def test_backward_is_deterministic_and_ignores_workspace(aa, grid, agrid, d):
+@pytest.mark.parametrize("grid,agrid,d,masked", [((12, 12), (4, 4), 32, None), ((40, 40), (12, 12), 64, None),
+                                                  ((21, 18), (5, 4), 32, False), ((21, 18), (5, 4), 32, True)])
+def test_backward_is_deterministic_and_ignores_workspace(aa, grid, agrid, d, masked):
+    """masked: None: no module terms; True: a token and an agent masked throughout in one of the heads, so that the blocks of
+    its units are told by their flags to take the form for large references"""
     import torch
     wl = _wl("det", "bf16", grid, agrid, d)
+    params = None
+    if masked is not None:
+        params = inputs.make_module_params(wl.heads, wl.n, d, grid, blk=(3, 2), index=wl.index)
+        if masked:
+            params["b1_row"][1, 2] = params["b2_row"][1, 3] = -1e9
+        params = util.params_to_device(params)
+    kw = dict(grid=wl.grid, agent_grid=wl.agent_grid, params=params)
     t = inputs.make_qkv(wl)
     shape = (wl.batch, wl.heads, wl.N, wl.d)
     dv = {k: util.to_device(v, wl.dtype, shape) for k, v in t.items()}
     dO = util.to_device(inputs.make_tensor((wl.units, wl.N, wl.d), stream=300, dtype=wl.dtype), wl.dtype, shape)
-    a = aa.agent_attn_bwd(dv["Q"], dv["K"], dv["V"], dO, grid=wl.grid, agent_grid=wl.agent_grid)
+    a = aa.agent_attn_bwd(dv["Q"], dv["K"], dv["V"], dO, **kw)
     desc = aa.make_desc(wl.batch, wl.heads, wl.N, wl.n, wl.d, 2, wl.grid, wl.agent_grid)
     import ctypes
-    need = int(aa.lib().agent_attn_bwd_workspace_bytes(ctypes.byref(desc), None))
-    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
-    b = aa.agent_attn_bwd(dv["Q"], dv["K"], dv["V"], dO, grid=wl.grid, agent_grid=wl.agent_grid, workspace=ws)
-    for k in ("dQ", "dK", "dV"):
-        assert torch.equal(a[k], b[k])
+    need = int(aa.lib().agent_attn_bwd_workspace_bytes(ctypes.byref(desc), aa._pp(aa.make_params(params))))
+    for fill in (0xFF, 0x41):
+        ws = torch.full((need,), fill, dtype=torch.uint8, device="cuda")
+        b = aa.agent_attn_bwd(dv["Q"], dv["K"], dv["V"], dO, workspace=ws, **kw)
+        for k in a:
+            assert torch.equal(a[k], b[k]), k
 
 
 @pytest.mark.parametrize("dtype,d", [("f32", 24), ("bf16", 32), ("f32", 21), ("bf16", 20), ("f16", 136)])
