@@ -1,0 +1,67 @@
+"""The large-agent broadcast that takes its tokens in columns (16 columns x 16 image rows a block, cell rows of the bias
+tables beside the agents): edges of blocks and row pairs, the numbers of cell rows a stage holds and the first one past them,
+components that are absent, masks.  Reference: the fp64 oracle, with the forward's bars."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from paper_2312_08874_amd import inputs
+from . import util
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def aa():
+    from paper_2312_08874_amd import binding
+    binding.lib()
+    return binding
+
+
+# grid, agent grid, block grid, components left out: rows 16 k + 1, + 15, a lone last row of a pair; columns 16 k + 4, + 12;
+# one cell row (no block component), 3, 4, 5, 6 and (12 of 16 rows: 14) too many for a stage
+CASES = [
+    ((17, 20), (9, 8), (7, 7), ()),
+    ((64, 16), (8, 9), (7, 7), ()),
+    ((47, 36), (13, 10), (7, 5), ("b2_row",)),
+    ((33, 28), (10, 10), (2, 3), ("b2_col",)),
+    ((31, 12), (11, 6), (3, 2), ("b2_blk",)),
+    ((16, 32), (8, 16), (4, 4), ("b1_col", "b1_row", "b1_blk")),
+    ((16, 24), (8, 12), (12, 7), ()),
+    ((15, 64), (5, 14), (3, 7), ("dwc_w", "dwc_b")),
+]
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f16", 40), ("bf16", 24), ("f16", 128)])
+@pytest.mark.parametrize("grid,agrid,blk,absent", CASES)
+def test_broadcast_in_columns(aa, oracle, grid, agrid, blk, absent, dtype, d):
+    wl = dataclasses.replace(inputs.WORKLOADS["tiny"], batch=2, heads=2, grid=grid, agent_grid=agrid, d=d, dtype=dtype, index=14)
+    t = inputs.make_qkv(wl)
+    params = {k: v for k, v in inputs.make_module_params(2, wl.n, d, grid, blk=blk, index=14).items() if k not in absent}
+    dev = {k: util.to_device(v, dtype, (2, 2, wl.N, d)) for k, v in t.items()}
+    O = aa.agent_attn_fwd(dev["Q"], dev["K"], dev["V"], grid=grid, agent_grid=agrid, params=util.params_to_device(params),
+                          v_residual_k=0.25)
+    ref = util.oracle_forward_units(oracle, wl, t, list(range(4)), params=params, v_residual_k=0.25)
+    util.assert_parity(util.to_host64(O).reshape(ref.shape), ref, dtype, "broadcast in columns",
+                       max_abs=1e-2 * max(1.0, float(np.abs(ref).max())))
+
+
+@pytest.mark.parametrize("mask", [-1e4, -1e9, float(np.finfo(np.float32).min), -np.inf])
+@pytest.mark.parametrize("key,where", [("b2_row", (slice(None), slice(0, 5), slice(0, 70))), ("b2_col", (slice(None), slice(2, 9), slice(1, None))),
+                                       ("b2_blk", (slice(None), slice(0, 2), slice(None), slice(0, 64)))])
+def test_broadcast_in_columns_masks(aa, oracle, key, where, mask):
+    """Agents masked for some tokens, the whole first chunk among them.  A masked weight is zero at any of these values, so
+    the oracle's value at -1e4 is the reference for all."""
+    grid, agrid, d, dtype = (35, 24), (9, 9), 64, "f16"
+    wl = dataclasses.replace(inputs.WORKLOADS["tiny"], batch=1, heads=2, grid=grid, agent_grid=agrid, d=d, dtype=dtype, index=14)
+    t = inputs.make_qkv(wl)
+    params = inputs.make_module_params(2, wl.n, d, grid, blk=(7, 7), index=14)
+    ref_params = {k: v.copy() for k, v in params.items()}
+    params[key][where] = mask
+    ref_params[key][where] = -1e4
+    dev = {k: util.to_device(v, dtype, (1, 2, wl.N, d)) for k, v in t.items()}
+    O = aa.agent_attn_fwd(dev["Q"], dev["K"], dev["V"], grid=grid, agent_grid=agrid, params=util.params_to_device(params))
+    ref = util.oracle_forward_units(oracle, wl, t, [0, 1], params=ref_params)
+    util.assert_parity(util.to_host64(O).reshape(ref.shape), ref, dtype, "masked broadcast in columns",
+                       max_abs=1e-2 * max(1.0, float(np.abs(ref).max())))
