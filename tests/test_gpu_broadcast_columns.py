@@ -1,4 +1,4 @@
-"""The large-agent broadcast that takes its tokens in columns (16 columns x 16 image rows a block, cell rows of the bias
+"""The broadcasts that take their tokens in columns.  Many agents (16 columns x 16 image rows a block, cell rows of the bias
 tables beside the agents): edges of blocks and row pairs, the numbers of cell rows a stage holds and the first one past them,
 components that are absent, masks.  Reference: the fp64 oracle, with the forward's bars."""
 import dataclasses
@@ -64,4 +64,26 @@ def test_broadcast_in_columns_masks(aa, oracle, key, where, mask):
     O = aa.agent_attn_fwd(dev["Q"], dev["K"], dev["V"], grid=grid, agent_grid=agrid, params=util.params_to_device(params))
     ref = util.oracle_forward_units(oracle, wl, t, [0, 1], params=ref_params)
     util.assert_parity(util.to_host64(O).reshape(ref.shape), ref, dtype, "masked broadcast in columns",
+                       max_abs=1e-2 * max(1.0, float(np.abs(ref).max())))
+
+
+# the small-agent broadcast with a convolution: widths on both sides of whole sixteens and of the rule, a last segment of one
+# image row, one image row in all, 1 .. 4 agent tiles
+SMALL = [((31, 44), (7, 7)), ((33, 33), (4, 4)), ((16, 64), (3, 11)), ((65, 15), (8, 8)), ((22, 50), (5, 6)), ((1, 700), (1, 40)), ((64, 17), (7, 7))]
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 32), ("f16", 64)])
+@pytest.mark.parametrize("absent", [(), ("b1_col", "b1_row", "b1_blk", "b2_col", "b2_row", "b2_blk"), ("dwc_b", "b2_row")])
+@pytest.mark.parametrize("grid,agrid", SMALL)
+def test_small_broadcast_in_columns(aa, oracle, grid, agrid, absent, dtype, d):
+    wl = dataclasses.replace(inputs.WORKLOADS["tiny"], batch=2, heads=2, grid=grid, agent_grid=agrid, d=d, dtype=dtype, index=15)
+    t = inputs.make_qkv(wl)
+    params = {k: v for k, v in inputs.make_module_params(2, wl.n, d, grid, blk=(7, 7), index=15).items() if k not in absent}
+    # token-major: the rows of one unit are not neighbours
+    dev = {k: util.to_device(v, dtype, (2, 2, wl.N, d)).permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3) for k, v in t.items()}
+    vk = 0.25 if absent else 0.0
+    O = aa.agent_attn_fwd(dev["Q"], dev["K"], dev["V"], grid=grid, agent_grid=agrid, params=util.params_to_device(params),
+                          v_residual_k=vk)
+    ref = util.oracle_forward_units(oracle, wl, t, list(range(4)), params=params, v_residual_k=vk)
+    util.assert_parity(util.to_host64(O).reshape(ref.shape), ref, dtype, "small broadcast in columns",
                        max_abs=1e-2 * max(1.0, float(np.abs(ref).max())))
