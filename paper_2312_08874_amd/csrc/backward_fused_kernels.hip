@@ -212,12 +212,15 @@ struct Pass {
   }
   hipError_t token(int prob, TokenArgs& a) {
     const int k = prob == kAgg ? 1 : 0;
-    const size_t lds = (size_t)2 * f.ch_rows * (f.DP + El<E>::kRowPad) * sizeof(T) + (size_t)3 * f.ch_rows * sizeof(float);
+    // The statistics with a bias fit four blocks a CU if LDS allows: chunks of 64 agents (8 units of 16384 tokens x 1024 agents:
+    // 110 -> 101 us; the other two, two blocks a CU for their registers, 148 -> 164 and 120 -> 136).
+    a.ch_rows = f.bias[k] && prob == kBcStat ? std::min(f.ch_rows, 64) : f.ch_rows;
+    const size_t lds = (size_t)2 * a.ch_rows * (f.DP + El<E>::kRowPad) * sizeof(T) + (size_t)3 * a.ch_rows * sizeof(float);
     if (f.bias[k]) {
       a.bt = bt[k];
       const int items = ((p.gw + 15) / 16) * ((p.gh + f.token_cols - 1) / f.token_cols);
       return launch_token<E, true>(prob, f.DP, f.token_cols, a, dim3((items + 3) / 4, p.units),
-                                   lds + (size_t)4 * f.token_cols * f.ch_rows * sizeof(float), st);
+                                   lds + (size_t)4 * f.token_cols * a.ch_rows * sizeof(float), st);
     }
     const int cols = f.wide && prob != kAgg ? 4 : f.token_cols;
     return launch_token<E, false>(prob, f.DP, cols, a, dim3((p.N + 64 * cols - 1) / (64 * cols), p.units), lds, st);
