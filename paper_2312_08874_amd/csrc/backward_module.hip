@@ -8,18 +8,20 @@ namespace aa {
 namespace {
 
 // ---------------------------------------------------------------------------
-// Tables of both bias kinds (BiasTables) in one launch.  A block makes a tile of 64 agents x 16 columns of one cell row
-// (T) or x 16 image rows (R) in LDS: the components are read with the lanes along their contiguous axis (columns or
+// Tables of both bias kinds (BiasTables) in one launch.  A block makes tiles of 64 agents x 16 columns of `run` cell rows
+// (T; the column component and the interpolation along x are the same for all of them) or x 16 image rows (R) in LDS: the components are read with the lanes along their contiguous axis (columns or
 // rows for B1, agents for B2) and both orders of T are written in pieces of 256 bytes and more.  The last blocks of a
 // kind: the image rows' interpolation along y.  Bound by the tables' bytes; with the lanes always along the agents
 // B1's components were read, and ta written, a few bytes per line (8 heads, 1024 agents, 128 x 128 tokens: 126 -> 44 us
-// for the 117 MB of both kinds; 3 heads, 49 agents, 14 x 14 tokens, where it is the launches: 14 -> 4 us).
+// for the 117 MB of both kinds; 3 heads, 49 agents, 14 x 14 tokens, where it is the launches: 14 -> 4 us).  run is as large
+// as leaves eight blocks a CU: with one cell row a block the divisions and coordinates were most of the arithmetic (the
+// first shape 47 -> 34 us).
 // ---------------------------------------------------------------------------
 struct TableKind {
   BiasArgs b;
   float *ta, *tx, *rows;
   YInfo* yi;
-  int kind, cells;
+  int kind, cells, run;      // run: cell rows per block
   unsigned tblocks, rblocks, blocks;
 };
 
@@ -27,7 +29,8 @@ __device__ __forceinline__ float floored(float v) { return v < kBiasFloor ? kBia
 
 template <int KIND>
 __device__ __forceinline__ void bias_table_block(const TableKind& k, unsigned block, int n, int gh, int gw, int ld,
-                                                 float (&tile)[16][68]) {
+                                                 float (&tiles)[2][16][68]) {
+  float (&tile)[16][68] = tiles[0];
   const BiasArgs& b = k.b;
   const int tid = threadIdx.x, ats = ld / 64, xts = (gw + 15) / 16, yts = (gh + 15) / 16;
   // entry (i, a) of the tile this thread makes in step j: lanes along the components' contiguous axis
@@ -36,42 +39,61 @@ __device__ __forceinline__ void bias_table_block(const TableKind& k, unsigned bl
     al = KIND == 1 ? (tid >> 4) + 16 * j : tid & 63;
   };
   if (block < k.tblocks) {
-    const int at = block % ats, xt = block / ats % xts, cell = block / ats / xts % k.cells, hd = block / ats / xts / k.cells;
+    const unsigned runs = (unsigned)((k.cells + k.run - 1) / k.run);
+    const int at = block % ats, xt = block / ats % xts, c0 = (int)(block / ats / xts % runs) * k.run, hd = block / ats / xts / runs;
+    const int c1 = min(c0 + k.run, k.cells);
+    float col[4], fx[4], v0[4], v1[4];
+    const float *q0[4], *q1[4];      // the block component's entries on both sides, of the cell row in hand
+    bool blk[4];
+    const size_t cell_step = KIND == 1 ? (size_t)b.w0 : (size_t)b.w0 * n;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       int i, al;
       place(j, i, al);
       const int x = 16 * xt + i, a = 64 * at + al;
-      float v = 0.0f;
-      if (x >= gw) {
-        v = kMaskedScore;      // a column past the image weighs nothing
-      } else if (a < n) {
-        if (b.col) v = KIND == 1 ? b.col[((size_t)hd * n + a) * gw + x] : b.col[((size_t)hd * gw + x) * n + a];
-        if (b.blk) {
-          int x0, x1;
-          float fx;
-          bilinear_coord(x, gw, b.w0, x0, x1, fx);
-          const size_t step = KIND == 1 ? 1 : n;
-          const float* q = KIND == 1 ? b.blk + (((size_t)hd * n + a) * b.h0 + cell) * b.w0
-                                     : b.blk + ((size_t)hd * b.h0 + cell) * b.w0 * n + a;
-          const float v0 = floored(q[x0 * step]), v1 = floored(q[x1 * step]);
-          v += v0 + (v1 - v0) * fx;
-        }
-        v = floored(v * kLog2e);
+      col[j] = x >= gw ? kMaskedScore : 0.0f;      // a column past the image weighs nothing
+      blk[j] = b.blk && x < gw && a < n;
+      if (x < gw && a < n && b.col) col[j] = KIND == 1 ? b.col[((size_t)hd * n + a) * gw + x] : b.col[((size_t)hd * gw + x) * n + a];
+      v0[j] = v1[j] = 0.0f;
+      if (blk[j]) {
+        int x0, x1;
+        bilinear_coord(x, gw, b.w0, x0, x1, fx[j]);
+        const size_t step = KIND == 1 ? 1 : n;
+        const float* q = KIND == 1 ? b.blk + (((size_t)hd * n + a) * b.h0 + c0) * b.w0 : b.blk + ((size_t)hd * b.h0 + c0) * b.w0 * n + a;
+        q0[j] = q + x0 * step, q1[j] = q + x1 * step;
+        v0[j] = *q0[j], v1[j] = *q1[j];
       }
-      tile[i][al] = v;
     }
-    __syncthreads();
     const int wp = 16 * xts;
-    const size_t base = ((size_t)hd * k.cells + cell) * ld * wp;
-    {
-      const int i = tid & 15, a4 = tid >> 4;
-      *reinterpret_cast<f32x4*>(k.ta + base + ((size_t)(16 * at + a4) * wp + 16 * xt + i) * 4) =
-          *reinterpret_cast<const f32x4*>(&tile[i][4 * a4]);
+    for (int cell = c0; cell < c1; ++cell) {
+      float (&t)[16][68] = tiles[(cell - c0) & 1];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        int i, al;
+        place(j, i, al);
+        float v = col[j];
+        if (blk[j]) {
+          const float f0 = floored(v0[j]), f1 = floored(v1[j]);
+          v += f0 + (f1 - f0) * fx[j];
+        }
+        t[i][al] = 16 * xt + i < gw ? floored(v * kLog2e) : v;
+      }
+      if (cell + 1 < c1) {      // the next cell row's entries are under way while this one's tile goes out
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (blk[j]) q0[j] += cell_step, q1[j] += cell_step, v0[j] = *q0[j], v1[j] = *q1[j];
+      }
+      __syncthreads();      // two tiles in turn: the one written next was read before this barrier
+      const size_t base = ((size_t)hd * k.cells + cell) * ld * wp;
+      {
+        const int i = tid & 15, a4 = tid >> 4;
+        *reinterpret_cast<f32x4*>(k.ta + base + ((size_t)(16 * at + a4) * wp + 16 * xt + i) * 4) =
+            *reinterpret_cast<const f32x4*>(&t[i][4 * a4]);
+      }
+      const int x4 = tid >> 6, al = tid & 63;
+      *reinterpret_cast<f32x4*>(k.tx + base + ((size_t)(4 * xt + x4) * ld + 64 * at + al) * 4) =
+          f32x4{t[4 * x4][al], t[4 * x4 + 1][al], t[4 * x4 + 2][al], t[4 * x4 + 3][al]};
     }
-    const int x4 = tid >> 6, al = tid & 63;
-    *reinterpret_cast<f32x4*>(k.tx + base + ((size_t)(4 * xt + x4) * ld + 64 * at + al) * 4) =
-        f32x4{tile[4 * x4][al], tile[4 * x4 + 1][al], tile[4 * x4 + 2][al], tile[4 * x4 + 3][al]};
   } else if (block < k.tblocks + k.rblocks) {
     block -= k.tblocks;
     const int at = block % ats, yt = block / ats % yts, hd = block / ats / yts;
@@ -109,7 +131,7 @@ __device__ __forceinline__ void bias_table_block(const TableKind& k, unsigned bl
 
 __global__ __launch_bounds__(256) void bias_tables_kernel(TableKind first, TableKind second, int n, int gh, int gw, int ld,
                                                           int* flags, int n_flags) {
-  __shared__ __align__(16) float tile[16][68];
+  __shared__ __align__(16) float tile[2][16][68];
   for (int i = blockIdx.x * 256 + threadIdx.x; i < n_flags; i += gridDim.x * 256) flags[i] = 0;
   const bool one = blockIdx.x < first.blocks;
   const unsigned block = one ? blockIdx.x : blockIdx.x - first.blocks;
@@ -420,7 +442,9 @@ hipError_t launch_backward_bias_tables(const Problem& p, const BiasTables (&t)[2
     k.ta = const_cast<float*>(t[i].ta), k.tx = const_cast<float*>(t[i].tx), k.rows = const_cast<float*>(t[i].rows);
     k.yi = const_cast<YInfo*>(t[i].yi);
     const size_t ats = (size_t)p.heads * (ld / 64);
-    k.tblocks = (unsigned)(ats * k.cells * ((p.gw + 15) / 16));
+    const size_t columns = ats * ((p.gw + 15) / 16);
+    k.run = (int)std::max<size_t>(1, std::min<size_t>(k.cells, columns * k.cells / (4 * kComputeUnits)));
+    k.tblocks = (unsigned)(columns * ((k.cells + k.run - 1) / k.run));
     k.rblocks = k.rows ? (unsigned)(ats * ((p.gh + 15) / 16)) : 0;
     k.blocks = k.tblocks + k.rblocks + (unsigned)((p.gh + 255) / 256);
   }
