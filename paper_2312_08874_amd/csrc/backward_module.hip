@@ -1,5 +1,7 @@
 // Module terms of the recomputing backward: the agent-bias tables its kernels read, the sums of the bias gradients
 // they leave behind, and the depthwise convolution's parameter gradients.  No atomics, every sum in a fixed order.
+#include <type_traits>
+
 #include "backward_fused.h"
 #include "mfma_common.h"
 
@@ -302,11 +304,13 @@ __global__ __launch_bounds__(256) void param_grad_out_kernel(GradKind first, Gra
 
 // ---------------------------------------------------------------------------
 // DWC parameter gradients: dw[c][tap] = sum over batch and tokens of dO[y,x,c] V[y + p, x + q, c], db[c] = sum dO.
-// A thread owns a 16-byte piece of the channels of an image column and walks down its rows with the 3 x 3 neighbourhood of V in
+// A thread owns a 16-byte piece of the channels of an image column and walks down V's rows with three rows of dO in
 // registers, so that a row costs three 16-byte reads of V (two of them shared with the neighbouring columns through
-// L1) and one of dO; CHP = 16-byte pieces per token rounded up to a power of two.  The lanes of a block are added by
-// a fixed tree, the blocks by param_grad_out_kernel.
-// grid = (slices, heads); slice = 256 / CHP (column, row segment, image) items.
+// L1) and one of dO, asked for three rows ahead (read where it was used, a row cost a round trip to memory); CHP = 16-byte
+// pieces per token rounded up to a power of two.  The lanes of a block are added by a fixed tree of register permutations
+// (through LDS they took as long as ten rows), the blocks by param_grad_out_kernel.  96 units of 3136 tokens, d = 32: 28 ->
+// 19 us.
+// A block: a head and a slice of 256 / CHP (column, row segment, image) items.
 // ---------------------------------------------------------------------------
 template <class E>
 struct Piece {      // 16 bytes of elements as floats
@@ -327,17 +331,34 @@ struct Piece<ElemF32> {
   }
 };
 
+// sum of v over the lanes with the same lane % CHP, in each of them
+template <int CHP>
+__device__ __forceinline__ float lane_sum(float v) {
+  auto rotated = [](float x, auto by) {      // within 16 lanes
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x120 + decltype(by)::value, 0xF, 0xF, false));
+  };
+  if constexpr (CHP <= 8) v += rotated(v, std::integral_constant<int, 8>{});
+  if constexpr (CHP <= 4) v += rotated(v, std::integral_constant<int, 4>{});
+  if constexpr (CHP <= 2) v += rotated(v, std::integral_constant<int, 2>{});
+  if constexpr (CHP <= 16) return xor16_32_sum(v);
+  const uint32_t b = __float_as_uint(v);
+  const auto h = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+  return __uint_as_float(h[0]) + __uint_as_float(h[1]);
+}
+
 template <class E, int CHP>
-__global__ __launch_bounds__(256) void dwc_param_kernel(const typename Piece<E>::S* __restrict__ V,
+__global__ __launch_bounds__(256, 2) void dwc_param_kernel(const typename Piece<E>::S* __restrict__ V,
                                                         const typename Piece<E>::S* __restrict__ dO,
                                                         float* __restrict__ part, int heads, int d, Layout lay, int gh, int gw,
-                                                        int segs, int seg_len, int items) {
+                                                        int segs, int seg_len, int items, int slices, XcdGrid xg) {
   using S = typename Piece<E>::S;
   constexpr int P = Piece<E>::kCount;
   __shared__ float red[4][CHP][10 * P];
-  const int hd = blockIdx.y, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  int slice, hd;      // the heads of a slice share the lines of token-major rows (see XcdGrid)
+  if (!xg.decode(blockIdx.x, slice, hd)) return;      // before the barrier
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int ch = tid % CHP;
-  const int item = blockIdx.x * (256 / CHP) + tid / CHP;
+  const int item = slice * (256 / CHP) + tid / CHP;
   float acc[10][P];
 #pragma unroll
   for (int k = 0; k < 10; ++k)
@@ -347,56 +368,71 @@ __global__ __launch_bounds__(256) void dwc_param_kernel(const typename Piece<E>:
     const int x = item % gw, s = item / gw % segs, b = item / gw / segs;
     const int u = b * heads + hd, pitch = lay.pitch(gw);
     const S* v = V + lay.in_unit(u, heads) + ch * P;
-    const S* g = dO + lay.out_unit(u, heads) + ch * P;
+    const S* g = dO + lay.out_unit(u, heads) + ch * P + (size_t)x * lay.on;
     const int y0 = s * seg_len, y1 = min(gh, y0 + seg_len);
-    float win[3][3][P];      // rows y - 1, y, y + 1 (rotating), columns x - 1 .. x + 1
-    auto load_row = [&](int y, float (&o)[3][P]) {
-      u32x4 p[3];
+    // addresses are clamped into the image: what a column beside it adds is struck from the sums at the end, rows of dO above
+    // and below it are zeros
+    const S* vx[3] = {v + (size_t)max(x - 1, 0) * lay.sn, v + (size_t)x * lay.sn, v + (size_t)min(x + 1, gw - 1) * lay.sn};
+    const size_t vrow = (size_t)pitch * lay.sn, grow = (size_t)pitch * lay.on;
+    struct Row {
+      u32x4 v[3], g;      // row y of V, row y + 1 of dO
+    } r0, r1, r2;
+    auto load_g = [&](int y) { return *reinterpret_cast<const u32x4*>(g + (size_t)min(max(y, 0), gh - 1) * grow); };
+    auto load = [&](int y, Row& r) {
+      const size_t at = (size_t)min(y, gh - 1) * vrow;
 #pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        const int xx = x + q - 1;
-        p[q] = u32x4{0u, 0u, 0u, 0u};
-        if (y >= 0 && y < gh && xx >= 0 && xx < gw) p[q] = *reinterpret_cast<const u32x4*>(v + ((size_t)y * pitch + xx) * lay.sn);
-      }
-#pragma unroll
-      for (int q = 0; q < 3; ++q) Piece<E>::unpack(p[q], o[q]);
+      for (int q = 0; q < 3; ++q) r.v[q] = *reinterpret_cast<const u32x4*>(vx[q] + at);
+      r.g = load_g(y + 1);
     };
-    auto row = [&](int y, const float (&a)[3][P], const float (&m)[3][P], float (&z)[3][P]) {
-      const u32x4 gp = *reinterpret_cast<const u32x4*>(g + ((size_t)y * pitch + x) * lay.on);
-      load_row(y + 1, z);
-      float gv[P];
-      Piece<E>::unpack(gp, gv);
+    float win[3][P];      // rows y - 1, y, y + 1 of dO (rotating)
+    auto unpack_g = [&](int y, u32x4 p, float (&o)[P]) {
+      Piece<E>::unpack(p, o);
 #pragma unroll
-      for (int i = 0; i < P; ++i) acc[9][i] += gv[i];
+      for (int i = 0; i < P; ++i) o[i] = y >= 0 && y < gh ? o[i] : 0.0f;
+    };
+    auto row = [&](int y, Row& r, const float (&above)[P], const float (&here)[P], float (&below)[P]) {
+      float v[3][P];
+      unpack_g(y + 1, r.g, below);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) Piece<E>::unpack(r.v[q], v[q]);
+      load(y + 3, r);
+#pragma unroll
+      for (int i = 0; i < P; ++i) acc[9][i] += here[i];
 #pragma unroll
       for (int q = 0; q < 3; ++q)
 #pragma unroll
         for (int i = 0; i < P; ++i) {
-          acc[q][i] = fmaf(gv[i], a[q][i], acc[q][i]);
-          acc[3 + q][i] = fmaf(gv[i], m[q][i], acc[3 + q][i]);
-          acc[6 + q][i] = fmaf(gv[i], z[q][i], acc[6 + q][i]);
+          acc[q][i] = fmaf(below[i], v[q][i], acc[q][i]);
+          acc[3 + q][i] = fmaf(here[i], v[q][i], acc[3 + q][i]);
+          acc[6 + q][i] = fmaf(above[i], v[q][i], acc[6 + q][i]);
         }
     };
-    load_row(y0 - 1, win[0]);
-    load_row(y0, win[1]);
+    const u32x4 g0 = load_g(y0 - 1), g1 = load_g(y0);
+    load(y0, r0);
+    load(y0 + 1, r1);
+    load(y0 + 2, r2);
+    unpack_g(y0 - 1, g0, win[0]);
+    unpack_g(y0, g1, win[1]);
     int y = y0;
     for (; y + 3 <= y1; y += 3) {
-      row(y, win[0], win[1], win[2]);
-      row(y + 1, win[1], win[2], win[0]);
-      row(y + 2, win[2], win[0], win[1]);
+      row(y, r0, win[0], win[1], win[2]);
+      row(y + 1, r1, win[1], win[2], win[0]);
+      row(y + 2, r2, win[2], win[0], win[1]);
     }
-    if (y < y1) row(y, win[0], win[1], win[2]);
-    if (y + 1 < y1) row(y + 1, win[1], win[2], win[0]);
+    if (y < y1) row(y, r0, win[0], win[1], win[2]);
+    if (y + 1 < y1) row(y + 1, r1, win[1], win[2], win[0]);
+#pragma unroll
+    for (int k = 0; k < 9; k += 3)
+#pragma unroll
+      for (int i = 0; i < P; ++i) {
+        if (x == 0) acc[k][i] = 0.0f;
+        if (x == gw - 1) acc[k + 2][i] = 0.0f;
+      }
   }
 #pragma unroll
   for (int k = 0; k < 10; ++k)
 #pragma unroll
-    for (int i = 0; i < P; ++i) {
-      float t = acc[k][i];
-#pragma unroll
-      for (int o = CHP; o < 64; o <<= 1) t += __shfl_xor(t, o, 64);
-      acc[k][i] = t;
-    }
+    for (int i = 0; i < P; ++i) acc[k][i] = lane_sum<CHP>(acc[k][i]);
   if (lane < CHP)
 #pragma unroll
     for (int k = 0; k < 10; ++k)
@@ -404,7 +440,7 @@ __global__ __launch_bounds__(256) void dwc_param_kernel(const typename Piece<E>:
       for (int i = 0; i < P; ++i) red[w][lane][i * 10 + k] = acc[k][i];
   __syncthreads();
   for (int i = tid; i < d * 10; i += 256)      // channel-major, ten sums each
-    part[((size_t)hd * gridDim.x + blockIdx.x) * d * 10 + i] =
+    part[((size_t)hd * slices + slice) * d * 10 + i] =
         (red[0][i / (10 * P)][i % (10 * P)] + red[1][i / (10 * P)][i % (10 * P)]) + (red[2][i / (10 * P)][i % (10 * P)] + red[3][i / (10 * P)][i % (10 * P)]);
 }
 
@@ -486,11 +522,12 @@ hipError_t launch_backward_param_grads(const Problem& p, const BiasGradParts (&p
   DwcTotal total{};
   if (p.dwc_w && (pg.ddwc_w || pg.ddwc_b)) {
     const DwcPlan q = dwc_plan(p);
-    const dim3 grid(q.slices, p.heads);
+    const XcdGrid xg = XcdGrid::make(q.slices, p.heads);
+    const dim3 grid((unsigned)xg.blocks());
     auto go = [&](auto kernel, auto elem) {
       using S = typename Piece<decltype(elem)>::S;
       kernel<<<grid, dim3(256), 0, st>>>((const S*)V, (const S*)dO, dwc_part, p.heads, p.d, p.lay, p.gh, p.gw, q.segs, q.seg_len,
-                                         q.items);
+                                         q.items, q.slices, xg);
     };
     auto by_pieces = [&](auto elem) {
       using E = decltype(elem);
