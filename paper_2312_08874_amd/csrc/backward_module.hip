@@ -412,7 +412,7 @@ __global__ __launch_bounds__(256, 2) void dwc_param_kernel(const typename Piece<
     const S* g = dO + lay.out_unit(u, heads) + ch * P + (size_t)x * lay.on;
     const int y0 = s * seg_len, y1 = min(gh, y0 + seg_len);
     // addresses are clamped into the image: what a column beside it adds is struck from the sums at the end, rows of dO above
-    // and below it are zeros
+    // and below it are passed over (not multiplied as zeros: V may hold infinities)
     const S* vx[3] = {v + (size_t)max(x - 1, 0) * lay.sn, v + (size_t)x * lay.sn, v + (size_t)min(x + 1, gw - 1) * lay.sn};
     const size_t vrow = (size_t)pitch * lay.sn, grow = (size_t)pitch * lay.on;
     struct Row {
@@ -426,34 +426,30 @@ __global__ __launch_bounds__(256, 2) void dwc_param_kernel(const typename Piece<
       r.g = load_g(y + 1);
     };
     float win[3][P];      // rows y - 1, y, y + 1 of dO (rotating)
-    auto unpack_g = [&](int y, u32x4 p, float (&o)[P]) {
-      Piece<E>::unpack(p, o);
-#pragma unroll
-      for (int i = 0; i < P; ++i) o[i] = y >= 0 && y < gh ? o[i] : 0.0f;
-    };
     auto row = [&](int y, Row& r, const float (&above)[P], const float (&here)[P], float (&below)[P]) {
       float v[3][P];
-      unpack_g(y + 1, r.g, below);
+      Piece<E>::unpack(r.g, below);
 #pragma unroll
       for (int q = 0; q < 3; ++q) Piece<E>::unpack(r.v[q], v[q]);
       load(y + 3, r);
 #pragma unroll
       for (int i = 0; i < P; ++i) acc[9][i] += here[i];
+      auto taps = [&](int first, const float (&o)[P]) {
 #pragma unroll
-      for (int q = 0; q < 3; ++q)
+        for (int q = 0; q < 3; ++q)
 #pragma unroll
-        for (int i = 0; i < P; ++i) {
-          acc[q][i] = fmaf(below[i], v[q][i], acc[q][i]);
-          acc[3 + q][i] = fmaf(here[i], v[q][i], acc[3 + q][i]);
-          acc[6 + q][i] = fmaf(above[i], v[q][i], acc[6 + q][i]);
-        }
+          for (int i = 0; i < P; ++i) acc[first + q][i] = fmaf(o[i], v[q][i], acc[first + q][i]);
+      };
+      taps(3, here);
+      if (y + 1 < gh) taps(0, below);
+      if (y > 0) taps(6, above);
     };
     const u32x4 g0 = load_g(y0 - 1), g1 = load_g(y0);
     load(y0, r0);
     load(y0 + 1, r1);
     load(y0 + 2, r2);
-    unpack_g(y0 - 1, g0, win[0]);
-    unpack_g(y0, g1, win[1]);
+    Piece<E>::unpack(g0, win[0]);
+    Piece<E>::unpack(g1, win[1]);
     int y = y0;
     for (; y + 3 <= y1; y += 3) {
       row(y, r0, win[0], win[1], win[2]);
