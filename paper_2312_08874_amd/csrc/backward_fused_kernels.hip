@@ -212,9 +212,7 @@ struct Pass {
   }
   hipError_t token(int prob, TokenArgs& a) {
     const int k = prob == kAgg ? 1 : 0;
-    // The statistics with a bias fit four blocks a CU if LDS allows: chunks of 64 agents (8 units of 16384 tokens x 1024 agents:
-    // 110 -> 101 us; the other two, two blocks a CU for their registers, 148 -> 164 and 120 -> 136).
-    a.ch_rows = f.bias[k] && prob == kBcStat ? std::min(f.ch_rows, 64) : f.ch_rows;
+    a.ch_rows = f.bias[k] && prob == kBcStat ? std::min(f.ch_rows, chunk_rows<E, kBcStat, true>()) : f.ch_rows;
     const size_t lds = (size_t)2 * a.ch_rows * (f.DP + El<E>::kRowPad) * sizeof(T) + (size_t)3 * a.ch_rows * sizeof(float);
     if (f.bias[k]) {
       a.bt = bt[k];
