@@ -87,3 +87,21 @@ def test_small_broadcast_in_columns(aa, oracle, grid, agrid, absent, dtype, d):
     ref = util.oracle_forward_units(oracle, wl, t, list(range(4)), params=params, v_residual_k=vk)
     util.assert_parity(util.to_host64(O).reshape(ref.shape), ref, dtype, "small broadcast in columns",
                        max_abs=1e-2 * max(1.0, float(np.abs(ref).max())))
+
+
+@pytest.mark.parametrize("dtype,d", [("f16", 64), ("bf16", 32)])
+def test_small_broadcast_output_rows_past_4_gib(aa, oracle, dtype, d):
+    """One image row of 600 tokens into a column slice of a buffer whose rows are 8 MiB: column 512 is 4 GiB past the first."""
+    import torch
+    grid, agrid = (1, 600), (1, 40)
+    wl = dataclasses.replace(inputs.WORKLOADS["tiny"], batch=1, heads=1, grid=grid, agent_grid=agrid, d=d, dtype=dtype, index=16)
+    t = inputs.make_qkv(wl)
+    params = {k: v for k, v in inputs.make_module_params(1, wl.n, d, grid, blk=(7, 7), index=16).items() if k in ("dwc_w", "dwc_b")}
+    dev = {k: util.to_device(v, dtype, (1, 1, wl.N, d)) for k, v in t.items()}
+    rows = torch.empty(600, 1 << 22, dtype=util.torch_dtype(dtype), device="cuda")
+    out = rows[:, 8:8 + d].view(1, 1, 600, d)
+    out.fill_(float("nan"))
+    aa.agent_attn_fwd(dev["Q"], dev["K"], dev["V"], grid=grid, agent_grid=agrid, params=util.params_to_device(params), out=out)
+    ref = util.oracle_forward_units(oracle, wl, t, [0], params=params)
+    util.assert_parity(util.to_host64(out).reshape(ref.shape), ref, dtype, "output rows past 4 GiB",
+                       max_abs=1e-2 * max(1.0, float(np.abs(ref).max())))
