@@ -16,6 +16,14 @@ inline bool small_columns(int gw, int out_token_stride) {
   return 32 * xts <= 3 * gw && (long long)gw * out_token_stride * 2 < (1ll << 32);
 }
 
+// Image rows a wave walks down: as many blocks (of kColumnWaves waves) as three a CU, which are resident together, and at least
+// four image rows a wave, since two rows of V are read besides.
+constexpr int kColumnWaves = 4;
+inline int small_column_segment(int units, int gh, int gw, int cus) {
+  const int want = std::max(1, (3 * cus + units - 1) / units * kColumnWaves / ((gw + 15) / 16));
+  return std::max(std::min(4, gh), (gh + want - 1) / want);
+}
+
 // --- many agents (large_broadcast_cols_kernel), with half-resized bias tables ---
 constexpr int kColumnRows = 16;          // image rows of a block
 constexpr int kMaxColumnParts = 6;       // cell rows of the tables that a block can hold

@@ -9,6 +9,7 @@ PROGRAM = r'''
 #include "columns_rule.h"
 extern "C" {
 int small_columns(int gw, int out_token_stride) { return aa::small_columns(gw, out_token_stride); }
+int small_column_segment(int units, int gh, int gw) { return aa::small_column_segment(units, gh, gw, 256); }
 int large_column_parts(int n, int gh, int cells) { return aa::large_column_parts(n, gh, cells); }
 int large_columns_pay(int width, int parts, int n, int units, int gh, int gw) { return aa::large_columns_pay(width, parts, n, units, gh, gw, 256); }
 }
