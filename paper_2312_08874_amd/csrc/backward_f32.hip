@@ -7,4 +7,6 @@ template hipError_t launch_token<ElemF32, false>(int, int, int, const TokenArgs&
 template hipError_t launch_token<ElemF32, true>(int, int, int, const TokenArgs&, dim3, size_t, hipStream_t);
 template hipError_t launch_agent<ElemF32, false>(int, int, int, const AgentArgs&, dim3, size_t, hipStream_t);
 template hipError_t launch_agent<ElemF32, true>(int, int, int, const AgentArgs&, dim3, size_t, hipStream_t);
+template hipError_t launch_both<ElemF32, false>(int, int, const AgentArgs&, dim3, size_t, hipStream_t);
+template hipError_t launch_both<ElemF32, true>(int, int, const AgentArgs&, dim3, size_t, hipStream_t);
 }  // namespace aa

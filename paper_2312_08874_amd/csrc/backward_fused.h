@@ -109,6 +109,14 @@ struct AgentArgs {
   int segs, seg_len, pairs, per;
   BiasTables bt;
   float *gt, *gr;             // parts of the gradients of T and R (null: not wanted), see BiasGradParts
+  // the tokens' gradients of the kernels that take both sides (launch_both): kBc O1 = dQ, or Of where the pooling term is
+  // still to come ([units][N][d]); kAgg O1 = dK, O2 = dV with the terms of G = dO as in TokenArgs
+  void *O1, *O2;
+  float* Of;
+  float oscale;
+  const void* G;
+  float vk;
+  const float* dwc_w;
 };
 
 // The kernels, compiled by backward_fused_kernels.hip (16-bit, no bias), backward_bias_{bf16,f16}.hip and
@@ -118,6 +126,9 @@ template <class E, bool BIAS>
 hipError_t launch_token(int prob, int dp, int cols, const TokenArgs& a, dim3 grid, size_t lds, hipStream_t st);
 template <class E, bool BIAS>
 hipError_t launch_agent(int prob, int dp, int cols, const AgentArgs& a, dim3 grid, size_t lds, hipStream_t st);
+// kBc / kAgg of units of at most 64 agents: the agents' and the tokens' gradients from one pass over the scores
+template <class E, bool BIAS>
+hipError_t launch_both(int prob, int dp, const AgentArgs& a, dim3 grid, size_t lds, hipStream_t st);
 
 // --- backward_module.hip ---
 // Fills the tables of the kinds in use ([0]: B2, [1]: B1; the same ld, a multiple of 64).

@@ -9,7 +9,8 @@ namespace aa {
 // compiled by backward_bias_{bf16,f16}.hip and backward_f32.hip
 #define AA_EXTERN(E, BIAS)                                                                                       \
   extern template hipError_t launch_token<E, BIAS>(int, int, int, const TokenArgs&, dim3, size_t, hipStream_t);   \
-  extern template hipError_t launch_agent<E, BIAS>(int, int, int, const AgentArgs&, dim3, size_t, hipStream_t);
+  extern template hipError_t launch_agent<E, BIAS>(int, int, int, const AgentArgs&, dim3, size_t, hipStream_t);   \
+  extern template hipError_t launch_both<E, BIAS>(int, int, const AgentArgs&, dim3, size_t, hipStream_t);
 AA_EXTERN(ElemBF16, true)
 AA_EXTERN(ElemF16, true)
 AA_EXTERN(ElemF32, false)
@@ -19,78 +20,209 @@ AA_EXTERN(ElemF32, true)
 namespace {
 
 // ---------------------------------------------------------------------------
-// Sums over the token ranges, one 64-lane block per (agent, unit), lane = channel (and channel + 64), ranges
-// in order.
+// Sums over the token ranges, in order.  Rows are the agents of all units; lpr lanes (a power of two, at least d / 4) take a
+// row, four channels a lane.  What bounds them is the way to memory: the ranges are asked for eight at a time, so that a row
+// costs a trip or two instead of one per range, and a block takes 8 to 32 rows (one 64-lane block per row and a trip per
+// range before: merge of 192 units x 49 rows of 64 channels in two ranges 7.6 -> 4.2 us, of 8 x 1024 in four 7.4 -> 5.3).
 // ---------------------------------------------------------------------------
+struct SumRows {
+  int rows, n, d, S, lpr_log2;
+  __device__ __forceinline__ bool place(int& row, int& c, size_t& first) const {      // first: of range 0, in rows
+    row = blockIdx.x * (kThreads >> lpr_log2) + (threadIdx.x >> lpr_log2);
+    c = 4 * (threadIdx.x & ((1 << lpr_log2) - 1));
+    const int there = min(row, rows - 1), u = unit(there);
+    first = (size_t)u * S * n + (there - u * n);
+    return row < rows && c < d;
+  }
+  __device__ __forceinline__ int unit(int r) const { return (int)((unsigned)r / (unsigned)n); }
+  // sum over a row's lanes
+  __device__ __forceinline__ float row_sum(float v) const {
+    for (int m = 1; m < 1 << lpr_log2; m <<= 1) v += __shfl_xor(v, m);
+    return v;
+  }
+};
+__device__ __forceinline__ f32x4 row4(const float* p, size_t row, int d, int c) { return load_global<f32x4>(p + row * d + c); }
+
 // log-sum-exp merge of the recomputed aggregation: V_A (fp32 and element type), reference and weight of the rows (log2
 // domain; w1 null: the log-sum-exp, no weight)
 template <class E>
-__global__ __launch_bounds__(64) void fused_merge_kernel(const float* __restrict__ acc, const float* __restrict__ pm,
-                                                         const float* __restrict__ pl, int S, int n, int d,
-                                                         float* VAf, typename E::T* VAe,
-                                                         float* __restrict__ lse1, float* __restrict__ w1, int* __restrict__ large) {
-  const int ag = blockIdx.x, u = blockIdx.y, lane = threadIdx.x;
-  __shared__ float wgt[64];
-  // lane s holds range s (S <= 64)
-  const size_t my = ((size_t)u * S + min(lane, S - 1)) * n + ag;
-  const float pm_s = lane < S ? pm[my] : -INFINITY, pl_s = lane < S ? pl[my] : 0.f;
-  const float M = wave_max(pm_s);
-  const float w_s = fast_exp2(pm_s - M);
-  const float L = wave_sum(pl_s * w_s);
-  wgt[lane] = w_s / L;
-  __syncthreads();
-  for (int c = lane; c < d; c += 64) {
-    float v = 0.f;
-    for (int s = 0; s < S; ++s) v += acc[(((size_t)u * S + s) * n + ag) * d + c] * wgt[s];
-    const size_t o = ((size_t)u * n + ag) * d + c;
-    VAf[o] = v;
-    VAe[o] = E::from_f32(v);      // fp32: the same array
+__global__ __launch_bounds__(kThreads) void fused_merge_kernel(SumRows g, const float* acc, const float* pm, const float* pl,
+                                                               float* VAf, typename E::T* VAe, float* lse1, float* w1, int* large) {
+  using X = El<E>;
+  int row, c;
+  size_t first;
+  const bool ok = g.place(row, c, first);
+  float M = -INFINITY;
+  for (int s0 = 0; s0 < g.S; s0 += 8) {
+    float m[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) m[k] = load_global<float>(pm + first + (size_t)min(s0 + k, g.S - 1) * g.n);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) M = fmaxf(M, m[k]);
   }
-  if (lane == 0) {
-    const bool apart = w1 && (El<E>::kBytes == 4 || fabsf(M) > kLargeRef);
-    lse1[(size_t)u * n + ag] = apart ? M : M + __builtin_amdgcn_logf(L);
-    if (w1) w1[(size_t)u * n + ag] = apart ? 1.0f / L : 1.0f;
-    if (large && apart) set_flag(large + u);
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  float L = 0.f;
+  for (int s0 = 0; s0 < g.S; s0 += 8) {
+    float m[8], l[8];
+    f32x4 x[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const size_t at = first + (size_t)min(s0 + k, g.S - 1) * g.n;
+      m[k] = load_global<float>(pm + at), l[k] = load_global<float>(pl + at);
+      x[k] = row4(acc, at, g.d, c < g.d ? c : 0);
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const float w = s0 + k < g.S ? fast_exp2(m[k] - M) : 0.f;
+      L = fmaf(l[k], w, L);
+      v += x[k] * w;
+    }
+  }
+  if (!ok) return;
+  v *= 1.0f / L;
+  const size_t o = (size_t)row * g.d + c;
+  *reinterpret_cast<f32x4*>(VAf + o) = v;
+  if constexpr (X::kBytes == 2) *reinterpret_cast<typename X::P4*>(VAe + o) = X::pack4(v[0], v[1], v[2], v[3]);      // fp32: the same array
+  if (c == 0) {
+    const bool apart = w1 && (X::kBytes == 4 || fabsf(M) > kLargeRef);
+    lse1[row] = apart ? M : M + __builtin_amdgcn_logf(L);
+    if (w1) w1[row] = apart ? 1.0f / L : 1.0f;
+    if (large && apart) set_flag(large + g.unit(row));
   }
 }
 
 // dV_A = sum of the ranges (element type), D1 = rowsum(dV_A o V_A), dA = c2 * sum of the ranges
 template <class E>
-__global__ __launch_bounds__(64) void fused_reduce_bc_kernel(const float* __restrict__ pva, const float* __restrict__ pa,
-                                                             int S, int n, int d, const float* __restrict__ VAf,
-                                                             typename E::T* __restrict__ dVAe, float* __restrict__ D1,
-                                                             float* __restrict__ dAf, float c2) {
-  const int ag = blockIdx.x, u = blockIdx.y, lane = threadIdx.x;
-  float dot = 0.f;
-  for (int c = lane; c < d; c += 64) {
-    float v = 0.f, q = 0.f;
-    for (int s = 0; s < S; ++s) {
-      const size_t i = (((size_t)u * S + s) * n + ag) * d + c;
-      v += pva[i];
-      q += pa[i];
+__global__ __launch_bounds__(kThreads) void fused_reduce_bc_kernel(SumRows g, const float* pva, const float* pa, const float* VAf,
+                                                                   typename E::T* dVAe, float* D1, float* dAf, float c2) {
+  using X = El<E>;
+  int row, c;
+  size_t first;
+  const bool ok = g.place(row, c, first);
+  f32x4 v = {0.f, 0.f, 0.f, 0.f}, q = v;
+  for (int s0 = 0; s0 < g.S; s0 += 8) {
+    f32x4 x[8], y[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const size_t at = first + (size_t)min(s0 + k, g.S - 1) * g.n;
+      x[k] = row4(pva, at, g.d, c < g.d ? c : 0), y[k] = row4(pa, at, g.d, c < g.d ? c : 0);
     }
-    const size_t o = ((size_t)u * n + ag) * d + c;
-    const typename E::T e = E::from_f32(v);
-    dVAe[o] = e;
-    dot += E::to_f32(e) * VAf[o];
-    dAf[o] = c2 * q;
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (s0 + k < g.S) v += x[k], q += y[k];
   }
-  dot = wave_sum(dot);
-  if (lane == 0) D1[(size_t)u * n + ag] = dot;
+  float dot = 0.f;
+  const size_t o = (size_t)row * g.d + c;
+  if (ok) {
+    const typename X::P4 e = X::pack4(v[0], v[1], v[2], v[3]);
+    *reinterpret_cast<typename X::P4*>(dVAe + o) = e;
+    *reinterpret_cast<f32x4*>(dAf + o) = q * c2;
+    const f32x4 p = X::unpack4(e) * load_global<f32x4>(VAf + o);
+    dot = (p[0] + p[1]) + (p[2] + p[3]);
+  }
+  dot = g.row_sum(dot);
+  if (ok && c == 0) D1[row] = dot;
 }
 
 // dA += c1 * sum of the ranges; written in the element type too when the agents were handed in
 template <class E>
-__global__ __launch_bounds__(64) void fused_reduce_agg_kernel(const float* __restrict__ pa, int S, int n, int d,
-                                                              float* __restrict__ dAf, typename E::T* __restrict__ dAe, float c1) {
-  const int ag = blockIdx.x, u = blockIdx.y, lane = threadIdx.x;
-  for (int c = lane; c < d; c += 64) {
-    float q = 0.f;
-    for (int s = 0; s < S; ++s) q += pa[(((size_t)u * S + s) * n + ag) * d + c];
-    const size_t o = ((size_t)u * n + ag) * d + c;
-    const float v = dAf[o] + c1 * q;
-    dAf[o] = v;
-    if (dAe) dAe[o] = E::from_f32(v);
+__global__ __launch_bounds__(kThreads) void fused_reduce_agg_kernel(SumRows g, const float* pa, float* dAf, typename E::T* dAe, float c1) {
+  using X = El<E>;
+  int row, c;
+  size_t first;
+  const bool ok = g.place(row, c, first);
+  f32x4 q = {0.f, 0.f, 0.f, 0.f};
+  for (int s0 = 0; s0 < g.S; s0 += 8) {
+    f32x4 x[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] = row4(pa, first + (size_t)min(s0 + k, g.S - 1) * g.n, g.d, c < g.d ? c : 0);
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (s0 + k < g.S) q += x[k];
+  }
+  if (!ok) return;
+  const size_t o = (size_t)row * g.d + c;
+  const f32x4 v = load_global<f32x4>(dAf + o) + q * c1;
+  *reinterpret_cast<f32x4*>(dAf + o) = v;
+  if (dAe) *reinterpret_cast<typename X::P4*>(dAe + o) = X::pack4(v[0], v[1], v[2], v[3]);
+}
+
+// ---------------------------------------------------------------------------
+// dQ = round(dQ of the broadcast + Pooling^T(dA)) where the broadcast's kernel has left dQ in fp32: `src` ([units][N][d];
+// null: dQ itself, in fp32).  dA = dAf + c1 * sum of the ranges of pa (S of them; none: dAf is complete) is finished here, in
+// LDS, by every block of a unit.  A block takes 256 tokens: their places in the pooling grid are found once each (a dozen
+// divisions), then a thread takes 16 bytes of a row.  Memory bounds it, most of all the way there: what a block reads is asked
+// for ahead of everything else, and no block takes a second turn.
+// ---------------------------------------------------------------------------
+struct PoolOutArgs {
+  const float *src, *dAf, *pa;
+  void* dQ;
+  int S, N, n, d, gh, gw, ah, aw;
+  uint32_t inv_cpr;      // of the 16-byte pieces in a row of dQ
+  float c1;
+  UnitPlace at;
+};
+template <class E>
+__global__ __launch_bounds__(kThreads) void pool_grad_out_kernel(PoolOutArgs a) {
+  using X = El<E>;
+  using S = typename X::S;
+  constexpr int kPer = X::kPerPiece, kBatch = 16 / kPer * 2;
+  extern __shared__ __align__(16) unsigned char smem[];
+  PoolPlace* place = reinterpret_cast<PoolPlace*>(smem);
+  float* dA = reinterpret_cast<float*>(place + kThreads);
+  const int u = blockIdx.y, tid = threadIdx.x, cpr = a.d / kPer, t0 = blockIdx.x * kThreads;
+  const int pieces = min(kThreads, a.N - t0) * cpr;
+  S* out = (S*)a.dQ + a.at.template base<kPer>(u, false);
+  const float* src = a.src ? a.src + (size_t)u * a.N * a.d : nullptr;
+  f32x4 v[kBatch][kPer / 4];
+  S* at[kBatch];
+  int tok[kBatch], c[kBatch];
+  auto fetch = [&](int p0) {
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) {
+      const int p = min(p0 + k * kThreads, pieces - 1);
+      tok[k] = quotient(p, a.inv_cpr);
+      c[k] = (p - tok[k] * cpr) * kPer;
+      at[k] = out + a.at.row(t0 + tok[k]) * a.at.sn + c[k];
+#pragma unroll
+      for (int h = 0; h < kPer / 4; ++h)
+        v[k][h] = load_global<f32x4>((src ? src + (size_t)(t0 + tok[k]) * a.d + c[k] : (const float*)at[k]) + 4 * h);
+    }
+  };
+  fetch(tid);
+  const size_t nd = (size_t)a.n * a.d;
+  for (int i = 4 * tid; i < (int)nd; i += 4 * kThreads) {
+    const f32x4 own = load_global<f32x4>(a.dAf + (size_t)u * nd + i);
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+    for (int s0 = 0; s0 < a.S; s0 += 8) {
+      f32x4 x[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) x[k] = load_global<f32x4>(a.pa + ((size_t)u * a.S + min(s0 + k, a.S - 1)) * nd + i);
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (s0 + k < a.S) sum += x[k];
+    }
+    *reinterpret_cast<f32x4*>(dA + i) = own + sum * a.c1;
+  }
+  const int mine = min(t0 + tid, a.N - 1), ty = mine / a.gw;
+  place[tid].find(ty, mine - ty * a.gw, a.gh, a.gw, a.ah, a.aw);
+  __syncthreads();
+  for (int p0 = tid; p0 < pieces; p0 += kBatch * kThreads) {
+    if (p0 != tid) fetch(p0);
+#pragma unroll
+    for (int k = 0; k < kBatch; ++k) {
+      if (p0 + k * kThreads >= pieces) continue;
+      const PoolPlace pp = place[tok[k]];
+#pragma unroll
+      for (int h = 0; h < kPer / 4; ++h) v[k][h] += pp.gather(dA, a.d, c[k] + 4 * h);
+      if constexpr (X::kBytes == 4) {
+        *reinterpret_cast<f32x4*>(at[k]) = v[k][0];
+      } else {
+        const auto lo = X::pack4(v[k][0][0], v[k][0][1], v[k][0][2], v[k][0][3]);
+        const auto hi = X::pack4(v[k][kPer / 4 - 1][0], v[k][kPer / 4 - 1][1], v[k][kPer / 4 - 1][2], v[k][kPer / 4 - 1][3]);
+        *reinterpret_cast<u32x4*>(at[k]) = u32x4{lo[0], lo[1], hi[0], hi[1]};
+      }
+    }
   }
 }
 
@@ -100,11 +232,12 @@ __global__ __launch_bounds__(64) void fused_reduce_agg_kernel(const float* __res
 struct FusedPlan {
   int DP, n_rows, ch_rows, token_cols, agent_cols[2], agent_blocks[2], S[2], chunk[2];      // [0]: agent kBc, [1]: kFwd / kAgg
   bool wide;
+  bool both[2];      // one kernel takes the agents' and the tokens' gradients ([0]: kBc, [1]: kAgg)
   // agent bias, [0]: the broadcast's (B2), [1]: the aggregation's (B1); segments and pairs of columns as in AgentArgs
   bool bias[2];
   int cells[2], ld, segs[2], seg_len[2], pairs[2], per[2];
   // workspace offsets in floats (every region a multiple of 64 floats)
-  size_t VAf, VAe, dVAe, lse1, w1, D1, lse2, w2, large, D2, dAf, part, total;
+  size_t VAf, VAe, dVAe, lse1, w1, D1, lse2, w2, large, D2, dAf, dQf, part, total;
   bool weights[2];      // softmax rows may have a weight beside their reference
   size_t ta[2], tx[2], rows[2], yi[2], gt[2], gr[2], gsum[2], dwc;
 };
@@ -153,6 +286,12 @@ FusedPlan fused_plan(const Problem& p, bool forward = false) {
   // four token columns per wave in the broadcast's token kernels when the unit has more than one 64-agent chunk to
   // reuse them on and that still leaves two blocks per CU
   f.wide = !f32 && f.DP <= 64 && p.n > 64 && (long long)((p.N + 255) / 256) * p.units >= 2 * kComputeUnits;
+  // One kernel for both sides wherever a block of four waves holds all agents of a unit and the registers suffice (105
+  // training steps of 8 .. 192 units of 196 .. 10000 tokens x 16 .. 64 agents, start / now: 0.73 to 0.97 of the time, 0.90 in the
+  // mean).  Not dK / dV with a bias at 128 channels in 16 bits (263 registers spilled: 16 x 4 units of 784 x 16 285 -> 299 us) nor
+  // fp32 above 64; the convolution without a bias is the token kernel's (its tokens are not walked down columns here).
+  for (int k = 0; k < 2; ++k)
+    f.both[k] = !forward && p.n <= 64 && (!f32 || f.DP <= 64) && (k == 0 || (f.bias[1] ? f32 || f.DP <= 64 : !p.dwc_w));
   const size_t u = (size_t)p.units, nd = up64((size_t)p.n * p.d), un = up64(u * p.n), uN = up64(u * p.N);
   size_t o = 0;
   f.VAf = o, o += u * nd;
@@ -169,6 +308,7 @@ FusedPlan fused_plan(const Problem& p, bool forward = false) {
     if (!f32 && (f.bias[0] || f.bias[1])) f.large = o, o += up64(2 * u);
     f.D2 = o, o += uN;
     f.dAf = o, o += u * nd;
+    if (f.both[0] && !f32) f.dQf = o, o += up64(u * p.N * p.d);
   }
   const size_t H = (size_t)p.heads, wp = 16 * (size_t)xts;
   for (int k = 0; k < 2; ++k) {
@@ -186,6 +326,15 @@ FusedPlan fused_plan(const Problem& p, bool forward = false) {
   if (p.dwc_w && !forward) f.dwc = o, o += up64(dwc_param_part_floats(p));
   f.total = o;
   return f;
+}
+
+// k: of the ranges, as in FusedPlan
+SumRows sum_rows(const Problem& p, const FusedPlan& f, int k, dim3& grid) {
+  SumRows g{p.units * p.n, p.n, p.d, f.S[k], 0};
+  while ((4 << g.lpr_log2) < p.d) ++g.lpr_log2;
+  const int per = kThreads >> g.lpr_log2;
+  grid = dim3((g.rows + per - 1) / per);
+  return g;
 }
 
 // Everything a pass launches: the tables of the biases in use and the token and agent kernels on top of them.
@@ -229,9 +378,11 @@ struct Pass {
     const size_t lds = (size_t)4 * 32 * (f.DP + El<E>::kRowPad) * sizeof(T) + 2 * 96 * sizeof(float);
     const dim3 grid(f.S[k], f.agent_blocks[k], p.units);
     a.chunk = f.chunk[k], a.S = f.S[k];
-    if (!f.bias[k]) return launch_agent<E, false>(prob, f.DP, f.agent_cols[k], a, grid, lds, st);
+    const bool both = prob != kFwd && f.both[k];
+    if (!f.bias[k]) return both ? launch_both<E, false>(prob, f.DP, a, grid, lds, st) : launch_agent<E, false>(prob, f.DP, f.agent_cols[k], a, grid, lds, st);
     a.bt = bt[k], a.segs = f.segs[k], a.seg_len = f.seg_len[k], a.pairs = f.pairs[k], a.per = f.per[k];
     a.gt = gt, a.gr = gr;
+    if (both) return launch_both<E, true>(prob, f.DP, a, grid, lds, st);
     return launch_agent<E, true>(prob, f.DP, f.agent_cols[k], a, grid, lds, st);
   }
   AgentArgs agent_args() const {
@@ -254,9 +405,10 @@ struct Pass {
     a.X = K, a.Y = V, a.M1 = A, a.P1 = part, a.pm = pm, a.pl = pl, a.sc = p.scale1 * kLog2e;
     const hipError_t e = agent(kFwd, a, nullptr, nullptr);
     if (e != hipSuccess) return e;
-    fused_merge_kernel<E><<<dim3(p.n, p.units), dim3(64), 0, st>>>(part, pm, pl, f.S[1], p.n, p.d, ws + f.VAf,
-                                                                   reinterpret_cast<T*>(ws + f.VAe), ws + f.lse1, w1,
-                                                                   large && f.bias[1] ? large + p.units : nullptr);
+    dim3 grid;
+    const SumRows g = sum_rows(p, f, 1, grid);
+    fused_merge_kernel<E><<<grid, dim3(kThreads), 0, st>>>(g, part, pm, pl, ws + f.VAf, reinterpret_cast<T*>(ws + f.VAe),
+                                                           ws + f.lse1, w1, large && f.bias[1] ? large + p.units : nullptr);
     return hipGetLastError();
   }
 };
@@ -274,7 +426,6 @@ hipError_t run_fused(const Problem& p, const FusedPlan& f, const void* Q, const 
   float* part1 = ws + f.part;
   float* part2 = part1 + (size_t)U * f.S[0] * n * d;      // kBc only
   const float sc1 = p.scale1 * kLog2e, sc2 = p.scale2 * kLog2e;
-  const dim3 rgrid(n, U);
   float *w1 = f.weights[1] ? ws + f.w1 : nullptr, *w2 = f.weights[0] ? ws + f.w2 : nullptr;
   int* large = El<E>::kBytes == 2 && (f.bias[0] || f.bias[1]) ? reinterpret_cast<int*>(ws + f.large) : nullptr;
   Pass<E> pass{p, f, ws, st, w1, large};
@@ -290,25 +441,48 @@ hipError_t run_fused(const Problem& p, const FusedPlan& f, const void* Q, const 
   tk.st3 = w2, ag.tw1 = w2, tk.rw1 = ag.rw1 = w1, tk.large = large, ag.large = large;
   if ((e = pass.token(kBcStat, tk)) != hipSuccess) return e;
   ag.X = Q, ag.Y = dO, ag.M1 = A, ag.M2 = VAe, ag.ts1 = lse2, ag.ts2 = D2, ag.P1 = part1, ag.P2 = part2, ag.sc = sc2;
+  float* dQf = f.both[0] && !agents_given && El<E>::kBytes == 2 ? ws + f.dQf : nullptr;
+  ag.O1 = dQ, ag.Of = dQf, ag.oscale = p.scale2;
   if ((e = pass.agent(kBc, ag, pg.db2_col || pg.db2_blk ? ws + f.gt[0] : nullptr, pg.db2_row ? ws + f.gr[0] : nullptr)) !=
       hipSuccess)
     return e;
-  fused_reduce_bc_kernel<E><<<rgrid, dim3(64), 0, st>>>(part1, part2, f.S[0], n, d, VAf, dVAe, D1, dAf, p.scale2);
+  dim3 rgrid;
+  const SumRows rows_bc = sum_rows(p, f, 0, rgrid);
+  fused_reduce_bc_kernel<E><<<rgrid, dim3(kThreads), 0, st>>>(rows_bc, part1, part2, VAf, dVAe, D1, dAf, p.scale2);
 
   // aggregation
   if (large) tk.large = large + U, ag.large = large + U;
   tk.X = K, tk.Y = V, tk.M2 = dVAe, tk.rs1 = lse1, tk.rs2 = D1, tk.sc = sc1, tk.oscale = p.scale1;
   tk.O1 = dK, tk.O2 = dV, tk.G = dO, tk.vk = p.vk, tk.dwc_w = p.dwc_w;
-  if ((e = pass.token(kAgg, tk)) != hipSuccess) return e;
+  if (!f.both[1] && (e = pass.token(kAgg, tk)) != hipSuccess) return e;
+  ag.O1 = dK, ag.O2 = dV, ag.Of = nullptr, ag.oscale = p.scale1, ag.G = dO, ag.vk = p.vk, ag.dwc_w = p.dwc_w;
   ag.X = K, ag.Y = V, ag.M2 = dVAe, ag.rs1 = lse1, ag.rs2 = D1, ag.P1 = part1, ag.sc = sc1;
   if ((e = pass.agent(kAgg, ag, pg.db1_col || pg.db1_blk ? ws + f.gt[1] : nullptr, pg.db1_row ? ws + f.gr[1] : nullptr)) !=
       hipSuccess)
     return e;
-  fused_reduce_agg_kernel<E><<<rgrid, dim3(64), 0, st>>>(part1, f.S[1], n, d, dAf, agents_given ? (T*)dA : nullptr, p.scale1);
   // dQ last: the pooling term needs the finished dA
-  tk.large = large;
-  tk.X = Q, tk.Y = dO, tk.M2 = VAe, tk.sc = sc2, tk.oscale = p.scale2, tk.O1 = dQ, tk.dA = agents_given ? nullptr : dAf;
-  if ((e = pass.token(kBc, tk)) != hipSuccess) return e;
+  if (f.both[0] && !agents_given) {
+    // many ranges (few units): added up first, not by every block
+    const bool sum_first = f.S[1] > 8;
+    if (sum_first) {
+      const SumRows rows_agg = sum_rows(p, f, 1, rgrid);
+      fused_reduce_agg_kernel<E><<<rgrid, dim3(kThreads), 0, st>>>(rows_agg, part1, dAf, (T*)nullptr, p.scale1);
+    }
+    PoolOutArgs po{};
+    po.src = dQf, po.dAf = dAf, po.pa = part1, po.dQ = dQ, po.S = sum_first ? 0 : f.S[1], po.N = p.N, po.n = n, po.d = d;
+    po.gh = p.gh, po.gw = p.gw, po.ah = p.ah, po.aw = p.aw, po.c1 = p.scale1, po.at = tk.at;
+    po.inv_cpr = quotient_inverse(d / El<E>::kPerPiece);
+    const size_t lds = kThreads * sizeof(PoolPlace) + (size_t)n * d * sizeof(float);
+    pool_grad_out_kernel<E><<<dim3((p.N + kThreads - 1) / kThreads, U), dim3(kThreads), lds, st>>>(po);
+    e = hipGetLastError();
+  } else {
+    const SumRows rows_agg = sum_rows(p, f, 1, rgrid);
+    fused_reduce_agg_kernel<E><<<rgrid, dim3(kThreads), 0, st>>>(rows_agg, part1, dAf, agents_given ? (T*)dA : nullptr, p.scale1);
+    tk.large = large;
+    tk.X = Q, tk.Y = dO, tk.M2 = VAe, tk.sc = sc2, tk.oscale = p.scale2, tk.O1 = dQ, tk.dA = agents_given ? nullptr : dAf;
+    if (!f.both[0]) e = pass.token(kBc, tk);
+  }
+  if (e != hipSuccess) return e;
 
   BiasGradParts parts[2] = {};
   for (int k = 0; k < 2; ++k)

@@ -128,6 +128,9 @@ ALLOWED = {
     # take) and in fp32 at 64 and 128
     ("token", "16", 128, 1, 1): (200, False), ("token", "16", 32, 2, 1): (100, False),
     ("token", "32", 64, 2, 1): (130, False), ("token", "32", 128, 2, 1): (60, False),
+    # agent kernels that take the tokens' side as well, with a bias: dK / dV at 32 channels (three blocks per CU), dQ at 128,
+    # fp32 dK / dV at 64
+    ("both", "16", 32, 2, 1): (12, False), ("both", "16", 128, 1, 1): (40, False), ("both", "32", 64, 2, 1): (24, False),
 }
 
 
@@ -136,8 +139,8 @@ def _backward_kernel(symbol):
     m = re.search(r"(fused_token|fused_agent|bias_agent)_kernelINS_\d+Elem(BF16|F16|F32)ELi(\d+)ELi(\d+)ELi\d+E(Lb(\d)E)?", symbol)
     if not m:
         return None
-    kind = "token" if m.group(1) == "fused_token" else "agent"
-    bias = int(m.group(6)) if kind == "token" else int(m.group(1) == "bias_agent")
+    kind = "token" if m.group(1) == "fused_token" else "both" if m.group(6) == "1" else "agent"
+    bias = int(m.group(6)) if kind == "token" else int(m.group(1) == "bias_agent")      # agent kernels: group 6 is BOTH
     return kind, "32" if m.group(2) == "F32" else "16", int(m.group(3)), int(m.group(4)), bias
 
 
