@@ -369,146 +369,223 @@ __global__ __launch_bounds__(256) void bias_dense_kernel(BiasArgs b1, float* __r
 
 // ---------------------------------------------------------------------------
 // The half-resized tables of BiasArgs (both kinds in one launch; a null output skips a kind).
+// The tables are transposes of the parameters: the lanes lie along a table's contiguous direction (kind 1: agents, kind 2: columns
+// or image rows), a wave stores 1 KB at a time, and reads the parameters in pieces of 16 bytes per lane, `quads` neighbouring ones,
+// all asked for at once, for all cell rows a block makes.  What a cell row contributes comes from LDS, where the block
+// component of the block's agents waits, `run` cell rows of it (kind 1 [agent][run w0], an odd stride apart; kind 2 [cell][16
+// quads agents]); block grids too wide for that are read from memory.  Blocks: kind 1 64 agents x 16 quads columns (R: image
+// rows), kind 2 64 columns (R: image rows) x 16 quads agents, a wave a quarter (of a narrow image more agents, so that no lane is idle).
+// Bound by the way to the cold parameters and the stores behind it.  8 heads, 1024 agents, 128 x 128 tokens, 7 cell rows, all four
+// tables (67 MB): 40.0 -> 19.9 us (one thread per 16 bytes of output and lanes in 8 x 8 tiles before: half of it was waiting for the
+// parameters, which every thread gathered by itself); 8 of 80 x 100 tokens x 256 agents 9.9 -> 8.0.
 // ---------------------------------------------------------------------------
-// One thread per 16 bytes of output (four neighbours in x, or four agents) and `run` cell rows (the half-resized part: what it
-// takes of the column component and the interpolation along x is the same for all of them; 8 heads, 1024 agents, 128 x 128
-// tokens, 7 cell rows: 34 -> 31 us).  The tables are transposes of
-// the parameter layouts, so the 64 lanes of a wave take an 8 x 8 tile of (agent, x) positions: eight lanes
-// along the table's contiguous direction and eight along the parameter's give 128-byte pieces on both
-// sides.  The counts are threads per segment (tiles x 64, ragged tiles included).
-__global__ __launch_bounds__(256) void bias_half_kernel(BiasArgs b1, float* __restrict__ half1, float* __restrict__ rows1,
-                                                        BiasArgs b2, float* __restrict__ half2, float* __restrict__ rows2,
-                                                        int n, int gh, int gw, unsigned q_half1, unsigned q_half2,
-                                                        unsigned q_rows, unsigned run1, unsigned run2) {
-  unsigned q = blockIdx.x * 256u + threadIdx.x;
-  const unsigned q_rows64 = (q_rows + 63u) & ~63u;      // every segment starts on a wave boundary
-  const unsigned seg[4] = {half1 ? q_half1 : 0u, rows1 ? q_rows64 : 0u, half2 ? q_half2 : 0u, rows2 ? q_rows64 : 0u};
-  int which = 0;
-  while (which < 4 && q >= seg[which]) q -= seg[which++];
-  if (which == 4) return;
-  const bool first = which < 2;
-  const BiasArgs& b = first ? b1 : b2;
-  const unsigned NA = (unsigned)round_up64(n), NAq = NA >> 2, gwq = (unsigned)gw >> 2;
-  const int h0 = b.blk ? b.h0 : 1, w0 = b.blk ? b.w0 : 1;
-  typedef float f32x4 __attribute__((ext_vector_type(4)));
-  const unsigned he = (unsigned)h0;
-  float out[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-  float* dst;
-  const unsigned lane = q & 63u, lo = lane & 7u, hi = lane >> 3;
-  q >>= 6;                     // tile index
-  bool live = true;
-  size_t quad = 0;             // index of this thread's 16 bytes in its table
-  auto store = [&](float* to, const float (&v)[4]) {
-    *(f32x4*)to = f32x4{floored(v[0] * kLog2e), floored(v[1] * kLog2e), floored(v[2] * kLog2e), floored(v[3] * kLog2e)};
-  };
-  // the column component `out` plus the block component between entries p0 and p1 (j of them `pitch` apart) of cell rows
-  // [c0, c1), `step` apart; the table's rows are `row` floats apart
-  auto cells = [&](float* to, size_t row, unsigned c0, unsigned c1, const float* const (&p0)[4], const float* const (&p1)[4],
-                   const float (&fx)[4], size_t step, int valid) {
-    f32x4 v0 = {0.0f, 0.0f, 0.0f, 0.0f}, v1 = v0;
-    auto load = [&](unsigned c) {
+// Block number = ((head * runs + run) * outer + o) * inner + i: blocks along the lanes (i) and along the waves' quads (o).  The
+// inverses (see quotient) are 0 where they would not be exact.
+struct HalfBlocks {
+  unsigned count, inner, outer, runs;
+  uint32_t inv_inner, inv_outer, inv_runs;
+  __device__ __forceinline__ static unsigned div(unsigned v, unsigned by, uint32_t inverse) {
+    return by == 1u ? v : inverse ? __umulhi(v, inverse) : v / by;
+  }
+  __device__ __forceinline__ void place(unsigned q, unsigned& i, unsigned& o, unsigned& run, unsigned& head) const {
+    const unsigned t = div(q, inner, inv_inner), t2 = div(t, outer, inv_outer);
+    i = q - t * inner, o = t - t2 * outer;
+    head = div(t2, runs, inv_runs), run = t2 - head * runs;
+  }
+};
+struct HalfKind {
+  BiasArgs b;
+  float *half, *rows;
+  HalfBlocks cells, row_part;
+  unsigned run;                                     // cell rows a block makes
+  unsigned quads, row_quads;                        // 1, 2 or 4
+  unsigned group_log2, row_group_log2;              // kind 2, images of up to 32 columns (rows): quads side by side in a wave
+  unsigned staged, col_pieces, row_pieces;          // the block component goes through LDS; pieces of the others lie on 16 bytes
+  uint32_t inv_per, inv_last;                       // quotient_inverse of run w0, and of what the last block has of it
+};
+typedef float table4 __attribute__((ext_vector_type(4)));
+// `quads` neighbouring pieces of a parameter from p on, of which `valid` floats exist (the others: 0)
+__device__ __forceinline__ void half_pieces(const float* p, int quads, int valid, bool pieces, table4 (&v)[4]) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (j < valid) v0[j] = p0[j][(c - c0) * step], v1[j] = p1[j][(c - c0) * step];
-    };
-    load(c0);
-    for (unsigned c = c0; c < c1; ++c, to += row) {
+  for (int m = 0; m < 4; ++m) {
+    v[m] = table4{0.f, 0.f, 0.f, 0.f};
+    if (m >= quads || 4 * m >= valid) continue;
+    if (pieces) {
+      v[m] = *(const table4*)(p + 4 * m);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[m][j] = p[min(4 * m + j, valid - 1)];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (4 * m + j >= valid) v[m][j] = 0.f;
+  }
+}
+template <int KIND>
+__device__ __forceinline__ void half_block(const HalfKind& k, unsigned q, int n, int gw, unsigned NA, float* lds) {
+  const BiasArgs& b = k.b;
+  const int h0 = b.blk ? b.h0 : 1, w0 = b.blk ? b.w0 : 1, Q = (int)k.quads, span = (int)(16 * Q) << k.group_log2;
+  const int lane = (threadIdx.x & 63) & (63 >> k.group_log2);      // narrow images: several of a wave's quads side by side
+  const int w = (int)((threadIdx.x >> 6 << k.group_log2) + ((threadIdx.x & 63) >> (6 - k.group_log2)));
+  unsigned li, wi, c0, hd;
+  k.cells.place(q, li, wi, c0, hd);
+  c0 *= k.run;
+  const int cells = min((int)k.run, h0 - (int)c0);
+  const int a = KIND == 1 ? (int)(64 * li) + lane : (int)wi * span + 4 * Q * w;      // this thread's agent, or the first of its agents
+  const int x = KIND == 1 ? (int)wi * span + 4 * Q * w : (int)(64 * li) + lane;      // its first column, or its column
+  table4 col[4];
+  const int valid = !b.col || a >= n || x >= gw ? 0 : KIND == 1 ? gw - x : n - a;
+  half_pieces(b.col + (KIND == 1 ? ((size_t)hd * n + a) * gw + x : ((size_t)hd * gw + x) * n + a), Q, valid, k.col_pieces, col);
+  const int stride = KIND == 1 ? (int)(k.run * (unsigned)w0) | 1 : span;      // of an agent's part, of a cell's
+  if (b.blk && k.staged) {      // four loads in flight; floored here, once
+    const int per = cells * w0, count = (KIND == 1 ? 64 : span) * per;
+    const uint32_t inv = cells == (int)k.run ? k.inv_per : k.inv_last;
+    const int shift = 31 - __clz(span);
+    for (int i0 = threadIdx.x; i0 < count; i0 += 4 * 256) {
+      float v[4];
+      int at[4];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        const int i = min(i0 + 256 * m, count - 1), ai = KIND == 1 ? quotient(i, inv) : i & (span - 1), e = KIND == 1 ? i - ai * per : i >> shift;
+        const int ag = (KIND == 1 ? (int)(64 * li) : (int)wi * span) + ai, agc = min(ag, n - 1);
+        v[m] = KIND == 1 ? b.blk[((size_t)hd * n + agc) * h0 * w0 + (size_t)c0 * w0 + e] : b.blk[(((size_t)hd * h0 + c0) * w0 + e) * n + agc];
+        v[m] = ag < n ? v[m] : 0.f;
+        at[m] = KIND == 1 ? ai * stride + e : i;
+      }
+#pragma unroll
+      for (int m = 0; m < 4; ++m) lds[at[m]] = floored(v[m]);
+    }
+    __syncthreads();
+  }
+  if (KIND == 2 && x >= gw) return;
+  int x0[4], x1[4];
+  float fx[4];
+  if (KIND == 2) bilinear_coord(x, gw, w0, x0[0], x1[0], fx[0]);
+  const size_t cell_floats = (size_t)gw * NA;
+  for (int m = 0; m < Q; ++m) {
+    const int am = KIND == 1 ? a : a + 4 * m, xm = KIND == 1 ? x + 4 * m : x;
+    if (KIND == 1 ? xm >= gw : am >= (int)NA) return;
+    if (KIND == 1) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) bilinear_coord(min(xm + j, gw - 1), gw, w0, x0[j], x1[j], fx[j]);
+    }
+    const table4 cv = m == 0 ? col[0] : m == 1 ? col[1] : m == 2 ? col[2] : col[3];
+    float* to = k.half + ((size_t)hd * h0 + c0) * cell_floats +
+                (KIND == 1 ? ((size_t)(xm >> 2) * NA + am) * 4 : ((size_t)(am >> 2) * gw + xm) * 4);
+    const float* part = lds + (KIND == 1 ? lane * stride : 4 * Q * w + 4 * m);
+    for (int c = 0; c < cells; ++c, to += cell_floats) {
       float v[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const float f0 = floored(v0[j]), f1 = floored(v1[j]);
-        v[j] = out[j] + (f0 + (f1 - f0) * fx[j]);
+        float p0 = 0.f, p1 = 0.f;
+        const int xa = KIND == 1 ? x0[j] : x0[0], xb = KIND == 1 ? x1[j] : x1[0];
+        if (b.blk && k.staged) {
+          if (KIND == 1) p0 = part[c * w0 + xa], p1 = part[c * w0 + xb];
+          else p0 = part[(c * w0 + xa) * stride + j], p1 = part[(c * w0 + xb) * stride + j];
+        } else if (b.blk && (KIND == 1 ? am : am + j) < n) {
+          const float* p = KIND == 1 ? b.blk + (((size_t)hd * n + am) * h0 + c0 + c) * w0 : b.blk + ((size_t)hd * h0 + c0 + c) * w0 * n + am + j;
+          p0 = floored(KIND == 1 ? p[xa] : p[(size_t)xa * n]), p1 = floored(KIND == 1 ? p[xb] : p[(size_t)xb * n]);
+        }
+        v[j] = floored((cv[j] + (p0 + (p1 - p0) * (KIND == 1 ? fx[j] : fx[0]))) * kLog2e);
       }
-      if (c + 1 < c1) load(c + 1);
-      store(to, v);
+      *(table4*)to = table4{v[0], v[1], v[2], v[3]};
     }
-  };
-  if (which == 0) {            // tiles over (x/4, a) for each (hd, i); table index ((hd * he + i) * w/4 + x/4) * NA + a
-    const unsigned ta = NA >> 3, tx = (gwq + 7) >> 3, runs = (he + run1 - 1) / run1;
-    const unsigned a = 8 * (q % ta) + lo, t = q / ta, xq = 8 * (t % tx) + hi, t2 = t / tx, c0 = t2 % runs * run1, hd = t2 / runs;
-    if (xq >= gwq) return;
-    quad = ((size_t)(hd * he + c0) * gwq + xq) * NA + a;
-    const unsigned c1 = min(c0 + run1, he);
-    const int valid = (int)a < n ? 4 : 0;
-    const float *p0[4], *p1[4];
-    float fx[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (valid && b.col) out[j] = b.col[((size_t)hd * n + a) * gw + 4 * xq + j];
-      p0[j] = p1[j] = nullptr;
-      if (valid && b.blk) {
-        int x0, x1;
-        bilinear_coord((int)(4 * xq) + j, gw, w0, x0, x1, fx[j]);
-        const float* p = b.blk + (((size_t)hd * n + a) * h0 + c0) * w0;
-        p0[j] = p + x0, p1[j] = p + x1;
-      }
-    }
-    cells(half1 + quad * 4, (size_t)gwq * NA * 4, c0, c1, p0, p1, fx, (size_t)w0, b.blk ? valid : 0);
-    return;
-  } else if (which == 2) {     // tiles over (a/4, x) for each (hd, i); table index ((hd * he + i) * NA/4 + a/4) * w + x
-    const unsigned tx = ((unsigned)gw + 7) >> 3, taq = NAq >> 3, runs = (he + run2 - 1) / run2;
-    const unsigned x = 8 * (q % tx) + lo, t = q / tx, aq = 8 * (t % taq) + hi, t2 = t / taq, c0 = t2 % runs * run2, hd = t2 / runs;
-    if (x >= (unsigned)gw) return;
-    quad = ((size_t)(hd * he + c0) * NAq + aq) * gw + x;
-    const unsigned c1 = min(c0 + run2, he);
-    const int a = (int)(4 * aq), valid = min(max(n - a, 0), 4);
-    int x0 = 0, x1 = 0;
-    float f = 0.0f;
-    if (b.blk) bilinear_coord((int)x, gw, w0, x0, x1, f);
-    const float* p = b.blk ? b.blk + ((size_t)hd * h0 + c0) * w0 * n + a : nullptr;
-    const float fx[4] = {f, f, f, f};
-    const float *p0[4], *p1[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if (j < valid && b.col) out[j] = b.col[((size_t)hd * gw + x) * n + a + j];
-      p0[j] = p + (size_t)x0 * n + j, p1[j] = p + (size_t)x1 * n + j;
-    }
-    cells(half2 + quad * 4, (size_t)NAq * gw * 4, c0, c1, p0, p1, fx, (size_t)w0 * n, b.blk ? valid : 0);
-    return;
-  } else if (which == 1) {     // table index (hd * h + y) * NA/4 + a/4, 64 of them per tile
-    quad = (size_t)q * 64 + lane;
-    live = quad < q_rows;
-    const unsigned aq = (unsigned)(quad % NAq), t = (unsigned)(quad / NAq), y = t % (unsigned)gh, hd = t / (unsigned)gh;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int a = (int)(4 * aq) + j;
-      if (live && a < n && b.row) out[j] = b.row[((size_t)hd * n + a) * gh + y];
-    }
-    dst = rows1;
-  } else {                     // table index (hd * NA/4 + a/4) * h + y
-    quad = (size_t)q * 64 + lane;
-    live = quad < q_rows;
-    const unsigned y = (unsigned)(quad % (unsigned)gh), t = (unsigned)(quad / (unsigned)gh), aq = t % NAq, hd = t / NAq;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int a = (int)(4 * aq) + j;
-      if (live && a < n && b.row) out[j] = b.row[((size_t)hd * gh + y) * n + a];
-    }
-    dst = rows2;
   }
-  if (live) store(dst + quad * 4, out);
+}
+template <int KIND>
+__device__ __forceinline__ void half_row_block(const HalfKind& k, unsigned q, int n, int gh, unsigned NA) {
+  const BiasArgs& b = k.b;
+  const int Q = (int)k.row_quads, span = (int)(16 * Q) << k.row_group_log2, lane = (threadIdx.x & 63) & (63 >> k.row_group_log2);
+  const int w = (int)((threadIdx.x >> 6 << k.row_group_log2) + ((threadIdx.x & 63) >> (6 - k.row_group_log2)));
+  unsigned li, wi, run, hd;
+  k.row_part.place(q, li, wi, run, hd);
+  const int a = KIND == 1 ? (int)(64 * li) + lane : (int)wi * span + 4 * Q * w;
+  const int y = KIND == 1 ? (int)wi * span + 4 * Q * w : (int)(64 * li) + lane;
+  table4 v[4];
+  const int valid = a >= n || y >= gh ? 0 : KIND == 1 ? gh - y : n - a;
+  half_pieces(b.row + (KIND == 1 ? ((size_t)hd * n + a) * gh + y : ((size_t)hd * gh + y) * n + a), Q, valid, k.row_pieces, v);
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    if (m >= Q) continue;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[m][j] = floored(v[m][j] * kLog2e);
+    if (KIND == 1) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (y + 4 * m + j < gh) k.rows[((size_t)hd * gh + y + 4 * m + j) * NA + a] = v[m][j];
+    } else if (y < gh && a + 4 * m < (int)NA) {
+      *(table4*)(k.rows + (((size_t)hd * (NA >> 2) + (a >> 2) + m) * gh + y) * 4) = v[m];
+    }
+  }
+}
+__global__ __launch_bounds__(256) void bias_half_kernel(HalfKind k1, HalfKind k2, int n, int gh, int gw) {
+  extern __shared__ __align__(16) float half_lds[];
+  const unsigned NA = (unsigned)round_up64(n);
+  unsigned q = blockIdx.x;
+  if (q < k1.cells.count) return half_block<1>(k1, q, n, gw, NA, half_lds);
+  q -= k1.cells.count;
+  if (q < k2.cells.count) return half_block<2>(k2, q, n, gw, NA, half_lds);
+  q -= k2.cells.count;
+  if (q < k1.row_part.count) return half_row_block<1>(k1, q, n, gh, NA);
+  half_row_block<2>(k2, q - k1.row_part.count, n, gh, NA);
 }
 
 size_t bias_half_floats(int heads, int n, int gw, int he) { return (size_t)heads * round_up64(n) * he * gw; }
 size_t bias_rows_floats(int heads, int n, int gh) { return (size_t)heads * round_up64(n) * gh; }
 
 hipError_t launch_bias_half(const Problem& p, float* half1, float* rows1, float* half2, float* rows2, hipStream_t st) {
-  // threads per segment: 64 per 8 x 8 tile (ragged tiles along x included); the caller keeps every table
-  // below 2 GiB, so 32-bit counts suffice
-  const unsigned NA = (unsigned)round_up64(p.n), gwq = (unsigned)p.gw >> 2;
-  auto tiles = [&](int he, bool kind1) {
-    return kind1 ? (unsigned)p.heads * he * ((gwq + 7) / 8) * (NA / 8) : (unsigned)p.heads * he * (((unsigned)p.gw + 7) / 8) * (NA / 32);
+  // the caller keeps every table below 2 GiB, so 32-bit counts suffice
+  const unsigned NA = (unsigned)round_up64(p.n), H = (unsigned)p.heads;
+  constexpr int kStageFloats = 8192;
+  int lds = 0;
+  auto kind = [&](const BiasArgs& b, float* half, float* rows, bool first) {
+    HalfKind k{};
+    k.b = b, k.half = half, k.rows = rows;
+    const int h0 = b.blk ? b.h0 : 1, w0 = b.blk ? b.w0 : 1;
+    auto group = [&](int length) {
+      unsigned g = 0;
+      while (!first && (length << (g + 1)) <= 64 && 16u << (g + 1) <= NA) ++g;
+      return g;
+    };
+    k.group_log2 = group(p.gw), k.row_group_log2 = group(p.gh);
+    auto blocks = [&](int length, unsigned quads, unsigned runs) {      // along `length` columns or image rows
+      const unsigned span = (16 * quads) << group(length);
+      HalfBlocks n{0, first ? NA >> 6 : ((unsigned)length + 63) >> 6, ((first ? (unsigned)length : NA) + span - 1) / span, runs, 0, 0, 0};
+      n.count = H * n.inner * n.outer * runs;
+      auto inverse = [&](unsigned by) { return (unsigned long long)n.count * by >> 32 == 0 ? quotient_inverse((int)by) : 0u; };
+      n.inv_inner = inverse(n.inner), n.inv_outer = inverse(n.outer), n.inv_runs = inverse(runs);
+      return n;
+    };
+    // The widest pieces that leave two blocks a CU, and as many cell rows a block as leave one and fit LDS.  Kernel alone in us, one
+    // block for the pieces / this / four, and this with two blocks a CU left by the cell rows; 7 cell rows: 8 heads of 128 x 128
+    // tokens x 1024 agents 19.8 / 19.9 / 20.2, 23.8; 8 of 80 x 100 x 256 12.7 / 8.0 / 7.6, 12.1; 4 of 96 x 96 x 576 13.4 / 8.7 / 8.0,
+    // 12.2; 8 of 17 x 40 x 160 6.5 / 5.1 / 5.1, 5.6; 8 of 128 x 4 x 66 4.1 / 4.2 / 4.8, 4.1.
+    auto widest = [&](int length, int cell_rows) {
+      unsigned quads = 4;
+      while (quads > 1 && blocks(length, quads, cell_rows).count < 2u * kComputeUnits) quads /= 2;
+      return quads;
+    };
+    k.quads = widest(p.gw, h0), k.row_quads = widest(p.gh, 1);
+    auto floats = [&](int run) { return first ? 64 * ((run * w0) | 1) : ((16 * (int)k.quads) << k.group_log2) * run * w0; };
+    int run = std::max(1, std::min(h0, (int)(blocks(p.gw, k.quads, h0).count / (unsigned)kComputeUnits)));
+    while (run > 1 && floats(run) > kStageFloats) --run;
+    const int runs = (h0 + run - 1) / run;
+    k.run = (unsigned)run;
+    k.staged = b.blk && run > 1 && floats(run) <= kStageFloats;      // (a single one is asked for beside the column component)
+    k.inv_per = quotient_inverse(run * w0), k.inv_last = quotient_inverse((h0 - (runs - 1) * run) * w0);
+    auto pieces = [&](const float* from, int length) { return ((uintptr_t)from % 16 == 0 && (first ? length : p.n) % 4 == 0) ? 1u : 0u; };
+    k.col_pieces = pieces(b.col, p.gw), k.row_pieces = pieces(b.row, p.gh);
+    if (half) {
+      k.cells = blocks(p.gw, k.quads, runs);
+      if (k.staged) lds = std::max(lds, floats(run) * 4);
+    }
+    if (rows) k.row_part = blocks(p.gh, k.row_quads, 1);
+    return k;
   };
-  // as many cell rows a thread as leave a wave a SIMD
-  auto run_of = [&](int he, bool kind1) { return std::max(1, std::min(he, (int)(tiles(he, kind1) / (4u * kComputeUnits)))); };
-  const int he1 = p.b1.blk ? p.b1.h0 : 1, he2 = p.b2.blk ? p.b2.h0 : 1, run1 = run_of(he1, true), run2 = run_of(he2, false);
-  const unsigned q_half1 = 64u * tiles((he1 + run1 - 1) / run1, true);
-  const unsigned q_half2 = 64u * tiles((he2 + run2 - 1) / run2, false);
-  const unsigned q_rows = (unsigned)(bias_rows_floats(p.heads, p.n, p.gh) / 4), q_rows64 = (q_rows + 63u) & ~63u;
-  const size_t total = (size_t)(half1 ? q_half1 : 0) + (rows1 ? q_rows64 : 0) + (half2 ? q_half2 : 0) + (rows2 ? q_rows64 : 0);
+  const HalfKind k1 = kind(p.b1, half1, rows1, true), k2 = kind(p.b2, half2, rows2, false);
+  const unsigned total = k1.cells.count + k2.cells.count + k1.row_part.count + k2.row_part.count;
   if (total == 0) return hipSuccess;
-  bias_half_kernel<<<dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st>>>(p.b1, half1, rows1, p.b2, half2, rows2,
-                                                                               p.n, p.gh, p.gw, q_half1, q_half2, q_rows, (unsigned)run1, (unsigned)run2);
+  bias_half_kernel<<<dim3(total), dim3(256), (size_t)lds, st>>>(k1, k2, p.n, p.gh, p.gw);
   return hipGetLastError();
 }
 
