@@ -12,6 +12,7 @@
 #include <initializer_list>
 #include <mutex>
 
+#include "columns_rule.h"
 #include "kernels.h"
 
 // Workspace of agent_attn_fwd_static(): one array per GPU, reserved when the library's code object is loaded
@@ -207,7 +208,8 @@ constexpr size_t kBiasDenseCapBytes = (size_t)2 << 30;
 
 int padded_width(int d);
 
-BiasPlan plan_bias(const aa_desc* d, const aa_params* params) {
+// small: the matrix form wherever it exists, its tables being the smaller ones
+BiasPlan plan_bias(const aa_desc* d, const aa_params* params, bool small = false) {
   BiasPlan bp;
   size_t off = 0;
   const bool tables_ok = d->grid_h > 0 && d->dtype != AA_F32;      // the MFMA kernels are the ones that read them
@@ -224,10 +226,11 @@ BiasPlan plan_bias(const aa_desc* d, const aa_params* params) {
       const bool blk = kind == 1 ? params->b1_blk != nullptr : params->b2_blk != nullptr;
       const bool row = kind == 1 ? params->b1_row != nullptr : params->b2_row != nullptr;
       // B1's block component goes through the matrix pipe (two more k-steps of the aggregation's score products)
-      // when its grid has at most 64 cells and the head width pads to 64; the half-resized table then holds the
-      // column component only.  (Not B2: in the broadcast's orientation a lane owns a token, the column and row
+      // when its grid has at most 64 cells, the head width pads to 64 and the aggregation takes its tokens in rows (up to 256
+      // agents, say: large_aggregate_columns); the half-resized table then holds the column component only.  (Not B2: in the broadcast's orientation a lane owns a token, the column and row
       // pieces it needs per agent tile stay the same 16-byte loads, and the same change measured no gain there.)
-      const bool matrix = kind == 1 && blk && params->blk_h0 * params->blk_w0 <= 64 && padded_width(d->d) == 64;
+      const bool matrix = kind == 1 && blk && params->blk_h0 * params->blk_w0 <= 64 && padded_width(d->d) == 64 &&
+                          (small || !aa::large_aggregate_columns(64, d->n, d->grid_h, d->grid_w, params->blk_h0));
       if (matrix) {
         bp.WT = off;
         off += align_up(aa::bias_wt_bytes(d->N));
@@ -271,7 +274,8 @@ bool few_biased_tokens(const Problem& p) {
   return p.d <= 64 ? tokens <= 1024 || p.N <= 256 : p.N <= 256 && tokens <= 2048;
 }
 
-// small: without the fp32 kernels' bias tables and partial sums (callers with a workspace of fixed size)
+// small: without the fp32 kernels' bias tables and partial sums, with the smaller form of the 16-bit ones (callers with a workspace
+// of fixed size)
 Plan make_plan(const aa_desc* d, const aa_params* params = nullptr, bool small = false) {
   Plan pl{};
   const size_t units = (size_t)units_of(d);
@@ -316,7 +320,7 @@ Plan make_plan(const aa_desc* d, const aa_params* params = nullptr, bool small =
     pl.off_stage = off;
     off += 4 * pl.stage_bytes;
   }
-  pl.bias = plan_bias(d, params);
+  pl.bias = plan_bias(d, params, small && !(params && params->bias_tables));      // (tables brought along have their form)
   pl.off_bias = off;
   if (!(params && params->bias_tables)) off += pl.bias.total;      // prepared tables need no room here
   pl.off_f32 = kNoStage;

@@ -1,4 +1,4 @@
-// Which forward broadcasts take their tokens in columns (16 image columns of some image rows a wave) and which in rows (runs of
+// Which forward kernels take their tokens in columns (16 image columns of some image rows a wave) and which in rows (runs of
 // consecutive tokens).  Plain C++ with no GPU dependency, so that the rules can be tested on a machine without a GPU.
 #pragma once
 #include <algorithm>
@@ -35,6 +35,21 @@ inline int large_column_parts(int n, int gh, int cells) {
   if (cells > 64 || (long long)((n + 63) / 64 * 64) * gh * 4 >= (1ll << 31)) return 0;
   const int parts = std::min(cells, (kColumnRows - 1) * cells / gh + 3);
   return parts <= kMaxColumnParts ? parts : 0;
+}
+// --- many agents, aggregation (large_aggregate_cols_kernel), with half-resized bias tables ---
+// A tile is 16 columns x 4 image rows whatever the image: not where more than half as many places again would lie beside it.  Up to 64
+// padded channels the kernels in rows run four waves a block up to 256 agents, which is as fast (whole forward, rows / columns in
+// us, d = 64: 16 units of 80 x 100 tokens x 256 agents 114 / 119, 96 of 77 x 40 x 81 161 / 166; d = 32 79 / 79, 89 / 92); above, a
+// tile should seldom lie across cell rows (d = 64: 4 of 96 x 96 x 576 82 / 76, 24 of 90 x 36 x 360 98 / 94; 3 of 50 x 52 x 400, seven
+// image rows a cell row, 58 / 62).  At 128 columns were never slower (192 of 24 x 24 x 144 353 / 252, 4 of 7 x 100 x 90 83 / 72).
+// 32-bit offsets: in a head's table and row component, and of a tile's last image row in a unit (which is below 2 GiB) from its
+// first.
+inline bool large_aggregate_columns(int padded_width, int n, int gh, int gw, int cells) {
+  const long long ld = (n + 63) / 64 * 64;
+  if (gw % 4 != 0 || gh < 4 || cells * (gw / 4) * ld * 16 >= (1ll << 31) || gh * ld * 4 >= (1ll << 31)) return false;
+  const long long tokens = (long long)((gw + 15) / 16 * 16) * ((gh + 3) / 4 * 4);
+  if (padded_width <= 64 && (n <= 256 || gh < 10 * cells)) return false;
+  return 2 * tokens <= 3ll * gh * gw;
 }
 inline long long large_column_blocks(int gh, int gw) {
   return (long long)((gw + 15) / 16) * ((gh + kColumnRows - 1) / kColumnRows);

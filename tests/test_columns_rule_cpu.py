@@ -57,3 +57,17 @@ def test_narrow_images_stay_in_rows(rules, units, grid, n, d, cells):
 @pytest.mark.parametrize("units,grid,n,d,cells", COLUMNS)
 def test_images_that_fill_the_blocks_go_in_columns(rules, units, grid, n, d, cells):
     assert columns_rule.large_parts(rules, grid, n, d, units, cells) > 0
+
+
+# (grid, agents, d, cell rows): the aggregation in rows / in columns
+@pytest.mark.parametrize("grid,n,d,cells,columns", [((128, 128), 1024, 64, 7, True), ((128, 128), 256, 64, 7, False), ((70, 48), 257, 32, 7, True),
+                                                    ((69, 48), 257, 32, 7, False), ((7, 100), 90, 128, 7, True), ((3, 100), 90, 128, 1, False),
+                                                    ((64, 12), 96, 128, 7, True), ((64, 20), 96, 128, 7, False), ((5, 16), 70, 96, 7, False),
+                                                    ((40, 18), 96, 128, 4, False)])
+def test_aggregation_in_columns(rules, grid, n, d, cells, columns):
+    assert columns_rule.aggregate_columns(rules, grid, n, d, cells) == columns
+
+
+def test_aggregation_offsets_fit_32_bits(rules):
+    assert rules.large_aggregate_columns(128, 1 << 16, 64, 512, 7) and not rules.large_aggregate_columns(128, 1 << 16, 64, 512, 16)
+    assert not rules.large_aggregate_columns(128, 1 << 20, 512, 16, 7) and rules.large_aggregate_columns(128, 1 << 20, 508, 16, 7)
