@@ -52,31 +52,37 @@ __global__ __launch_bounds__(kThreads) void fused_merge_kernel(SumRows g, const 
   int row, c;
   size_t first;
   const bool ok = g.place(row, c, first);
-  float M = -INFINITY;
-  for (int s0 = 0; s0 < g.S; s0 += 8) {
-    float m[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) m[k] = load_global<float>(pm + first + (size_t)min(s0 + k, g.S - 1) * g.n);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) M = fmaxf(M, m[k]);
-  }
-  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  // the rows of eight ranges and their references and weights are asked for together; the references of later ranges before
+  float M = -INFINITY, m[8], l[8];
+  f32x4 v = {0.f, 0.f, 0.f, 0.f}, x[8];
   float L = 0.f;
-  for (int s0 = 0; s0 < g.S; s0 += 8) {
-    float m[8], l[8];
-    f32x4 x[8];
+  auto fetch = [&](int s0) {
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
       const size_t at = first + (size_t)min(s0 + k, g.S - 1) * g.n;
       m[k] = load_global<float>(pm + at), l[k] = load_global<float>(pl + at);
       x[k] = row4(acc, at, g.d, c < g.d ? c : 0);
     }
+  };
+  fetch(0);
+  for (int s0 = 8; s0 < g.S; s0 += 8) {
+    float later[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) later[k] = load_global<float>(pm + first + (size_t)min(s0 + k, g.S - 1) * g.n);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) M = fmaxf(M, later[k]);
+  }
+#pragma unroll
+  for (int k = 0; k < 8; ++k) M = fmaxf(M, m[k]);
+  for (int s0 = 0;;) {
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
       const float w = s0 + k < g.S ? fast_exp2(m[k] - M) : 0.f;
       L = fmaf(l[k], w, L);
       v += x[k] * w;
     }
+    if ((s0 += 8) >= g.S) break;
+    fetch(s0);
   }
   if (!ok) return;
   v *= 1.0f / L;
