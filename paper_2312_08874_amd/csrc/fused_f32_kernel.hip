@@ -1,8 +1,8 @@
 // Whole forward pass of one (batch, head) unit in ONE launch for fp32 tensors whose unit fits in LDS
-// (Eq. (3), (5), (6); Sec. 4.2 pooling): block = unit, 16 waves.  The unit's Q, K and V rows are read from
-// memory once into LDS; pooling, both softmax attentions (flash style, nothing of size n x N is stored), the
-// merge of the token slices, DWC and k*V all work out of LDS, and only O goes back to memory.  All products
-// are fp32 MFMAs (v_mfma_f32_16x16x4_f32, fp32 inputs, fp32 accumulation).
+// (Eq. (3), (5), (6); Sec. 4.2 pooling): block = unit, or a share of its output where units are few; 16 waves.
+// The unit's Q, K and V rows are read from memory once into LDS; pooling, both softmax attentions (flash style,
+// nothing of size n x N is stored), the merge of the token slices, DWC and k*V all work out of LDS, and only O
+// goes back to memory.  All products are fp32 MFMAs (v_mfma_f32_16x16x4_f32, fp32 inputs, fp32 accumulation).
 //
 // Operand conventions of that instruction (r = lane % 16, g = lane / 16): the A operand is element
 // [row r][k = g], the B operand element [k = g][column r], C/D holds column r, rows 4g..4g+3.  A lane reads
@@ -10,6 +10,8 @@
 // then stands for channel 4g + j in BOTH operands, so the contraction is merely taken in another order.
 // The same trick turns the C registers of a score tile (rows = 4 consecutive tokens or agents per lane)
 // into the B operand of the following value product without any data movement.
+#include <algorithm>
+
 #include "kernels.h"
 #include "mfma_common.h"
 
@@ -42,20 +44,25 @@ __device__ __forceinline__ float group_sum(float v) {
 
 // LDS row stride in floats: the 16*DT padded channels plus 4, so that the 16 rows x 4 pieces of an operand
 // read fall into 64 different banks.
-template <int DT>
+template <int DT, int CT>
 struct F32Geo {
   static constexpr int RS = 16 * DT + 4;
-  static constexpr int PART = 16 * 16 * DT + 32;      // floats of one (agent tile, token slice) partial
+  static constexpr int PART = 16 * 16 * CT + 32;      // floats of one (agent tile, token slice) partial
 };
 
-template <int NAT, int DT, bool MODULE>
+// CT: 16-channel tiles of V, V_A and O that a block takes (blockIdx.z: which), of DT; 0: a block takes the whole unit (its own code,
+// as the bounds of a share cost 3 % where units of 440 tokens of 16 channels fill the chip: 14.2 -> 14.6 us for 192 of them)
+template <int NAT, int DT, bool MODULE, int CTS>
 __global__ __launch_bounds__(64 * kF32Waves) void fused_f32_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     const float* __restrict__ Agiven, float* __restrict__ O, const float* __restrict__ dwc_w,
     const float* __restrict__ dwc_b, float sc1, float sc2, float vk, int N, int n, int d, int heads, Layout lay, int gh,
-    int gw, int ah, int aw, int S) {
+    int gw, int ah, int aw, int S, int share) {      // share: tiles of tokens a block writes, from share * blockIdx.y on
   extern __shared__ __attribute__((aligned(16))) float smem_f32[];
-  constexpr int RS = F32Geo<DT>::RS, PART = F32Geo<DT>::PART, C4 = RS / 4;
+  constexpr bool kWhole = CTS == 0;
+  constexpr int CT = kWhole ? DT : CTS;
+  constexpr int RS = F32Geo<DT, CT>::RS, PART = F32Geo<DT, CT>::PART, C4 = RS / 4;
+  const int cb = kWhole ? 0 : 16 * CT * blockIdx.z;
   const int ntiles = (N + 15) / 16, rows = 16 * ntiles;
   float* Q_lds = smem_f32;
   float* K_lds = Q_lds + (size_t)rows * RS;
@@ -169,9 +176,9 @@ __global__ __launch_bounds__(64 * kF32Waves) void fused_f32_kernel(
 #pragma unroll
     for (int kc = 0; kc < DT; ++kc) areg[kc] = *(const f32x4*)(A_lds + agent * RS + 16 * kc + 4 * g) * c1;
     float m = -INFINITY, l = 0.0f;
-    f32x4 acc[DT];
+    f32x4 acc[CT];
 #pragma unroll
-    for (int ct = 0; ct < DT; ++ct) acc[ct] = f32x4{0, 0, 0, 0};
+    for (int ct = 0; ct < CT; ++ct) acc[ct] = f32x4{0, 0, 0, 0};
     const int tile_end = min(ntiles, (s + 1) * tps);
     for (int tile = s * tps; tile < tile_end; ++tile) {
       const int t0 = 16 * tile;
@@ -199,49 +206,50 @@ __global__ __launch_bounds__(64 * kF32Waves) void fused_f32_kernel(
       l = l * alpha + (p[0] + p[1]) + (p[2] + p[3]);      // this lane's four tokens; the groups are added at the end
       // V_A^T tile += V^T P^T: rows = channels 16ct + 4g + i, column = agent; k slot g of product j = token t0 + 4g + j
 #pragma unroll
-      for (int ct = 0; ct < DT; ++ct) acc[ct] *= alpha;
+      for (int ct = 0; ct < CT; ++ct) acc[ct] *= alpha;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const float* vrow = V_lds + (size_t)(t0 + 4 * g + j) * RS + r;
+        const float* vrow = V_lds + (size_t)(t0 + 4 * g + j) * RS + cb + r;
 #pragma unroll
-        for (int ct = 0; ct < DT; ++ct) acc[ct] = mma4(vrow[16 * ct], p[j], acc[ct]);
+        for (int ct = 0; ct < CT; ++ct) acc[ct] = mma4(vrow[16 * ct], p[j], acc[ct]);
       }
 #pragma unroll
-      for (int ct = 0; ct < DT; ++ct) mfma_results_ready(acc[ct]);      // read by the rescaling of the next tile / the stores
+      for (int ct = 0; ct < CT; ++ct) mfma_results_ready(acc[ct]);      // read by the rescaling of the next tile / the stores
     }
     l = group_sum(l);
     float* dst = part + (size_t)item * PART;
 #pragma unroll
-    for (int ct = 0; ct < DT; ++ct)
+    for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
       for (int i = 0; i < 4; ++i) dst[(16 * ct + 4 * g + i) * 16 + r] = acc[ct][i];
     if (g == 0) {
-      dst[256 * DT + r] = m;
-      dst[256 * DT + 16 + r] = l;
+      dst[256 * CT + r] = m;
+      dst[256 * CT + 16 + r] = l;
     }
   }
   __syncthreads();
   // merge of the slices (log-sum-exp, fixed order): thread = (agent, channel)
-  for (int idx = tid; idx < 16 * NAT * 16 * DT; idx += blockDim.x) {
+  for (int idx = tid; idx < 16 * NAT * 16 * CT; idx += blockDim.x) {
     // the 16 agents of a tile vary fastest: consecutive LDS addresses in the partials, stride RS in V_A (both conflict free)
-    const int a16 = idx & 15, c = (idx >> 4) % (16 * DT), at = idx / (256 * DT), a = 16 * at + a16;
+    const int a16 = idx & 15, c = (idx >> 4) % (16 * CT), at = idx / (256 * CT), a = 16 * at + a16;
     float M = -INFINITY;
 #pragma unroll 4
-    for (int s = 0; s < S; ++s) M = fmaxf(M, part[(size_t)(s * NAT + at) * PART + 256 * DT + a16]);
+    for (int s = 0; s < S; ++s) M = fmaxf(M, part[(size_t)(s * NAT + at) * PART + 256 * CT + a16]);
     float num = 0.0f, den = 0.0f;
 #pragma unroll 4
     for (int s = 0; s < S; ++s) {
       const float* src = part + (size_t)(s * NAT + at) * PART;
-      const float w = fast_exp2(src[256 * DT + a16] - M);
+      const float w = fast_exp2(src[256 * CT + a16] - M);
       num += w * src[c * 16 + a16];
-      den += w * src[256 * DT + 16 + a16];
+      den += w * src[256 * CT + 16 + a16];
     }
     VA_lds[a * RS + c] = num * __builtin_amdgcn_rcpf(den);      // 1 ulp reciprocal: far inside the fp32 bar
   }
   __syncthreads();
 
   // ---- agent broadcast O = softmax(s2 Q A^T + B2) V_A (+ DWC(V) + k V): work item = 16-token tile ----
-  for (int tile = wave; tile < ntiles; tile += kF32Waves) {
+  const int share_start = kWhole ? 0 : share * (int)blockIdx.y, share_end = kWhole ? ntiles : min(ntiles, share_start + share);
+  for (int tile = share_start + wave; tile < share_end; tile += kF32Waves) {
     const int t0 = 16 * tile, tok = t0 + r, tokc = min(tok, N - 1);
     f32x4 qreg[DT];
     const float c2 = sc2 * kLog2eF;
@@ -286,24 +294,24 @@ __global__ __launch_bounds__(64 * kF32Waves) void fused_f32_kernel(
       }
     l = group_sum(l);
     // O^T tile = V_A^T P^T: rows = channels 16ct + 4g + i, column = token
-    f32x4 o[DT];
+    f32x4 o[CT];
 #pragma unroll
-    for (int ct = 0; ct < DT; ++ct) o[ct] = f32x4{0, 0, 0, 0};
+    for (int ct = 0; ct < CT; ++ct) o[ct] = f32x4{0, 0, 0, 0};
 #pragma unroll
     for (int at = 0; at < NAT; ++at)
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const float* varow = VA_lds + (16 * at + 4 * g + j) * RS + r;
 #pragma unroll
-        for (int ct = 0; ct < DT; ++ct) o[ct] = mma4(varow[16 * ct], sc[at][j], o[ct]);
+        for (int ct = 0; ct < CT; ++ct) o[ct] = mma4(varow[16 * ct], sc[at][j], o[ct]);
       }
 #pragma unroll
-    for (int ct = 0; ct < DT; ++ct) mfma_results_ready(o[ct]);
+    for (int ct = 0; ct < CT; ++ct) mfma_results_ready(o[ct]);
     const float inv = __builtin_amdgcn_rcpf(l);
 #pragma unroll
-    for (int ct = 0; ct < DT; ++ct) {
+    for (int ct = 0; ct < CT; ++ct) {
       f32x4 out = o[ct] * inv;
-      const int ch = 16 * ct + 4 * g;
+      const int ch = cb + 16 * ct + 4 * g;
       if constexpr (MODULE) {
         if (ch < d) {
           if (dwc_w) {      // Eq. (6): 3x3 depthwise convolution of V, zero padded at the border of the grid
@@ -326,9 +334,9 @@ __global__ __launch_bounds__(64 * kF32Waves) void fused_f32_kernel(
   }
 }
 
-size_t fused_f32_lds(int N, int nat, int dt, int S) {
+size_t fused_f32_lds(int N, int nat, int dt, int ct, int S) {
   const size_t rows = (size_t)(N + 15) / 16 * 16, rs = 16 * (size_t)dt + 4;
-  return (3 * rows * rs + 2 * 16 * (size_t)nat * rs + (size_t)nat * S * (256 * (size_t)dt + 32) + 160 * (size_t)dt) * sizeof(float);
+  return (3 * rows * rs + 2 * 16 * (size_t)nat * rs + (size_t)nat * S * (256 * (size_t)ct + 32) + 160 * (size_t)dt) * sizeof(float);
 }
 // token slices of the aggregation: as many as there are waves for the agent tiles, tiles of tokens, and room in LDS
 int fused_f32_slices(const Problem& p) {
@@ -336,7 +344,7 @@ int fused_f32_slices(const Problem& p) {
   int S = kF32Waves / nat;
   if (S > ntiles) S = ntiles;
   if (S < 1) S = 1;
-  while (S > 1 && fused_f32_lds(p.N, nat, dt, S) > 160 * 1024) --S;
+  while (S > 1 && fused_f32_lds(p.N, nat, dt, dt, S) > 160 * 1024) --S;
   return S;
 }
 
@@ -349,33 +357,43 @@ int fused_f32_slices(const Problem& p) {
 bool fused_f32_supported(const Problem& p) {
   if (p.dtype != 0 || p.d % 4 != 0 || p.d > 64 || p.n > 64 || p.N > (1 << 16)) return false;
   if (p.b1.any() || p.b2.any()) return false;
-  return fused_f32_lds(p.N, (p.n + 15) / 16, (p.d + 15) / 16, fused_f32_slices(p)) <= 160 * 1024;
+  return fused_f32_lds(p.N, (p.n + 15) / 16, (p.d + 15) / 16, (p.d + 15) / 16, fused_f32_slices(p)) <= 160 * 1024;
 }
 
 hipError_t launch_fused_f32(const Problem& p, const void* Q, const void* K, const void* V, const void* A, void* out,
                             hipStream_t st) {
   const int nat = (p.n + 15) / 16, dt = (p.d + 15) / 16;
   const int S = fused_f32_slices(p);
-  const size_t lds = fused_f32_lds(p.N, nat, dt, S);
   const bool mod = p.dwc_w != nullptr || p.vk != 0.0f;
+  // Blocks per unit: while CUs are idle, further blocks repeat what comes before the broadcast and share out its tiles of 16 tokens,
+  // down to one per SIMD, and the channels of V, one 16-channel tile each (or two of four).  The same sums in the same order.
+  // 1 unit of 196 tokens x 49 agents, d = 32: 15.0 us in one block, 11.8 in four, 10.5 in eight (tiles and channels).
+  const int ntiles = (p.N + 15) / 16, share = (ntiles - 1) / std::max(1, std::min((ntiles + 3) / 4, kComputeUnits / p.units)) + 1;
+  const int parts = (ntiles - 1) / share + 1;
+  int ct = 1;
+  while (ct < dt && (dt % ct != 0 || dt / ct * parts * p.units > kComputeUnits)) ++ct;
+  const size_t lds = fused_f32_lds(p.N, nat, dt, ct, S);
   hipError_t err = hipErrorInvalidValue;
   auto launch = [&](auto kernel) {
     err = allow_lds(kernel, lds);
     if (err == hipSuccess)
-      kernel<<<dim3(p.units), dim3(64 * kF32Waves), lds, st>>>((const float*)Q, (const float*)K, (const float*)V,
-                                                               (const float*)A, (float*)out, p.dwc_w, p.dwc_b,
-                                                               p.scale1, p.scale2, p.vk, p.N, p.n, p.d, p.heads, p.lay,
-                                                               p.gh, p.gw, p.ah, p.aw, S);
+      kernel<<<dim3(p.units, parts, dt / ct), dim3(64 * kF32Waves), lds, st>>>(
+          (const float*)Q, (const float*)K, (const float*)V, (const float*)A, (float*)out, p.dwc_w, p.dwc_b, p.scale1, p.scale2, p.vk, p.N,
+          p.n, p.d, p.heads, p.lay, p.gh, p.gw, p.ah, p.aw, S, share);
   };
-#define AA_F32_CASE(NAT, DT)                                         \
-  if (nat == NAT && dt == DT) {                                      \
-    if (mod) launch(fused_f32_kernel<NAT, DT, true>);                \
-    else launch(fused_f32_kernel<NAT, DT, false>);                   \
+  const int tiles = parts == 1 && ct == dt ? 0 : ct;
+#define AA_F32_TILES(NAT, DT, CT)                                                     \
+  if (nat == NAT && dt == DT && tiles == CT) {                                        \
+    if (mod) launch(fused_f32_kernel<NAT, DT, true, CT>);                             \
+    else launch(fused_f32_kernel<NAT, DT, false, CT>);                                \
   }
-#define AA_F32_ROW(NAT) AA_F32_CASE(NAT, 1) AA_F32_CASE(NAT, 2) AA_F32_CASE(NAT, 3) AA_F32_CASE(NAT, 4)
+#define AA_F32_ROW(NAT)                                                                                                \
+  AA_F32_TILES(NAT, 1, 0) AA_F32_TILES(NAT, 1, 1) AA_F32_TILES(NAT, 2, 0) AA_F32_TILES(NAT, 2, 1) AA_F32_TILES(NAT, 2, 2) \
+  AA_F32_TILES(NAT, 3, 0) AA_F32_TILES(NAT, 3, 1) AA_F32_TILES(NAT, 3, 3)                                               \
+  AA_F32_TILES(NAT, 4, 0) AA_F32_TILES(NAT, 4, 1) AA_F32_TILES(NAT, 4, 2) AA_F32_TILES(NAT, 4, 4)
   AA_F32_ROW(1) AA_F32_ROW(2) AA_F32_ROW(3) AA_F32_ROW(4)
 #undef AA_F32_ROW
-#undef AA_F32_CASE
+#undef AA_F32_TILES
   return err != hipSuccess ? err : hipGetLastError();
 }
 
