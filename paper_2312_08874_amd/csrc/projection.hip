@@ -3,10 +3,12 @@
 // The library's product wrote Y without the bias and another kernel went over Y again, element by element, and the
 // windows of an image were copied to window-major tensors and back around the attention.  Here the bias is the
 // accumulators' first value, so that Y is rounded once, and rows of windows are read and written where the attention
-// keeps them.  Small widths are bound by memory, for which three or four blocks per CU keep enough loads in flight; large
-// ones by the LDS reads of the operands, which a wave's 64 x 64 tile brings level with its products.  Measured, library +
-// bias (+ copies of windows) against this kernel: 100352 rows in windows, width 96: q | k | v 49 + 45 + 30 -> 25 us
-// (3.1 TB/s), output 28 + 17 + 9 -> 12; 16384 rows, width 512: 45 + 38 -> 40 us (640 TFLOP/s), 15 + 15 -> 17.
+// keeps them.  What bounds them is the way of the operands to LDS (a product's step waits for loads asked for one step
+// before; products, loads and stores alone take 22, 20 and 15 of 42 us at 16384 rows of width 512): direct loads need no
+// registers, so that as many blocks as LDS holds share a CU.  Library + bias (+ copies of windows), operands through
+// registers (three blocks of 36 KB per CU), direct loads: 100352 rows in windows, width 96: q | k | v 49 + 45 + 30 -> 25 ->
+// 19 us (4.1 TB/s), output 28 + 17 + 9 -> 12.6 -> 10.4; 16384 rows, width 512: 45 + 38 -> 43.7 -> 41.7 us (620 TFLOP/s),
+// 15 + 15 -> 18.8 -> 15.2.
 #include "kernels.h"
 #include "mfma_common.h"
 
@@ -16,9 +18,6 @@ namespace aa {
 
 namespace {
 
-constexpr int kThreads = 256;      // four waves per block
-constexpr int kStep = 64;          // channels of X and W in LDS at a time
-constexpr int kLst = kStep + 8;    // LDS row stride in elements: 16-byte reads of 16 rows are free of bank conflicts
 
 struct ProjArgs {
   const uint16_t *X, *W, *b;
@@ -26,10 +25,11 @@ struct ProjArgs {
   int M, O, K;
   ProjRows x, y;
   XcdGrid grid;
+  long long bytes() const { return 2ll * M * (K + O); }      // of X and Y
 };
 
 // Where row m (token m % tokens of image m / tokens) lies: a base for the rows from m0 on and this row's offset from it
-// (an image has fewer than 2^30 elements, so that the 128 rows of a block and the images around them fit 32 bits).
+// (an image has fewer than 2^30 elements, so that the rows of a block and the two images around them, in bytes, fit 32 bits).
 __device__ __forceinline__ size_t rows_base(const ProjRows& p, int m0) {
   return p.ww == 0 ? (size_t)m0 * p.ld : (size_t)quotient(m0, p.inv_tokens) * p.wyn * p.wxn * p.heads * p.head_elems;
 }
@@ -46,88 +46,103 @@ __device__ __forceinline__ size_t channel_place(const ProjRows& p, int c) {
   return part * p.part_elems + (size_t)hd * p.head_elems + (in - hd * p.d);
 }
 
-// uniform base, this lane's element offset (below 2^31)
-__device__ __forceinline__ u32x4 load16(const uint16_t* base, unsigned at) {
-  typedef const __attribute__((address_space(1))) char* bytes;
-  return *(const __attribute__((address_space(1))) u32x4*)((bytes)base + (size_t)at * 2);
+#define AA_LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
+// all but the youngest N of this wave's loads have arrived and its LDS reads are done
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
+  asm volatile("" ::: "memory");
 }
 
 // Block: BM rows of X times BN rows of W, WN waves along W.  A wave's tiles hold 16 outputs x 16 rows of X; two of
 // them take every other four outputs, so that a lane holds eight neighbours of a row of Y, one 16-byte store.
 // The blocks of the same rows of X are on one XCD (W, at most a few MB, is in every L2).
-template <class E, int BM, int BN, int WN>
-__global__ __launch_bounds__(kThreads, BM == 128 && BN == 128 ? 3 : 4) void projection_kernel(ProjArgs a) {
-  constexpr int WM = 4 / WN, TM = BM / WM / 16, TN = BN / WN / 16;
-  constexpr int PX = BM * 8 / kThreads, PW = BN * 8 / kThreads;      // 16-byte pieces per thread and step
-  __shared__ __align__(16) uint16_t xs[BM * kLst], ws[BN * kLst];
+// Both operands go to LDS by direct loads, KS channels at a time into a ring of NS stages (two or three); piece c of row R lies in slot
+// c ^ swz(R), which spreads the 16 rows of an operand read over all banks.
+template <class E, int BM, int BN, int NW, int WN, int KS, int NS, int OCC>
+__global__ __launch_bounds__(64 * NW, OCC) void projection_kernel(ProjArgs a) {
+  constexpr int WM = NW / WN, TM = BM / WM / 16, TN = BN / WN / 16;
+  constexpr int PPR = KS / 8, RPL = 64 / PPR;              // 16-byte pieces per row, rows per wave-wide load
+  constexpr int LX = BM / (NW * RPL), LW = (BN / RPL + NW - 1) / NW;      // loads per wave and step
+  constexpr bool kEven = BN % (NW * RPL) == 0;      // else the last load of W's tile is the first half of the waves' alone
+  constexpr int RB = 2 * KS, kStage = (BM + BN) * RB;
+  constexpr unsigned kNone = 0xffffffffu;      // past every buffer: the piece is zeros
+  static_assert(LX * NW * RPL == BM && (kEven || (LW * NW - NW / 2) * RPL == BN) && TN % 2 == 0, "whole loads");
+  extern __shared__ __align__(1024) unsigned char smem[];
   int rows, cols;
   if (!a.grid.decode(blockIdx.x, rows, cols)) return;
   const int m0 = rows * BM, o0 = cols * BN;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6), wm = w / WN, wn = w % WN;
-  const int pr = tid >> 3, pc = (tid & 7) * 8;      // this thread's pieces: rows pr + 32 j, channel pc
-
-  // rows past the last are read from the last one: they do not reach Y
-  const uint16_t *Xb = a.X + rows_base(a.x, m0), *Wb = a.W + (size_t)o0 * a.K;
-  unsigned px[PX], pw[PW];
-#pragma unroll
-  for (int j = 0; j < PX; ++j) px[j] = row_offset(a.x, m0, min(m0 + pr + 32 * j, a.M - 1));
-#pragma unroll
-  for (int j = 0; j < PW; ++j) pw[j] = (unsigned)min(pr + 32 * j, a.O - 1 - o0) * (unsigned)a.K;
-  u32x4 vx[PX], vw[PW];
-  auto fetch = [&](int k0) {      // channels past the last are zeros
-    const bool ok = k0 + pc < a.K;
-    const int k = ok ? k0 + pc : 0;
-    const unsigned xk = (unsigned)channel_place(a.x, k);
-#pragma unroll
-    for (int j = 0; j < PX; ++j) vx[j] = load16(Xb, px[j] + xk);
-#pragma unroll
-    for (int j = 0; j < PW; ++j) vw[j] = load16(Wb, pw[j] + (unsigned)k);
-    if (!ok) {
-#pragma unroll
-      for (int j = 0; j < PX; ++j) vx[j] = u32x4{0u, 0u, 0u, 0u};
-#pragma unroll
-      for (int j = 0; j < PW; ++j) vw[j] = u32x4{0u, 0u, 0u, 0u};
-    }
-  };
-  fetch(0);
+  auto swz = [](int R) { return PPR == 8 ? (R >> 1) & 7 : (R >> 2) & 3; };
 
   // output of register i of tile t: ob + 32 (t / 2) + 4 (t % 2) + i
   const int ob = o0 + wn * TN * 16 + 8 * g;
+  u32x2 bias[TN];
+#pragma unroll
+  for (int t = 0; t < TN; ++t) {
+    const int o = ob + 32 * (t / 2) + 4 * (t % 2);
+    bias[t] = a.b != nullptr && o < a.O ? *reinterpret_cast<const u32x2*>(a.b + o) : u32x2{0u, 0u};
+  }
+  // this lane's pieces: rows R0 + 4 RPL j of the tile, slot lane % PPR.  Rows past the last are read from the last one: they
+  // do not reach Y.  Row 16 t + r of W's tile is output 32 (t / 2) + 8 (r / 4) + 4 (t % 2) + r % 4.
+  const int R0 = RPL * w + lane / PPR, pc = 8 * ((lane % PPR) ^ swz(R0));
+  const __amdgpu_buffer_rsrc_t Xrs = __builtin_amdgcn_make_buffer_rsrc((void*)(a.X + rows_base(a.x, m0)), 0, (int)0xfffffff0u, 0x00020000);
+  const __amdgpu_buffer_rsrc_t Wrs = __builtin_amdgcn_make_buffer_rsrc((void*)(a.W + (size_t)o0 * a.K), 0, (int)0xfffffff0u, 0x00020000);
+  unsigned px[LX], pw[LW];
+#pragma unroll
+  for (int j = 0; j < LX; ++j) px[j] = 2 * row_offset(a.x, m0, min(m0 + R0 + NW * RPL * j, a.M - 1));
+#pragma unroll
+  for (int j = 0; j < LW; ++j) {
+    const int R = R0 + NW * RPL * j, o = 32 * (R >> 5) + 8 * ((R >> 2) & 3) + 4 * ((R >> 4) & 1) + (R & 3);
+    pw[j] = 2 * (unsigned)min(o, a.O - 1 - o0) * (unsigned)a.K;
+  }
+  auto issue = [&](int step) {      // channels past the last are zeros
+    const int k = step * KS + pc;
+    const bool ok = k < a.K;
+    const unsigned xk = 2 * (unsigned)channel_place(a.x, ok ? k : 0), wk = 2 * (unsigned)k;
+    unsigned char* st = smem + (step % NS) * kStage + w * 1024;
+#pragma unroll
+    for (int j = 0; j < LX; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(Xrs, AA_LDS_PTR(st + NW * 1024 * j), 16, (int)(ok ? px[j] + xk : kNone), 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < LW; ++j)
+      if (kEven || j < LW - 1 || w < NW / 2)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(Wrs, AA_LDS_PTR(st + BM * RB + NW * 1024 * j), 16, (int)(ok ? pw[j] + wk : kNone), 0, 0, 0);
+  };
+  const int steps = (a.K + KS - 1) / KS;
+#pragma unroll
+  for (int s = 0; s < NS - 1; ++s)
+    if (s < steps) issue(s);
+
   f32x4 acc[TM][TN];
 #pragma unroll
   for (int t = 0; t < TN; ++t) {
-    f32x4 first = {0.f, 0.f, 0.f, 0.f};
-    const int o = ob + 32 * (t / 2) + 4 * (t % 2);
-    if (a.b != nullptr && o < a.O) {
-      const u32x2 bv = *reinterpret_cast<const u32x2*>(a.b + o);
-      float v0, v1, v2, v3;
-      Mx<E>::unpack2(bv[0], v0, v1);
-      Mx<E>::unpack2(bv[1], v2, v3);
-      first = f32x4{v0, v1, v2, v3};
-    }
+    float v0, v1, v2, v3;
+    Mx<E>::unpack2(bias[t][0], v0, v1);
+    Mx<E>::unpack2(bias[t][1], v2, v3);
 #pragma unroll
-    for (int m = 0; m < TM; ++m) acc[m][t] = first;
+    for (int m = 0; m < TM; ++m) acc[m][t] = f32x4{v0, v1, v2, v3};
   }
-  // row r of tile t is output 32 (t / 2) + 8 (r / 4) + 4 (t % 2) + r % 4: W goes to LDS in that order
-  const int wr = 16 * ((pr >> 2) & 1) + 4 * (pr >> 3) + (pr & 3);
-  const uint16_t* wl = ws + (wn * TN * 16 + r) * kLst + 8 * g;
-  const uint16_t* xl = xs + (wm * TM * 16 + r) * kLst + 8 * g;
-  for (int k0 = 0; k0 < a.K; k0 += kStep) {
-    if (k0 > 0) __syncthreads();      // the last step has been read
+  const int xl = (wm * TM * 16 + r) * RB, wl = BM * RB + (wn * TN * 16 + r) * RB;
+  for (int i = 0; i < steps; ++i) {
+    // step i has arrived when at most the loads of the step after it are outstanding
+    if (NS == 2 || i + 1 == steps) wait_loads<0>();
+    else if (kEven || w < NW / 2) wait_loads<LX + LW>();
+    else wait_loads<LX + LW - 1>();
+    __builtin_amdgcn_s_barrier();      // step i is visible to every wave, and every wave has read step i - 1
+    asm volatile("" ::: "memory");
+    if (i + NS - 1 < steps) issue(i + NS - 1);      // into the stage of step i - 1
+    const unsigned char* st = smem + (i % NS) * kStage;
 #pragma unroll
-    for (int j = 0; j < PX; ++j) *reinterpret_cast<u32x4*>(xs + (pr + 32 * j) * kLst + pc) = vx[j];
-#pragma unroll
-    for (int j = 0; j < PW; ++j) *reinterpret_cast<u32x4*>(ws + (wr + 32 * j) * kLst + pc) = vw[j];
-    __syncthreads();
-    if (k0 + kStep < a.K) fetch(k0 + kStep);
-#pragma unroll
-    for (int ks = 0; ks < kStep / 32; ++ks) {
+    for (int ks = 0; ks < KS / 32; ++ks) {
+      const int at = 16 * ((4 * ks + g) ^ swz(r));
       u32x4 xo[TM], wo[TN];
 #pragma unroll
-      for (int m = 0; m < TM; ++m) xo[m] = *reinterpret_cast<const u32x4*>(xl + 16 * m * kLst + 32 * ks);
+      for (int m = 0; m < TM; ++m) xo[m] = *reinterpret_cast<const u32x4*>(st + xl + 16 * m * RB + at);
 #pragma unroll
-      for (int t = 0; t < TN; ++t) wo[t] = *reinterpret_cast<const u32x4*>(wl + 16 * t * kLst + 32 * ks);
+      for (int t = 0; t < TN; ++t) wo[t] = *reinterpret_cast<const u32x4*>(st + wl + 16 * t * RB + at);
 #pragma unroll
       for (int t = 0; t < TN; ++t)
 #pragma unroll
@@ -151,26 +166,46 @@ __global__ __launch_bounds__(kThreads, BM == 128 && BN == 128 ? 3 : 4) void proj
   }
 }
 
-template <class E, int BM, int BN, int WN>
+template <class E, int BM, int BN, int NW, int WN, int KS, int NS>
 hipError_t launch(ProjArgs& a, hipStream_t st) {
+  constexpr size_t lds = (size_t)NS * (BM + BN) * 2 * KS;
+  constexpr int waves = std::min<int>(4, 160 * 1024 / (int)lds * NW / 4);      // per SIMD, of the blocks that LDS holds
   a.grid = XcdGrid::make((a.M + BM - 1) / BM, (a.O + BN - 1) / BN);
-  projection_kernel<E, BM, BN, WN><<<dim3((unsigned)a.grid.blocks()), dim3(kThreads), 0, st>>>(a);
+  auto kernel = projection_kernel<E, BM, BN, NW, WN, KS, NS, waves>;
+  const hipError_t err = allow_lds(kernel, lds);
+  if (err != hipSuccess) return err;
+  kernel<<<dim3((unsigned)a.grid.blocks()), dim3(64 * NW), lds, st>>>(a);
   return hipGetLastError();
+}
+
+// Columns per block: the least padded width, a column of a narrower block priced higher: it takes 8 / 12 (96) or 6 / 8 (64)
+// LDS reads per product where 128 takes 8 / 16.
+template <class E, int BM, int KS>
+hipError_t columns(ProjArgs& a, hipStream_t st) {
+  auto price = [&](int bn, int per_column) { return (long long)((a.O + bn - 1) / bn) * bn * per_column; };
+  const long long p128 = price(128, 10), p96 = price(96, 12), p64 = price(64, 13);
+  if (p128 <= p96 && p128 <= p64) {
+    // X and Y beyond three quarters of the 256 MB that caches keep: the loads are longer under way, and blocks of 256 rows with
+    // two steps of 32 channels ahead do better.  100352 rows, q | k | v of width 256: 81.5 us in the blocks below, 75.8; of
+    // 384: 149, 138.5; 25088 rows, width 1024: 200, 188; but width 768 (147 MB): 115, 116 to 123.
+    if (BM == 128 && KS == 64 && a.bytes() > (192ll << 20)) return launch<E, 256, 128, 8, 2, 32, 3>(a, st);
+    return launch<E, BM, 128, 4, 2, KS, 2>(a, st);
+  }
+  return p96 <= p64 ? launch<E, BM, 96, 4, 1, KS, 2>(a, st) : launch<E, BM, 64, 4, 2, KS, 2>(a, st);
 }
 
 template <class E>
 hipError_t dispatch(ProjArgs& a, hipStream_t st) {
-  // Columns per block: the least padded width, a column of a narrower block priced higher: it takes 8 / 12 (96) or 6 / 8
-  // (64) LDS reads per product where 128 takes 8 / 16.
-  auto price = [&](int bn, int per_column) { return (long long)((a.O + bn - 1) / bn) * bn * per_column; };
-  const long long p128 = price(128, 10), p96 = price(96, 12), p64 = price(64, 13);
-  // Rows per block: 64 while blocks of 128 would leave CUs with fewer than two (1 x 196 tokens, width 192: the call 51 ->
-  // 21 us with the library's launches gone; 16384 rows, width 320: 12 us as 640 blocks of 64 rows).
-  const long long cols = (a.O + 127) / 128, tall = (long long)((a.M + 127) / 128) * cols;
-  const bool low = tall < 2 * kComputeUnits;
-  if (p128 <= p96 && p128 <= p64) return low ? launch<E, 64, 128, 2>(a, st) : launch<E, 128, 128, 2>(a, st);
-  if (p96 <= p64) return low ? launch<E, 64, 96, 1>(a, st) : launch<E, 128, 96, 1>(a, st);
-  return low ? launch<E, 64, 64, 2>(a, st) : launch<E, 128, 64, 2>(a, st);
+  // Channels per step: 64 ask for whole 128-byte lines (16384 rows, width 512: 41.7 us, 47.0 with steps of 32).  32 where four to
+  // five blocks a CU do more: up to a width of 96 (100352 rows, width 96: 18.7 us, 22.5 with steps of 64), and below 256 where
+  // the last 64 would be half empty (width 160: 32.4, 38.2) or from memory (100352 rows, width 192: 50.8 + 20.5, 52.9 + 21.8;
+  // 25088 rows: 17.1 + 7.9, 15.5 + 7.5).
+  const bool half = a.K < 128 || (a.K < 256 && ((a.K - 1) % 64 < 32 || a.bytes() > (64ll << 20)));
+  // Rows per block: 64 while blocks of 128 would leave CUs at less than half of what they hold (784 rows, width 512: 11.1 ->
+  // 9.0 us; 6272 rows, output of width 512: 10.0 -> 8.4; but q | k | v of width 256, 294 blocks: 10.2, 12.2 with 64 rows).
+  const long long tall = (long long)((a.M + 127) / 128) * ((a.O + 127) / 128);
+  if (half) return tall < 2 * kComputeUnits ? columns<E, 64, 32>(a, st) : columns<E, 128, 32>(a, st);
+  return tall < kComputeUnits ? columns<E, 64, 64>(a, st) : columns<E, 128, 64>(a, st);
 }
 
 }  // namespace

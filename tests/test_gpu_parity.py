@@ -746,14 +746,19 @@ def test_module_with_projections(aa, oracle, name, batch, heads, d, grid, window
     assert np.abs(ref - ref2).max() > 1e-3
 
 
-# rows and widths on and off the blocks of the projection kernel (128 or 64 rows; 128, 96 or 64 outputs; steps of 64
-# channels), windows that are staged for the few-agents and for the many-agents kernels, and the library's product
+# rows and widths on and off the blocks of the projection kernel (256, 128 or 64 rows; 128, 96 or 64 outputs; steps of 64
+# or 32 channels), windows that are staged for the few-agents and for the many-agents kernels, and the library's product
 PROJECTION_CASES = [
     ("width 8", 1, 1, 8, (9, 7), None, (2, 2), "f16", True),
     ("width 80, many agents, windows", 2, 2, 40, (40, 16), (20, 16), (9, 9), "bf16", True),
     ("width 96, few agents, windows", 2, 3, 32, (28, 56), (28, 28), (7, 7), "f16", True),
     ("blocks of 128 rows, 96 and 64 outputs", 8, 2, 16, (97, 95), None, (3, 3), "bf16", True),
     ("blocks of 128 rows, 128 outputs", 8, 4, 32, (97, 95), None, (3, 3), "f16", True),
+    ("steps of 64 channels, blocks of 64 rows, the last step part full", 1, 29, 8, (19, 7), None, (3, 3), "bf16", True),
+    ("steps of 64 channels, blocks of 128 rows, windows", 4, 4, 64, (56, 28), (28, 28), (7, 7), "f16", True),
+    ("steps of 64 channels, 64 outputs", 1, 5, 64, (23, 21), None, (3, 3), "f16", True),
+    ("steps of 64 channels, 96 outputs, blocks of 128 rows", 8, 6, 32, (79, 53), None, (3, 3), "bf16", True),
+    ("past the caches: blocks of 256 rows", 8, 4, 64, (111, 111), None, (3, 3), "bf16", True),
     ("unaligned rows", 1, 3, 12, (11, 9), None, (3, 3), "bf16", True),
     ("unaligned weights", 1, 2, 32, (14, 14), None, (7, 7), "bf16", False),
 ]
