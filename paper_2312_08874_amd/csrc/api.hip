@@ -227,8 +227,9 @@ BiasPlan plan_bias(const aa_desc* d, const aa_params* params, bool small = false
       const bool row = kind == 1 ? params->b1_row != nullptr : params->b2_row != nullptr;
       // B1's block component goes through the matrix pipe (two more k-steps of the aggregation's score products)
       // when its grid has at most 64 cells, the head width pads to 64 and the aggregation takes its tokens in rows (up to 256
-      // agents, say: large_aggregate_columns); the half-resized table then holds the column component only.  (Not B2: in the broadcast's orientation a lane owns a token, the column and row
-      // pieces it needs per agent tile stay the same 16-byte loads, and the same change measured no gain there.)
+      // agents, say: large_aggregate_columns); the half-resized table then holds the column component only.  (Not B2: in the
+      // broadcast's orientation a lane owns a token, the column and row pieces it needs per agent tile stay the same 16-byte loads,
+      // and the same change measured no gain there.)
       const bool matrix = kind == 1 && blk && params->blk_h0 * params->blk_w0 <= 64 && padded_width(d->d) == 64 &&
                           (small || !aa::large_aggregate_columns(64, d->n, d->grid_h, d->grid_w, params->blk_h0));
       if (matrix) {

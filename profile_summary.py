@@ -90,7 +90,7 @@ BACKWARD_KERNELS = ("matmul_kernel", "mfma_matmul_kernel", "mfma_matmul_pair_ker
                     "value_extras_kernel", "dwc_param_partial_kernel", "dwc_param_sum_kernel", "batch_sum_kernel",
                     "bias_grad_kernel", "bias_grad_row_kernel", "pool_grad_kernel", "to_f32_kernel",
                     "from_f32_kernel", "fused_token_kernel", "fused_agent_kernel", "fused_merge_kernel",
-                    "fused_reduce_bc_kernel", "fused_reduce_agg_kernel",
+                    "fused_reduce_bc_kernel", "fused_reduce_agg_kernel", "pool_grad_out_kernel",
                     "bias_agent_kernel", "bias_tables_kernel", "bias_grad_sum_kernel", "bias_grad_batch_sum_kernel", "param_grad_out_kernel",
                     "dwc_param_kernel")
 
