@@ -202,10 +202,13 @@ hipError_t dispatch(ProjArgs& a, hipStream_t st) {
   // 25088 rows: 17.1 + 7.9, 15.5 + 7.5).
   const bool half = a.K < 128 || (a.K < 256 && ((a.K - 1) % 64 < 32 || a.bytes() > (64ll << 20)));
   // Rows per block: 64 while blocks of 128 would leave CUs at less than half of what they hold (784 rows, width 512: 11.1 ->
-  // 9.0 us; 6272 rows, output of width 512: 10.0 -> 8.4; but q | k | v of width 256, 294 blocks: 10.2, 12.2 with 64 rows).
+  // 9.0 us; 6272 rows, output of width 512: 10.0 -> 8.4; but q | k | v of width 256, 294 blocks: 10.2, 12.2 with 64 rows), and
+  // where two a CU leave a few for a second round, for which three blocks of 64 rows a CU are shorter (14 products of 517 to
+  // 588 blocks of 128 rows 0.85 to 0.97 of the time: 18000 rows, width 512, output 18.4 -> 16.6).
   const long long tall = (long long)((a.M + 127) / 128) * ((a.O + 127) / 128);
   if (half) return tall < 2 * kComputeUnits ? columns<E, 64, 32>(a, st) : columns<E, 128, 32>(a, st);
-  return tall < kComputeUnits ? columns<E, 64, 64>(a, st) : columns<E, 128, 64>(a, st);
+  const bool few = tall < kComputeUnits || (tall > 2 * kComputeUnits && tall <= 5 * kComputeUnits / 2);
+  return few ? columns<E, 64, 64>(a, st) : columns<E, 128, 64>(a, st);
 }
 
 }  // namespace
