@@ -4,6 +4,8 @@ branch: agents at and beside the 16 of a wave and the 32 of a product step, toke
 convolution.  Reference and bars as in test_gpu_backward."""
 import pytest
 
+from paper_2312_08874_amd import inputs
+
 from .test_gpu_backward import _run_case, _wl, aa  # noqa: F401  (fixture)
 
 pytestmark = pytest.mark.gpu
@@ -25,3 +27,26 @@ def test_both_sides_at_their_edges(aa, oracle, grid, agrid, d, module, dtype):  
 def test_both_sides_of_one_unit_in_many_ranges(aa, oracle, given, module, dtype, d):  # noqa: F811
     _run_case(aa, oracle, _wl("ranges", dtype, (61, 45), (7, 7), d, batch=1, heads=1, index=62), given=given, module=module,
               kw=RESIDUAL)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("n,d", [(16, 32), (49, 64), (64, 48), (33, 128)])
+def test_a_token_that_is_not_a_number_reaches_every_gradient_it_enters(aa, n, d, value, dtype):  # noqa: F811
+    """Given agents: a query that is no finite number makes its weights NaN, hence dV_A = sum_t P2^T dO, and with it all of its
+    unit's dK and dV; the gradients of the other queries, and of the other units, stay what they are."""
+    import torch
+    from . import util
+    wl = _wl("nan", dtype, (13, 21), (1, n), d, batch=1, heads=2, index=63)
+    t = {k: util.to_device(v, dtype, (1, 2, wl.N, d)) for k, v in inputs.make_qkv(wl).items()}
+    rows = [util.to_device(inputs.make_tensor((2, r, d), stream=wl.index * 16 + 11 + i, dtype=dtype), dtype, (1, 2, r, d)) for i, r in ((0, n), (1, wl.N))]
+    clean = aa.agent_attn_bwd(t["Q"], t["K"], t["V"], rows[1], rows[0])
+    q = t["Q"].clone()
+    q[0, 1, 37, 5] = value
+    got = aa.agent_attn_bwd(q, t["K"], t["V"], rows[1], rows[0])
+    for k in ("dK", "dV", "dA"):
+        assert torch.isnan(got[k][0, 1]).all(), k
+        assert torch.equal(got[k][0, 0], clean[k][0, 0]), k
+    other = [i for i in range(wl.N) if i != 37]
+    assert torch.isnan(got["dQ"][0, 1, 37]).all() and torch.equal(got["dQ"][0, 1, other], clean["dQ"][0, 1, other])
+    assert torch.equal(got["dQ"][0, 0], clean["dQ"][0, 0])
