@@ -77,7 +77,8 @@ __global__ __launch_bounds__(kThreads) void fused_merge_kernel(SumRows g, const 
   for (int s0 = 0;;) {
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-      const float w = s0 + k < g.S ? fast_exp2(m[k] - M) : 0.f;
+      if (s0 + k >= g.S) continue;      // (not a weight of 0: a row may hold infinities)
+      const float w = fast_exp2(m[k] - M);
       L = fmaf(l[k], w, L);
       v += x[k] * w;
     }
