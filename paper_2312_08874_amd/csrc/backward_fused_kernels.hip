@@ -43,6 +43,8 @@ struct SumRows {
 };
 __device__ __forceinline__ f32x4 row4(const float* p, size_t row, int d, int c) { return load_global<f32x4>(p + row * d + c); }
 
+constexpr int kMaxRanges = 64;      // of a unit's tokens
+
 // log-sum-exp merge of the recomputed aggregation: V_A (fp32 and element type), reference and weight of the rows (log2
 // domain; w1 null: the log-sum-exp, no weight)
 template <class E>
@@ -56,6 +58,7 @@ __global__ __launch_bounds__(kThreads) void fused_merge_kernel(SumRows g, const 
   float M = -INFINITY, m[8], l[8];
   f32x4 v = {0.f, 0.f, 0.f, 0.f}, x[8];
   float L = 0.f;
+  constexpr float kShare = 1.0f / kMaxRanges;      // (a power of two) what fits fp32 in every range fits it in their sum
   auto fetch = [&](int s0) {
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
@@ -80,13 +83,13 @@ __global__ __launch_bounds__(kThreads) void fused_merge_kernel(SumRows g, const 
       if (s0 + k >= g.S) continue;      // (not a weight of 0: a row may hold infinities)
       const float w = fast_exp2(m[k] - M);
       L = fmaf(l[k], w, L);
-      v += x[k] * w;
+      v += x[k] * (w * kShare);
     }
     if ((s0 += 8) >= g.S) break;
     fetch(s0);
   }
   if (!ok) return;
-  v *= 1.0f / L;
+  v *= (1.0f / L) * (1.0f / kShare);
   const size_t o = (size_t)row * g.d + c;
   *reinterpret_cast<f32x4*>(VAf + o) = v;
   if constexpr (X::kBytes == 2) *reinterpret_cast<typename X::P4*>(VAe + o) = X::pack4(v[0], v[1], v[2], v[3]);      // fp32: the same array
@@ -262,7 +265,7 @@ FusedPlan fused_plan(const Problem& p, bool forward = false) {
   f.weights[0] = f32 || f.bias[0], f.weights[1] = f32 || f.bias[1];
   f.token_cols = f32 && f.DP > 64 ? 1 : 2;
   // token ranges: about two blocks per CU for the broadcast's agent kernel (192 registers) and with a bias, three for
-  // the other two (which fit three blocks; four measured no faster).  At most 64: the merge gives every range a lane.
+  // the other two (which fit three blocks; four measured no faster).  At most kMaxRanges, which the merge's scale is made for.
   int groups[2];
   for (int k = 0; k < 2; ++k) {
     f.agent_cols[k] = (f32 || f.DP == 128 || p.n <= 64 || (k == 0 && f.bias[0] && f.DP == 64)) ? 1 : 2;
@@ -271,7 +274,7 @@ FusedPlan fused_plan(const Problem& p, bool forward = false) {
     groups[k] = f.agent_blocks[k] * p.units;
     f.ld = std::max(f.ld, f.agent_blocks[k] * per_block);
     int S = ((2 + k) * kComputeUnits + groups[k] - 1) / groups[k];
-    S = std::max(std::min(std::min(S, 64), (p.N + 127) / 128), 1);
+    S = std::max(std::min(std::min(S, kMaxRanges), (p.N + 127) / 128), 1);
     f.chunk[k] = ((p.N + S - 1) / S + 31) / 32 * 32;
     f.S[k] = (p.N + f.chunk[k] - 1) / f.chunk[k];
   }
@@ -281,7 +284,7 @@ FusedPlan fused_plan(const Problem& p, bool forward = false) {
     if (!f.bias[k]) continue;
     // the ranges are pairs of columns: enough segments of at least four image rows for the number of ranges wanted,
     // an even number of columns, ranges of equally many pairs
-    const int want = std::max(std::min((2 * kComputeUnits + groups[k] - 1) / groups[k], 64), 1);
+    const int want = std::max(std::min((2 * kComputeUnits + groups[k] - 1) / groups[k], kMaxRanges), 1);
     int segs = std::max(1, std::min((2 * want + xts - 1) / xts, p.gh / 4));
     if (xts % 2 == 1 && segs % 2 == 1 && segs < p.gh) ++segs;
     f.seg_len[k] = (p.gh + segs - 1) / segs;

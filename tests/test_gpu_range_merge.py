@@ -25,3 +25,13 @@ def test_an_infinite_value_stays_infinite(aa, grid, agrid, d, value):
     assert (out[0, 1, :, 5] == value).all()
     rest = [c for c in range(d) if c != 5]
     assert torch.equal(out[0, 0], clean[0, 0]) and torch.equal(out[0, 1][:, rest], clean[0, 1][:, rest])
+
+
+@pytest.mark.parametrize("value", [4e35, -8e35])
+def test_sums_of_the_ranges_that_pass_the_type_do_not(aa, value):
+    """3136 equal scores: the sum over a range of at most 400 tokens fits fp32, over all of them it does not.  Their mean is the value
+    itself, to a rounding (2^-24) for each term of a range and a few more."""
+    q = torch.zeros(1, 64, 3136, 32, device="cuda")
+    v = torch.full_like(q, value)
+    out = aa.agent_attn_fwd(q, q, v, grid=(56, 56), agent_grid=(7, 7)).double()
+    assert (out / value - 1).abs().max() <= 400 * 2.0 ** -24
