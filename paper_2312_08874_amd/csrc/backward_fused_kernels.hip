@@ -299,12 +299,13 @@ FusedPlan fused_plan(const Problem& p, bool forward = false) {
   // One kernel for both sides wherever a block of four waves holds all agents of a unit and the registers suffice (105
   // training steps of 8 .. 192 units of 196 .. 10000 tokens x 16 .. 64 agents, start / now: 0.73 to 0.97 of the time, 0.90 in the
   // mean).  Not dK / dV with a bias at 128 channels in 16 bits (263 registers spilled: 16 x 4 units of 784 x 16 285 -> 299 us) nor
-  // fp32 above 64; the convolution without a bias is the token kernel's (its tokens are not walked down columns here).  From 2^30
+  // fp32 above 64; the convolution without a bias is the token kernel's (its tokens are not walked down columns here), and so is
+  // the residual with a bias and no convolution (a path for it beside the convolution's cost the latter 1 to 2 %).  From 2^30
   // elements on (16 bits) the broadcast's tokens stay with their own kernel, dQ in fp32 beside tensors of that size being 4 GiB
   // and more of workspace (time is not why: 256 units of 16384 x 49, d = 64, 2^28 elements, 2805 -> 2547 us).
   const bool room = f32 || (unsigned long long)p.units * p.N * p.d < 1ull << 30;
   for (int k = 0; k < 2; ++k)
-    f.both[k] = !forward && p.n <= 64 && (!f32 || f.DP <= 64) && (k == 0 ? room : f.bias[1] ? f32 || f.DP <= 64 : !p.dwc_w);
+    f.both[k] = !forward && p.n <= 64 && (!f32 || f.DP <= 64) && (k == 0 ? room : f.bias[1] ? (f32 || f.DP <= 64) && (p.dwc_w || p.vk == 0.0f) : !p.dwc_w);
   const size_t u = (size_t)p.units, nd = up64((size_t)p.n * p.d), un = up64(u * p.n), uN = up64(u * p.N);
   size_t o = 0;
   f.VAf = o, o += u * nd;

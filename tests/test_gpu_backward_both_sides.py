@@ -50,3 +50,26 @@ def test_a_token_that_is_not_a_number_reaches_every_gradient_it_enters(aa, n, d,
     other = [i for i in range(wl.N) if i != 37]
     assert torch.isnan(got["dQ"][0, 1, 37]).all() and torch.equal(got["dQ"][0, 1, other], clean["dQ"][0, 1, other])
     assert torch.equal(got["dQ"][0, 0], clean["dQ"][0, 0])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("grid,d", [((17, 19), 32), ((17, 20), 64), ((12, 16), 40)])
+def test_a_residual_without_the_convolution_reads_its_own_token(aa, grid, d, dtype):  # noqa: F811
+    """dV = P1^T dV_A + k dO: with an agent bias and no convolution an infinite dO adds to its own token's dV alone, so that the
+    channel is as infinite as P1^T dV_A makes it everywhere (P1 > 0, the sign of dV_A's infinity is that of dO's).  Tokens of an
+    image's last column also stand in for places beside it, with weights of 0, and are left out."""
+    import torch
+    from . import util
+    wl = _wl("own", dtype, grid, (7, 7), d, batch=1, heads=2, index=64)
+    t = {k: util.to_device(v, dtype, (1, 2, wl.N, d)) for k, v in inputs.make_qkv(wl).items()}
+    dO = util.to_device(inputs.make_tensor((2, wl.N, d), stream=wl.index * 16 + 12, dtype=dtype), dtype, (1, 2, wl.N, d))
+    params = {k: v for k, v in inputs.make_module_params(2, wl.n, d, grid, blk=(3, 2), index=64).items() if not k.startswith("dwc")}
+    kw = dict(grid=grid, agent_grid=(7, 7), params=util.params_to_device(params), v_residual_k=0.3)
+    clean = aa.agent_attn_bwd(t["Q"], t["K"], t["V"], dO, **kw)["dV"]
+    for tok in (3, grid[1] + 2, wl.N - 2):
+        g = dO.clone()
+        g[0, 1, tok, 5] = float("inf")
+        dV = aa.agent_attn_bwd(t["Q"], t["K"], t["V"], g, **kw)["dV"]
+        assert torch.isposinf(dV[0, 1, :, 5]).all()
+        rest = [c for c in range(d) if c != 5]
+        assert torch.equal(dV[0, 0], clean[0, 0]) and torch.equal(dV[0, 1][:, rest], clean[0, 1][:, rest])
