@@ -73,3 +73,26 @@ def test_a_residual_without_the_convolution_reads_its_own_token(aa, grid, d, dty
         assert torch.isposinf(dV[0, 1, :, 5]).all()
         rest = [c for c in range(d) if c != 5]
         assert torch.equal(dV[0, 0], clean[0, 0]) and torch.equal(dV[0, 1][:, rest], clean[0, 1][:, rest])
+
+
+@pytest.mark.parametrize("grid,agrid,d", [((31, 43), (7, 9), 48), ((20, 33), (4, 8), 32), ((17, 50), (5, 5), 64)])
+def test_fp32_value_gradient_rounds_no_more_than_nine_additions(aa, oracle, grid, agrid, d):  # noqa: F811
+    """dV is nine weighted dO beside small products of the attention: added one after another onto the products, the partial sums
+    grow evenly to the result, nine roundings that come to sqrt((1 + .. + 9) / 9) = sqrt(5) roundings of the result itself.  The bound
+    leaves a twentieth for the products."""
+    import numpy as np
+    from . import util
+    wl = _wl("rounding", "f32", grid, agrid, d, batch=1, heads=4, index=65)
+    t = inputs.make_qkv(wl)
+    dO = inputs.make_tensor((4, wl.N, d), stream=wl.index * 16 + 12, dtype="f32")
+    params = inputs.make_module_params(4, wl.n, d, grid, blk=(3, 2), index=65)
+    dev = {k: util.to_device(v, "f32", (1, 4, wl.N, d)) for k, v in t.items()}
+    got = aa.agent_attn_bwd(dev["Q"], dev["K"], dev["V"], util.to_device(dO, "f32", (1, 4, wl.N, d)), grid=grid, agent_grid=agrid,
+                            params=util.params_to_device(params))["dV"]
+    B1, B2 = util.dense_biases(oracle, params, 4, wl.n, grid)
+    ref = oracle.agent_attn_bwd(*(t[k].astype(np.float64) for k in ("Q", "K", "V")), dO.astype(np.float64), heads=4, grid=grid,
+                                agent_grid=agrid, B1=B1, B2=B2, dwc_w=params["dwc_w"], dwc_b=params["dwc_b"])["dV"]
+    one = np.linalg.norm(ref.astype(np.float32) - ref)
+    err = np.linalg.norm(util.to_host64(got).reshape(ref.shape) - ref)
+    print("dV error: %.3f roundings of the result" % (err / one))
+    assert err <= 1.05 * np.sqrt(5) * one
