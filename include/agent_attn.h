@@ -135,10 +135,12 @@ aa_status agent_attn_fwd(const aa_desc *desc, const void *Q, const void *K, cons
  * over: code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  The
  * workspace is an array of agent_attn_static_scratch_bytes() bytes (64 MiB) that the library holds in
  * every GPU's memory from the moment it is loaded there until the process ends; the call allocates and
- * frees nothing (no hipMalloc, no hipFree, no allocating library routine).  Problems whose
- * agent_attn_workspace_bytes() exceeds that size are rejected with AA_ERR_WORKSPACE before anything is
- * launched (module mode with many agents fits when params->bias_tables brings prepared tables).
- * Everything else -- arguments, validation, kernels, results bit for bit -- is agent_attn_fwd's.
+ * frees nothing (no hipMalloc, no hipFree, no allocating library routine).  Arguments, validation and kernels are
+ * agent_attn_fwd's, and so are the results, bit for bit, where agent_attn_workspace_bytes() fits that size.  Problems that
+ * fit only with less are served with B1's block component in matrix form (16 bits, more than 64 agents, up to 64 channels)
+ * or with kernels that take an fp32 bias per score: 16-bit ones again bit for bit if the tables of the two biases fit one
+ * after the other, the others within rounding.  What does not fit then is rejected with AA_ERR_WORKSPACE before anything
+ * is launched (module mode with many agents fits when params->bias_tables brings prepared tables).
  * All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (different streams
  * or threads) race and give unspecified results; calls on one stream are ordered and safe.  The array
  * keeps the last call's contents; nothing in it has to be cleared between calls. */

@@ -42,8 +42,12 @@ constexpr size_t kNone = ~(size_t)0;
 struct BiasPlan {
   size_t B1d = kNone, B2d = kNone, H1 = kNone, R1 = kNone, H2 = kNone, R2 = kNone;
   size_t WT = kNone, K1 = kNone;      // matrix form of the block component of B1 (BiasArgs::wt / blkop)
+  bool in_turn = false;               // the half-resized tables of B2 take the place of B1's after the aggregation
   size_t total = 0;
 };
+// How much of a workspace a plan may take: what is fastest; the same kernels, with the tables of the two biases in turn where they
+// are half-resized ones; the least (B1 in matrix form wherever it exists, no bias tables and partial sums of the fp32 kernels)
+enum class Room { kAll, kInTurn, kLeast };
 
 struct Plan {
   int S;               // N-splits of the generic aggregation
@@ -208,8 +212,7 @@ constexpr size_t kBiasDenseCapBytes = (size_t)2 << 30;
 
 int padded_width(int d);
 
-// small: the matrix form wherever it exists, its tables being the smaller ones
-BiasPlan plan_bias(const aa_desc* d, const aa_params* params, bool small = false) {
+BiasPlan plan_bias(const aa_desc* d, const aa_params* params, Room room = Room::kAll) {
   BiasPlan bp;
   size_t off = 0;
   const bool tables_ok = d->grid_h > 0 && d->dtype != AA_F32;      // the MFMA kernels are the ones that read them
@@ -231,7 +234,8 @@ BiasPlan plan_bias(const aa_desc* d, const aa_params* params, bool small = false
       // broadcast's orientation a lane owns a token, the column and row pieces it needs per agent tile stay the same 16-byte loads,
       // and the same change measured no gain there.)
       const bool matrix = kind == 1 && blk && params->blk_h0 * params->blk_w0 <= 64 && padded_width(d->d) == 64 &&
-                          (small || !aa::large_aggregate_columns(64, d->n, d->grid_h, d->grid_w, params->blk_h0));
+                          (room == Room::kLeast || !aa::large_aggregate_columns(64, d->n, d->grid_h, d->grid_w, params->blk_h0));
+      if (room == Room::kInTurn && kind == 2) bp.in_turn = off > 0, bp.total = off, off = 0;
       if (matrix) {
         bp.WT = off;
         off += align_up(aa::bias_wt_bytes(d->N));
@@ -252,7 +256,7 @@ BiasPlan plan_bias(const aa_desc* d, const aa_params* params, bool small = false
       off += align_up(bytes);
     }
   }
-  bp.total = off;
+  bp.total = std::max(bp.total, off);
   return bp;
 }
 
@@ -275,9 +279,7 @@ bool few_biased_tokens(const Problem& p) {
   return p.d <= 64 ? tokens <= 1024 || p.N <= 256 : p.N <= 256 && tokens <= 2048;
 }
 
-// small: without the fp32 kernels' bias tables and partial sums, with the smaller form of the 16-bit ones (callers with a workspace
-// of fixed size)
-Plan make_plan(const aa_desc* d, const aa_params* params = nullptr, bool small = false) {
+Plan make_plan(const aa_desc* d, const aa_params* params = nullptr, Room room = Room::kAll) {
   Plan pl{};
   const size_t units = (size_t)units_of(d);
   pl.S = choose_splits(d);
@@ -321,14 +323,14 @@ Plan make_plan(const aa_desc* d, const aa_params* params = nullptr, bool small =
     pl.off_stage = off;
     off += 4 * pl.stage_bytes;
   }
-  pl.bias = plan_bias(d, params, small && !(params && params->bias_tables));      // (tables brought along have their form)
+  pl.bias = plan_bias(d, params, params && params->bias_tables ? Room::kAll : room);      // (tables brought along have their form)
   pl.off_bias = off;
   if (!(params && params->bias_tables)) off += pl.bias.total;      // prepared tables need no room here
   pl.off_f32 = kNoStage;
   const Problem full = make_problem(d, params);
   // not with an explicit split count (the kernels that take one), nor where the one-launch kernel serves the shape (it asks
   // the same of pointers and strides, so these are no fallback)
-  if (!small && d->n_splits <= 0 && aa::forward_f32_supported(full) && !few_biased_tokens(full) &&
+  if (room != Room::kLeast && d->n_splits <= 0 && aa::forward_f32_supported(full) && !few_biased_tokens(full) &&
       !(pl.prefer_fused && aa::fused_f32_supported(full))) {
     pl.off_f32 = off;
     off += align_up(aa::forward_f32_workspace_floats(full) * sizeof(float));
@@ -498,7 +500,13 @@ aa::LargeFwdBuffers large_buffers(void* ws, const Plan& pl, const Problem& pr) {
   return b;
 }
 
-// The three launches of the large-agent forward pass.  A == nullptr: agents pooled from Q.
+// The tables of B2 where they take the place of B1's
+hipError_t second_tables(const Problem& pr, const Plan& pl, hipStream_t st) {
+  if (!pl.bias.in_turn) return hipSuccess;
+  return aa::launch_bias_half(pr, nullptr, nullptr, const_cast<float*>(pr.b2.half), const_cast<float*>(pr.b2.rows), st);
+}
+
+// The launches of the large-agent forward pass.  A == nullptr: agents pooled from Q.
 aa_status run_large_forward(const Problem& pr, const void* Q, const void* K, const void* V, const void* A, void* ws,
                             const Plan& pl, void* out, hipStream_t st) {
   const aa::LargeFwdBuffers b = large_buffers(ws, pl, pr);
@@ -507,18 +515,21 @@ aa_status run_large_forward(const Problem& pr, const void* Q, const void* K, con
       AA_HIP(aa::launch_large_agents_dp32(pr, Q, A, b, st));
       AA_HIP(aa::launch_large_aggregate2_dp32(pr, K, V, b, nullptr, st));
       if (b.S > 1) AA_HIP(aa::launch_large_merge2_dp32(pr, b, nullptr, st));
+      AA_HIP(second_tables(pr, pl, st));
       AA_HIP(aa::launch_large_broadcast2_dp32(pr, Q, V, out, b, pl.bcast_waves_large, st));
       break;
     case 64:
       AA_HIP(aa::launch_large_agents_dp64(pr, Q, A, b, st));
       AA_HIP(aa::launch_large_aggregate2_dp64(pr, K, V, b, nullptr, st));
       if (b.S > 1) AA_HIP(aa::launch_large_merge2_dp64(pr, b, nullptr, st));
+      AA_HIP(second_tables(pr, pl, st));
       AA_HIP(aa::launch_large_broadcast2_dp64(pr, Q, V, out, b, pl.bcast_waves_large, st));
       break;
     default:
       AA_HIP(aa::launch_large_agents_dp128(pr, Q, A, b, st));
       AA_HIP(aa::launch_large_aggregate2_dp128(pr, K, V, b, nullptr, st));
       if (b.S > 1) AA_HIP(aa::launch_large_merge2_dp128(pr, b, nullptr, st));
+      AA_HIP(second_tables(pr, pl, st));
       AA_HIP(aa::launch_large_broadcast2_dp128(pr, Q, V, out, b, pl.bcast_waves_large, st));
       break;
   }
@@ -597,7 +608,7 @@ aa_status prepare_bias_tables(Problem& pr, const BiasPlan& bp, void* base_ptr, b
     AA_HIP(aa::launch_bias_dense(pr, d1, d2, st));
     Problem colrow = pr;      // a kind in matrix form keeps its block component out of the half-resized table
     if (k1) colrow.b1.blk = nullptr;
-    AA_HIP(aa::launch_bias_half(colrow, h1, r1, h2, r2, st));
+    AA_HIP(aa::launch_bias_half(colrow, h1, r1, bp.in_turn ? nullptr : h2, bp.in_turn ? nullptr : r2, st));
     AA_HIP(aa::launch_bias_matrix(pr, wt, k1, st));
   }
   if (h1) {
@@ -847,10 +858,10 @@ static bool windows_staged(const Problem& pr, const Plan& pl, std::initializer_l
   return mfma && !fused;
 }
 
-// agent_attn_fwd; small: plan without the streaming fp32 kernels' workspace
+// agent_attn_fwd
 static aa_status forward_checked(const aa_desc* desc, const void* Q, const void* K, const void* V, const void* A,
                                  const aa_params* params, void* workspace, size_t workspace_bytes, void* out,
-                                 void* hip_stream, bool small) {
+                                 void* hip_stream, Room room) {
   const bool pooling = (A == nullptr);
   aa_status st = check_desc(desc, pooling || params_use_grid(params), pooling);
   if (st == AA_ERR_SHAPE && pooling && desc && desc->grid_h == 0 && desc->grid_w == 0) st = AA_ERR_POOL;
@@ -858,7 +869,7 @@ static aa_status forward_checked(const aa_desc* desc, const void* Q, const void*
   st = check_params(params);
   if (st != AA_OK) return st;
   if (!Q || !K || !V || !out) return AA_ERR_NULL;
-  const Plan pl = make_plan(desc, params, small);
+  const Plan pl = make_plan(desc, params, room);
   st = check_workspace(workspace, workspace_bytes, pl);
   if (st != AA_OK) return st;
   const size_t es = elem_size(desc->dtype), units = (size_t)units_of(desc);
@@ -889,7 +900,7 @@ static aa_status forward_checked(const aa_desc* desc, const void* Q, const void*
 aa_status agent_attn_fwd(const aa_desc* desc, const void* Q, const void* K, const void* V, const void* A,
                          const aa_params* params, void* workspace, size_t workspace_bytes, void* out,
                          void* hip_stream) {
-  return forward_checked(desc, Q, K, V, A, params, workspace, workspace_bytes, out, hip_stream, false);
+  return forward_checked(desc, Q, K, V, A, params, workspace, workspace_bytes, out, hip_stream, Room::kAll);
 }
 
 // Backward workspace: the pooled agents in the element type (256-byte aligned), then the fp32 scratch, then,
@@ -1024,8 +1035,9 @@ aa_status agent_attn_fwd_static(const aa_desc* desc, const void* Q, const void* 
   st = check_params(params);
   if (st != AA_OK) return st;
   if (!Q || !K || !V || !out) return AA_ERR_NULL;
-  const bool small = make_plan(desc, params).total > AA_STATIC_SCRATCH_BYTES;
-  if (small && make_plan(desc, params, true).total > AA_STATIC_SCRATCH_BYTES) return AA_ERR_WORKSPACE;
+  auto fits = [&](Room r) { return make_plan(desc, params, r).total <= AA_STATIC_SCRATCH_BYTES; };
+  const Room room = fits(Room::kAll) ? Room::kAll : fits(Room::kInTurn) ? Room::kInTurn : Room::kLeast;
+  if (!fits(room == Room::kInTurn ? Room::kLeast : room)) return AA_ERR_WORKSPACE;      // (accepted is what fits in the least form)
   // device address of this GPU's copy of the array, looked up once per device
   constexpr int kMaxDevices = 64;
   static std::mutex mu;
@@ -1044,7 +1056,7 @@ aa_status agent_attn_fwd_static(const aa_desc* desc, const void* Q, const void* 
     }
     ptr = base[dev];
   }
-  return forward_checked(desc, Q, K, V, A, params, ptr, AA_STATIC_SCRATCH_BYTES, out, hip_stream, small);
+  return forward_checked(desc, Q, K, V, A, params, ptr, AA_STATIC_SCRATCH_BYTES, out, hip_stream, room);
 }
 
 aa_status agent_attn_fwd_timed(const aa_desc* desc, const void* Q, const void* K, const void* V, const void* A,

@@ -49,6 +49,25 @@ def test_static_workspace_matches_caller_workspace(name, first, second, module):
         assert torch.equal(out, ref)
 
 
+@pytest.mark.parametrize("dtype,d,grid,agrid", [("bf16", 64, (128, 128), (28, 28)), ("f16", 40, (96, 128), (30, 30))])
+def test_static_workspace_takes_the_tables_of_the_biases_in_turn(dtype, d, grid, agrid):
+    """Many agents, whose tables do not fit the array at once."""
+    import torch
+    from paper_2312_08874_amd import binding as aa
+    wl = dataclasses.replace(WL["tiny"], batch=1, heads=8, grid=grid, agent_grid=agrid, d=d, dtype=dtype, index=26)
+    dv = _dev(wl)
+    host = inputs.make_module_params(wl.heads, wl.n, d, grid, blk=(7, 7), index=26)
+    params = util.params_to_device(host)
+    desc = aa.make_desc(1, wl.heads, wl.N, wl.n, d, aa._dtype_code(dv["Q"]), grid, agrid)
+    assert aa.workspace_bytes(desc, aa.make_params(params)) > aa.static_scratch_bytes()
+    kw = dict(grid=grid, agent_grid=agrid, params=params)
+    ref = aa.agent_attn_fwd(dv["Q"], dv["K"], dv["V"], **kw)
+    out = torch.full_like(dv["Q"], 3.0)
+    for _ in range(2):
+        aa.agent_attn_fwd_static(dv["Q"], dv["K"], dv["V"], out=out, **kw)
+        assert torch.equal(out, ref)
+
+
 def test_static_workspace_rejects_oversized_problems():
     import torch
     from paper_2312_08874_amd import binding as aa
