@@ -230,7 +230,8 @@ aa_status agent_broadcast_fwd(const aa_desc *desc, const void *Q, const void *A,
  * used and keep no attention matrix in memory, module terms included; strided tensors
  * and windows are read where they lie.  For 16-bit problems without agent bias and DWC
  * the workspace is then a few n*d and N-long arrays per unit and the partial sums of
- * the split token ranges.  Every other problem (other widths, fp32 or module terms on
+ * the split token ranges and, for up to 64 agents on an agent grid and fewer than 2^30
+ * elements, dQ in fp32 (N*d floats per unit).  Every other problem (other widths, fp32 or module terms on
  * unaligned tensors) runs reference-quality kernels that materialise both attention
  * matrices in the workspace: about 4*n*N + 7*N*d + 4*n*d floats per unit, which the
  * query also covers for fp32 problems and for 16-bit problems with module terms.

@@ -322,7 +322,7 @@ FusedPlan fused_plan(const Problem& p, bool forward = false) {
     if (!f32 && (f.bias[0] || f.bias[1])) f.large = o, o += up64(2 * u);
     f.D2 = o, o += uN;
     f.dAf = o, o += u * nd;
-    if (f.both[0] && !f32) f.dQf = o, o += up64(u * p.N * p.d);
+    if (f.both[0] && !f32 && p.ah > 0) f.dQf = o, o += up64(u * p.N * p.d);      // (no agent grid, no pooling term to wait for)
   }
   const size_t H = (size_t)p.heads, wp = 16 * (size_t)xts;
   for (int k = 0; k < 2; ++k) {

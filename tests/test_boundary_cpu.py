@@ -241,6 +241,15 @@ def test_bwd_workspace_of_the_largest_workload():
                                                                    (32, 32))), None) > 2e9
 
 
+def test_bwd_workspace_holds_dQ_only_where_its_pooling_term_is_to_come():
+    """16 bits, at most 64 agents: dQ waits in fp32 for the pooling term; without an agent grid the agents are handed in and have none."""
+    def need(n, grid, dtype=binding.AA_BF16):
+        return binding.lib().agent_attn_bwd_workspace_bytes(ctypes.byref(make_desc(8, 3, 3136, n, 32, dtype, (56, 56), grid)), None)
+    dQ = 8 * 3 * 3136 * 32 * 4
+    assert need(49, (7, 7)) - need(49, None) == dQ
+    assert need(81, (9, 9)) == need(81, None) and need(49, (7, 7), binding.AA_F32) == need(49, None, binding.AA_F32)
+
+
 @pytest.mark.parametrize("heads,side,d", [(1, 4096, 64), (64, 1024, 64), (3, 4096, 128)])
 def test_bwd_workspace_of_very_large_tensors(heads, side, d):
     """Pure 16-bit problems whose units or images pass 2^30 and 2^32 elements keep no attention matrix either: a few
