@@ -10,10 +10,9 @@
 // then stands for channel 4g + j in BOTH operands, so the contraction is merely taken in another order.
 // The same trick turns the C registers of a score tile (rows = 4 consecutive tokens or agents per lane)
 // into the B operand of the following value product without any data movement.
-#include <algorithm>
-
 #include "kernels.h"
 #include "mfma_common.h"
+#include "split_rules.h"
 
 namespace aa {
 
@@ -365,23 +364,18 @@ hipError_t launch_fused_f32(const Problem& p, const void* Q, const void* K, cons
   const int nat = (p.n + 15) / 16, dt = (p.d + 15) / 16;
   const int S = fused_f32_slices(p);
   const bool mod = p.dwc_w != nullptr || p.vk != 0.0f;
-  // Blocks per unit: while CUs are idle, further blocks repeat what comes before the broadcast and share out its tiles of 16 tokens,
-  // down to one per SIMD, and the channels of V, one 16-channel tile each (or two of four).  The same sums in the same order.
-  // 1 unit of 196 tokens x 49 agents, d = 32: 15.0 us in one block, 11.8 in four, 10.5 in eight (tiles and channels).
-  const int ntiles = (p.N + 15) / 16, share = (ntiles - 1) / std::max(1, std::min((ntiles + 3) / 4, kComputeUnits / p.units)) + 1;
-  const int parts = (ntiles - 1) / share + 1;
-  int ct = 1;
-  while (ct < dt && (dt % ct != 0 || dt / ct * parts * p.units > kComputeUnits)) ++ct;
+  const UnitShares split = fused_f32_shares(p.N, p.d, p.units, kComputeUnits);
+  const int ct = split.channel_tiles;
   const size_t lds = fused_f32_lds(p.N, nat, dt, ct, S);
   hipError_t err = hipErrorInvalidValue;
   auto launch = [&](auto kernel) {
     err = allow_lds(kernel, lds);
     if (err == hipSuccess)
-      kernel<<<dim3(p.units, parts, dt / ct), dim3(64 * kF32Waves), lds, st>>>(
+      kernel<<<dim3(p.units, split.parts, dt / ct), dim3(64 * kF32Waves), lds, st>>>(
           (const float*)Q, (const float*)K, (const float*)V, (const float*)A, (float*)out, p.dwc_w, p.dwc_b, p.scale1, p.scale2, p.vk, p.N,
-          p.n, p.d, p.heads, p.lay, p.gh, p.gw, p.ah, p.aw, S, share);
+          p.n, p.d, p.heads, p.lay, p.gh, p.gw, p.ah, p.aw, S, split.tiles);
   };
-  const int tiles = parts == 1 && ct == dt ? 0 : ct;
+  const int tiles = split.parts == 1 && ct == dt ? 0 : ct;
 #define AA_F32_TILES(NAT, DT, CT)                                                     \
   if (nat == NAT && dt == DT && tiles == CT) {                                        \
     if (mod) launch(fused_f32_kernel<NAT, DT, true, CT>);                             \

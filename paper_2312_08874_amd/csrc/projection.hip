@@ -11,6 +11,7 @@
 // 15 + 15 -> 18.8 -> 15.2.
 #include "kernels.h"
 #include "mfma_common.h"
+#include "split_rules.h"
 
 #include <algorithm>
 
@@ -18,14 +19,12 @@ namespace aa {
 
 namespace {
 
-
 struct ProjArgs {
   const uint16_t *X, *W, *b;
   uint16_t* Y;
   int M, O, K;
   ProjRows x, y;
   XcdGrid grid;
-  long long bytes() const { return 2ll * M * (K + O); }      // of X and Y
 };
 
 // Where row m (token m % tokens of image m / tokens) lies: a base for the rows from m0 on and this row's offset from it
@@ -178,37 +177,20 @@ hipError_t launch(ProjArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Columns per block: the least padded width, a column of a narrower block priced higher: it takes 8 / 12 (96) or 6 / 8 (64)
-// LDS reads per product where 128 takes 8 / 16.
 template <class E, int BM, int KS>
-hipError_t columns(ProjArgs& a, hipStream_t st) {
-  auto price = [&](int bn, int per_column) { return (long long)((a.O + bn - 1) / bn) * bn * per_column; };
-  const long long p128 = price(128, 10), p96 = price(96, 12), p64 = price(64, 13);
-  if (p128 <= p96 && p128 <= p64) {
-    // X and Y beyond three quarters of the 256 MB that caches keep: the loads are longer under way, and blocks of 256 rows with
-    // two steps of 32 channels ahead do better.  100352 rows, q | k | v of width 256: 81.5 us in the blocks below, 75.8; of
-    // 384: 149, 138.5; 25088 rows, width 1024: 200, 188; but width 768 (147 MB): 115, 116 to 123.
-    if (BM == 128 && KS == 64 && a.bytes() > (192ll << 20)) return launch<E, 256, 128, 8, 2, 32, 3>(a, st);
-    return launch<E, BM, 128, 4, 2, KS, 2>(a, st);
-  }
-  return p96 <= p64 ? launch<E, BM, 96, 4, 1, KS, 2>(a, st) : launch<E, BM, 64, 4, 2, KS, 2>(a, st);
+hipError_t columns(ProjArgs& a, int outputs, hipStream_t st) {
+  if (outputs == 128) return launch<E, BM, 128, 4, 2, KS, 2>(a, st);
+  if (outputs == 96) return launch<E, BM, 96, 4, 1, KS, 2>(a, st);
+  if constexpr (KS == 32) return launch<E, BM, 64, 4, 2, KS, 2>(a, st);
+  return hipErrorInvalidValue;
 }
 
 template <class E>
 hipError_t dispatch(ProjArgs& a, hipStream_t st) {
-  // Channels per step: 64 ask for whole 128-byte lines (16384 rows, width 512: 41.7 us, 47.0 with steps of 32).  32 where four to
-  // five blocks a CU do more: up to a width of 96 (100352 rows, width 96: 18.7 us, 22.5 with steps of 64), and below 256 where
-  // the last 64 would be half empty (width 160: 32.4, 38.2) or from memory (100352 rows, width 192: 50.8 + 20.5, 52.9 + 21.8;
-  // 25088 rows: 17.1 + 7.9, 15.5 + 7.5).
-  const bool half = a.K < 128 || (a.K < 256 && ((a.K - 1) % 64 < 32 || a.bytes() > (64ll << 20)));
-  // Rows per block: 64 while blocks of 128 would leave CUs at less than half of what they hold (784 rows, width 512: 11.1 ->
-  // 9.0 us; 6272 rows, output of width 512: 10.0 -> 8.4; but q | k | v of width 256, 294 blocks: 10.2, 12.2 with 64 rows), and
-  // where two a CU leave a few for a second round, for which three blocks of 64 rows a CU are shorter (14 products of 517 to
-  // 588 blocks of 128 rows 0.85 to 0.97 of the time: 18000 rows, width 512, output 18.4 -> 16.6).
-  const long long tall = (long long)((a.M + 127) / 128) * ((a.O + 127) / 128);
-  if (half) return tall < 2 * kComputeUnits ? columns<E, 64, 32>(a, st) : columns<E, 128, 32>(a, st);
-  const bool few = tall < kComputeUnits || (tall > 2 * kComputeUnits && tall <= 5 * kComputeUnits / 2);
-  return few ? columns<E, 64, 64>(a, st) : columns<E, 128, 64>(a, st);
+  const ProjectionBlocks b = projection_blocks(a.M, a.O, a.K, kComputeUnits);
+  if (b.rows == 256) return launch<E, 256, 128, 8, 2, 32, 3>(a, st);
+  if (b.step == 32) return b.rows == 64 ? columns<E, 64, 32>(a, b.outputs, st) : columns<E, 128, 32>(a, b.outputs, st);
+  return b.rows == 64 ? columns<E, 64, 64>(a, b.outputs, st) : columns<E, 128, 64>(a, b.outputs, st);
 }
 
 }  // namespace

@@ -71,3 +71,26 @@ def test_aggregation_in_columns(rules, grid, n, d, cells, columns):
 def test_aggregation_offsets_fit_32_bits(rules):
     assert rules.large_aggregate_columns(128, 1 << 16, 64, 512, 7) and not rules.large_aggregate_columns(128, 1 << 16, 64, 512, 16)
     assert not rules.large_aggregate_columns(128, 1 << 20, 512, 16, 7) and rules.large_aggregate_columns(128, 1 << 20, 508, 16, 7)
+
+
+def test_the_blocks_of_the_projections_are_those_their_tests_name(rules):
+    """Every product of the edge cases runs on the blocks that its case says, and between them on every kernel that the rule can choose."""
+    from .test_gpu_parity import PROJECTION_CASES
+    named = set()
+    for name, batch, heads, d, grid, _, _, _, blocks in PROJECTION_CASES:
+        C = heads * d
+        if blocks:
+            assert [columns_rule.projection_blocks(rules, batch * grid[0] * grid[1], O, C) for O in (3 * C, C)] == blocks, name
+            named.update(blocks)
+    chosen = {columns_rule.projection_blocks(rules, M, O, C) for C in range(8, 1032, 8) for O in (3 * C, C)
+              for M in (1, 784, 3136, 9216, 18000, 33496, 42008, 100352, 200704)}
+    assert named == chosen and len(chosen) == 11
+
+
+def test_the_shares_of_fp32_units_are_those_their_test_names(rules):
+    """... and between them every number of 16-channel tiles a block can take, of one to four, and one block and several along the tokens."""
+    from .test_gpu_fp32_shares import CASES
+    assert [columns_rule.fused_f32_shares(rules, grid[0] * grid[1], d, units) for grid, _, d, units, _ in CASES] == [c[4] for c in CASES]
+    builds = {((d + 15) // 16, 0 if split == (1, (d + 15) // 16) else split[1]) for _, _, d, _, split in CASES}
+    assert builds >= {(dt, ct) for dt in (1, 2, 3, 4) for ct in range(1, dt + 1) if dt % ct == 0}
+    assert [columns_rule.fused_f32_shares(rules, 196, 64, units) for units in (1, 64, 128, 256, 1000)] == [(4, 1), (4, 4), (2, 4), (1, 4), (1, 4)]

@@ -16,11 +16,29 @@ def aa():
     return binding
 
 
-# one tile of tokens; four and five (one block, two); a ragged last tile; channels that end inside a tile; two of four tiles a block
-@pytest.mark.parametrize("grid,agrid,d,units", [((3, 5), (2, 2), 16, 1), ((8, 8), (4, 4), 32, 1), ((13, 5), (5, 3), 20, 3), ((14, 14), (7, 7), 32, 1),
-                                                ((11, 13), (7, 7), 48, 2), ((10, 10), (8, 8), 64, 1), ((9, 9), (3, 3), 64, 30), ((14, 14), (7, 7), 16, 200)])
+# (blocks along the tokens, 16-channel tiles a block takes) by the rule (split_rules.h): whole units first and last (one block, its own
+# code), then one tile of one to four, two of two and four, three of three, four of four, ragged last tiles and shares, channels that
+# end inside a tile
+CASES = [
+    ((3, 5), (2, 2), 16, 1, (1, 1)),
+    ((8, 8), (4, 4), 32, 1, (1, 1)),
+    ((13, 5), (5, 3), 20, 3, (2, 1)),
+    ((14, 14), (7, 7), 16, 4, (4, 1)),
+    ((14, 14), (7, 7), 32, 1, (4, 1)),
+    ((11, 13), (7, 7), 48, 2, (3, 1)),
+    ((10, 10), (8, 8), 64, 1, (2, 1)),
+    ((9, 9), (3, 3), 64, 30, (2, 1)),
+    ((14, 14), (7, 7), 32, 100, (2, 2)),
+    ((9, 9), (3, 3), 64, 40, (2, 2)),
+    ((11, 13), (7, 7), 48, 100, (2, 3)),
+    ((9, 9), (3, 3), 64, 100, (2, 4)),
+    ((14, 14), (7, 7), 16, 200, (1, 1)),
+]
+
+
+@pytest.mark.parametrize("grid,agrid,d,units,split", CASES)
 @pytest.mark.parametrize("module,given", [(False, False), (True, False), (False, True)])
-def test_shares_equal_whole_units(aa, oracle, grid, agrid, d, units, module, given):
+def test_shares_equal_whole_units(aa, oracle, grid, agrid, d, units, split, module, given):
     rng = np.random.default_rng(units + d)
     N, n = grid[0] * grid[1], agrid[0] * agrid[1]
     q, k, v = (rng.standard_normal((units, 1, N, d)).astype(np.float32) for _ in range(3))

@@ -746,29 +746,32 @@ def test_module_with_projections(aa, oracle, name, batch, heads, d, grid, window
     assert np.abs(ref - ref2).max() > 1e-3
 
 
-# rows and widths on and off the blocks of the projection kernel (256, 128 or 64 rows; 128, 96 or 64 outputs; steps of 64
-# or 32 channels), windows that are staged for the few-agents and for the many-agents kernels, and the library's product
+# rows and widths on and off the blocks of the projection kernel, windows that are staged for the few-agents and for the many-agents
+# kernels, and the library's product.  blocks: (rows, outputs, channels a step) of the two products by the dispatch rule (split_rules.h)
 PROJECTION_CASES = [
-    ("width 8", 1, 1, 8, (9, 7), None, (2, 2), "f16", True),
-    ("width 80, many agents, windows", 2, 2, 40, (40, 16), (20, 16), (9, 9), "bf16", True),
-    ("width 96, few agents, windows", 2, 3, 32, (28, 56), (28, 28), (7, 7), "f16", True),
-    ("blocks of 128 rows, 96 and 64 outputs", 8, 2, 16, (97, 95), None, (3, 3), "bf16", True),
-    ("blocks of 128 rows, 128 outputs", 8, 4, 32, (97, 95), None, (3, 3), "f16", True),
-    ("steps of 64 channels, blocks of 64 rows, the last step part full", 1, 29, 8, (19, 7), None, (3, 3), "bf16", True),
-    ("steps of 64 channels, blocks of 128 rows, windows", 4, 4, 64, (56, 28), (28, 28), (7, 7), "f16", True),
-    ("steps of 64 channels, 64 outputs", 1, 5, 64, (23, 21), None, (3, 3), "f16", True),
-    ("steps of 64 channels, 96 outputs, blocks of 128 rows", 8, 6, 32, (79, 53), None, (3, 3), "bf16", True),
-    ("past the caches: blocks of 256 rows", 8, 4, 64, (111, 111), None, (3, 3), "bf16", True),
-    ("unaligned rows", 1, 3, 12, (11, 9), None, (3, 3), "bf16", True),
-    ("unaligned weights", 1, 2, 32, (14, 14), None, (7, 7), "bf16", False),
+    # name, batch, heads, d, grid, window, agent grid, dtype, blocks (None: tensors off 16 bytes, the library's product)
+    ("width 8", 1, 1, 8, (9, 7), None, (2, 2), "f16", [(64, 64, 32), (64, 64, 32)]),
+    ("width 80, many agents, windows", 2, 2, 40, (40, 16), (20, 16), (9, 9), "bf16", [(64, 128, 32), (64, 96, 32)]),
+    ("width 96, few agents, windows", 2, 3, 32, (28, 56), (28, 28), (7, 7), "f16", [(64, 96, 32), (64, 96, 32)]),
+    ("blocks of 128 rows, 96 and 64 outputs", 8, 2, 16, (97, 95), None, (3, 3), "bf16", [(128, 96, 32), (128, 64, 32)]),
+    ("blocks of 128 rows, 128 outputs", 8, 4, 32, (97, 95), None, (3, 3), "f16", [(128, 128, 32), (64, 128, 64)]),
+    ("steps of 64 channels, blocks of 64 rows, the last step part full", 1, 29, 8, (19, 7), None, (3, 3), "bf16", [(64, 128, 64), (64, 128, 64)]),
+    ("steps of 64 channels, blocks of 128 rows, windows", 4, 4, 64, (56, 28), (28, 28), (7, 7), "f16", [(128, 128, 64), (64, 128, 64)]),
+    ("steps of 64 channels, half a block of outputs", 1, 5, 64, (23, 21), None, (3, 3), "f16", [(64, 128, 64), (64, 128, 64)]),
+    ("steps of 64 channels, a few blocks of 128 rows past two a CU", 8, 6, 32, (79, 53), None, (3, 3), "bf16", [(128, 128, 64), (64, 96, 64)]),
+    ("steps of 64 channels, 96 outputs, blocks of 128 rows", 8, 6, 32, (89, 59), None, (3, 3), "bf16", [(128, 128, 64), (128, 96, 64)]),
+    ("past the caches: blocks of 256 rows", 8, 4, 64, (111, 111), None, (3, 3), "bf16", [(256, 128, 32), (128, 128, 64)]),
+    ("unaligned rows", 1, 3, 12, (11, 9), None, (3, 3), "bf16", None),
+    ("unaligned weights", 1, 2, 32, (14, 14), None, (7, 7), "bf16", None),
 ]
 
 
-@pytest.mark.parametrize("name,batch,heads,d,grid,window,agrid,dtype,aligned", PROJECTION_CASES,
+@pytest.mark.parametrize("name,batch,heads,d,grid,window,agrid,dtype,blocks", PROJECTION_CASES,
                          ids=[c[0] for c in PROJECTION_CASES])
-def test_projection_kernel_edges(aa, oracle, name, batch, heads, d, grid, window, agrid, dtype, aligned):
+def test_projection_kernel_edges(aa, oracle, name, batch, heads, d, grid, window, agrid, dtype, blocks):
     import torch
     C, T = heads * d, grid[0] * grid[1]
+    aligned = name != "unaligned weights"
     mk = lambda shape, stream, std: inputs.make_tensor(shape, stream=930 + stream, std=std, dtype=dtype)
     x = mk((batch, T, C), 0, 1.0)
     w_qkv, b_qkv = mk((3 * C, C), 1, C ** -0.5), mk((3 * C,), 2, 0.5)
