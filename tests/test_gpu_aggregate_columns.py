@@ -9,6 +9,7 @@ import pytest
 
 from paper_2312_08874_amd import inputs
 from . import columns_rule, util
+from .test_gpu_broadcast_columns import _layouts
 
 pytestmark = pytest.mark.gpu
 
@@ -71,6 +72,23 @@ def test_aggregation_in_columns_of_many_agents(aa, oracle, rules, grid, agrid, b
 def test_aggregation_in_columns_splits(aa, oracle, rules, grid, agrid, d, n_splits):
     """Splits that begin inside a strip, and inside a cell row."""
     _forward(aa, oracle, rules, grid, agrid, (5, 3), (), "bf16", d, units=(1, 2), n_splits=n_splits, tables=n_splits == 5)
+
+
+@pytest.mark.parametrize("dtype,d,grid,agrid", [("bf16", 64, (70, 28), (20, 13)), ("f16", 40, (83, 44), (20, 20)), ("f16", 32, (70, 28), (20, 13)),
+                                                ("bf16", 24, (41, 36), (17, 17)), ("bf16", 128, (23, 28), (11, 9))])
+def test_aggregation_in_columns_layouts(aa, rules, dtype, d, grid, agrid):
+    """Token-major tensors, slices of a fused projection and padded outputs have the dense call's values, bit for bit."""
+    import torch
+    blk = (3, 2) if grid[0] == 41 else (7, 7)
+    wl = dataclasses.replace(inputs.WORKLOADS["tiny"], batch=2, heads=2, grid=grid, agent_grid=agrid, d=d, dtype=dtype, index=27)
+    assert columns_rule.aggregate_columns(rules, grid, wl.n, d, blk[0])
+    t = inputs.make_qkv(wl)
+    kw = dict(grid=grid, agent_grid=agrid, v_residual_k=0.25,
+              params=util.params_to_device(inputs.make_module_params(2, wl.n, d, grid, blk=blk, index=27)))
+    dense = aa.agent_attn_fwd(*(util.to_device(t[k], dtype, (2, 2, wl.N, d)) for k in ("Q", "K", "V")), **kw)
+    for name, q, k, v, out in _layouts(t, 2, 2, wl.N, d, dtype):
+        aa.agent_attn_fwd(q, k, v, out=out, **kw)
+        assert torch.equal(out, dense), name
 
 
 @pytest.mark.parametrize("value", [-1e9, float(np.finfo(np.float32).min), -np.inf])

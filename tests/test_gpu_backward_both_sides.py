@@ -29,6 +29,60 @@ def test_both_sides_of_one_unit_in_many_ranges(aa, oracle, given, module, dtype,
               kw=RESIDUAL)
 
 
+PLACES = [((17, 19), (4, 4), 32), ((14, 13), (4, 8), 64), ((12, 21), (5, 9), 48), ((16, 20), (8, 8), 40)]
+
+
+def _tensors(grid, d, dtype, batch, heads, index):
+    from . import util
+    wl = _wl("places", dtype, grid, (1, 1), d, batch=batch, heads=heads, index=index)
+    shape = (batch, heads, wl.N, d)
+    t = [util.to_device(v, dtype, shape) for v in inputs.make_qkv(wl).values()]
+    return t + [util.to_device(inputs.make_tensor((batch * heads, wl.N, d), stream=index * 16 + 12, dtype=dtype), dtype, shape)]
+
+
+def _params(module, heads, n, d, grid):
+    from . import util
+    return dict(params=util.params_to_device(inputs.make_module_params(heads, n, d, grid, blk=(3, 2), index=66)) if module else None)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("module", [False, True])
+@pytest.mark.parametrize("grid,agrid,d", PLACES)
+def test_both_sides_of_strided_tensors(aa, grid, agrid, d, module, dtype):  # noqa: F811
+    """Token-major tensors and slices of a fused projection have the dense call's gradients, bit for bit."""
+    import torch
+    dense = _tensors(grid, d, dtype, 2, 2, 66)
+    kw = dict(grid=grid, agent_grid=agrid, v_residual_k=0.075, **_params(module, 2, agrid[0] * agrid[1], d, grid))
+    ref = aa.agent_attn_bwd(*dense, **kw)
+    major = [x.permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3) for x in dense]
+    fused = torch.stack([x.permute(0, 2, 1, 3) for x in dense[:3]], dim=2).contiguous()
+    for q, k, v, g in (major, [fused[:, :, i].permute(0, 2, 1, 3) for i in range(3)] + [major[3]], [fused[:, :, i].permute(0, 2, 1, 3) for i in range(3)] + [dense[3]]):
+        got = aa.agent_attn_bwd(q, k, v, g, **kw)
+        assert ref.keys() == got.keys() and all(torch.equal(got[key], ref[key]) for key in ref)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("module", [False, True])
+@pytest.mark.parametrize("token_major", [False, True])
+@pytest.mark.parametrize("window,agrid,d", PLACES)
+def test_both_sides_of_windows(aa, window, agrid, d, token_major, module, dtype):  # noqa: F811
+    """2 x 3 windows read where they lie have the gradients of window-major copies, bit for bit."""
+    import torch
+    (h, w), B, H = window, 2, 2
+    image = _tensors((2 * h, 3 * w), d, dtype, B, H, 67)
+    kw = dict(agent_grid=agrid, v_residual_k=0.075, **_params(module, H, agrid[0] * agrid[1], d, window))
+
+    def part(x):
+        return x.reshape(B, H, 2, h, 3, w, d).permute(0, 2, 4, 1, 3, 5, 6).reshape(B * 6, H, h * w, d).contiguous()
+    ref = aa.agent_attn_bwd(*(part(x) for x in image), grid=window, **kw)
+    if token_major:
+        image = [x.permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3) for x in image]
+    got = aa.agent_attn_bwd(*image, grid=(2 * h, 3 * w), window=window, **kw)
+    assert ref.keys() == got.keys()
+    for key in ref:
+        assert torch.equal(part(got[key]) if key in ("dQ", "dK", "dV") else got[key], ref[key]), key
+
+
 @pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
 @pytest.mark.parametrize("value", [float("nan"), float("inf")])
 @pytest.mark.parametrize("n,d", [(16, 32), (49, 64), (64, 48), (33, 128)])

@@ -125,14 +125,14 @@ def test_broadcast_in_columns_layouts(aa, oracle, rules, dtype, d):
         assert torch.equal(out, dense), name
 
 
-# Half-resized tables of both kinds made in runs of cell rows: 1024 wave tiles and more of a kind's table in one cell row each are
-# shared out so that 1024 waves are left (kind 1 at widths padded to 32 and 128; at 64 its block component has another form)
+# Half-resized tables of both kinds made in runs of cell rows, as many as leave a block per CU (kind 1 at widths padded to 32 and
+# 128; at 64 its block component has another form)
 @pytest.mark.parametrize("dtype,d", [("bf16", 32), ("f16", 96)])
 @pytest.mark.parametrize("blk,runs", [((7, 7), 3), ((5, 3), 2)])
 def test_half_resized_tables_in_runs(aa, oracle, blk, runs, dtype, d):
     grid, agrid, heads = (64, 64), (16, 16), 8
-    tiles = heads * blk[0] * (64 // 4 // 8) * (256 // 8)      # kind 1; kind 2 has as many: 64 / 8 of 256 / 32
-    assert tiles // 1024 == runs and blk[0] % runs == 1
+    blocks = heads * blk[0] * (256 // 64) * (64 // 16)      # of 64 agents x 16 columns of a cell row; kind 2: 64 columns x 16 agents
+    assert blocks // 2 < 512 and blocks // 256 == runs and blk[0] % runs == 1      # (blocks of 32 would leave fewer than two a CU)
     wl = dataclasses.replace(inputs.WORKLOADS["tiny"], batch=1, heads=heads, grid=grid, agent_grid=agrid, d=d, dtype=dtype, index=19)
     t = inputs.make_qkv(wl)
     params = inputs.make_module_params(heads, wl.n, d, grid, blk=blk, index=19)
