@@ -162,7 +162,7 @@ __global__ __launch_bounds__(kThreads) void fused_reduce_agg_kernel(SumRows g, c
 // null: dQ itself, in fp32).  dA = dAf + c1 * sum of the ranges of pa (S of them; none: dAf is complete) is finished here, in
 // LDS, by every block of a unit.  A block takes 256 tokens: their places in the pooling grid are found once each (a dozen
 // divisions), then a thread takes 16 bytes of a row.  Memory bounds it, most of all the way there: what a block reads is asked
-// for ahead of everything else, and no block takes a second turn.
+// for ahead of everything else, all of it up to 32 channels (128 bytes of fp32 a thread; above, a turn for every 32).
 // ---------------------------------------------------------------------------
 struct PoolOutArgs {
   const float *src, *dAf, *pa;
